@@ -64,12 +64,16 @@ typedef struct {
     int32_t wg_size;      /* threads per workgroup, multiple of 64 (<= 1024) */
     int32_t wg_count;     /* workgroups; 0 = the call's default: queue
                              benchmarks fill the chip (occupancy x CUs);
-                             sssp_bf and sssp_bf_batched take about one per
-                             16K units of n + m/16 (per query, at least one),
-                             up to the co-resident maximum */
+                             sssp_bf takes about one (of 16 waves) per 128
+                             units of n + m/16, at most one per CU; with
+                             buckets or a timeline one (of 2 waves) per 8K
+                             units; sssp_bf_batched about one per 16K units
+                             (per query, at least one), up to the co-resident
+                             maximum */
     int32_t ticket_batch; /* b: a wave dequeues up to 64*b items per ticket;
                              0 = 1; the solvers take 1, 2 or 4 (BQ_EINVAL
-                             otherwise: their LDS staging grows with b) */
+                             otherwise: their LDS staging grows with b); the
+                             sweeps of sssp_bf size their batches themselves */
     uint32_t flags;       /* BQ_F_* */
     uint64_t timeout_us;  /* watchdog for a single wait; 0 = 2 s. A solve
                              running longer than 10x this is stopped too
@@ -82,10 +86,11 @@ typedef struct {
                              pow2(queue_scale * (n + m/row_chunk + 1)) slots,
                              1 or 2; 0 = 2 */
     int32_t segments;     /* sssp_bf: the queue is split into this many
-                             Broker Queues (1..8, one per XCD), workgroup i
-                             publishing to segment i mod segments and taking
-                             from the fullest other segment when its own is
-                             empty; 0 = min(8, workgroups). Forced to 1 with
+                             segments (1..8, one per XCD), workgroup i
+                             publishing to segment i mod segments; a sweep
+                             takes the items of all of them, and with buckets
+                             a wave takes from the fullest other segment when
+                             its own is empty; 0 = min(8, workgroups). Forced to 1 with
                              BQ_F_TRACE. bq_bench_mixed / bq_bench_enqdeq:
                              1, 2, 4 or 8 segments of capacity/segments
                              slots (0 = 1). Other calls ignore it. */

@@ -14,6 +14,7 @@
 #include "csr_device.hpp"
 #include "host_common.hpp"
 #include "sssp_kernels.hpp"
+#include "sssp_sweep.hpp"
 
 
 // ---------------------------------------------------------------------------
@@ -37,6 +38,9 @@ struct sssp_ctx {
     bool dirty;        // queue state must be rebuilt before the next solve
     sssp_stats last;
     int solve_per_cu[3];
+    // sweep form: its words, buffers and stamps (sweep_layout)
+    char* sweep_mem;
+    int sweep_per_cu;
 };
 
 namespace {
@@ -136,6 +140,71 @@ bq_status max_grid_for(sssp_ctx* c, int batch, int* out) {
     }
 }
 
+// The sweep form runs every query but those that ask for near / far buckets
+// or a timeline of the queue.
+bool sweeps(const bqh::Launch& L) {
+    return L.bucket_width == 0 && (L.flags & BQ_F_TRACE) == 0;
+}
+
+// Chunk items one buffer's segment holds at most: a row longer than C gives
+// ceil(degree / C) <= 2 degree / C of them.
+unsigned long long sweep_chunk_cap(long long m, unsigned chunk_log) {
+    return 2ull * ((unsigned long long)m >> chunk_log) + 64ull;
+}
+
+// Memory of a sweep solve, carved from `base` (256-byte aligned): words, the
+// light and chunk items of the two buffers, the stamps. Returns its size.
+unsigned long long sweep_layout(char* base, int n, long long m, unsigned chunk_log, int nseg,
+                                SweepArgs* f) {
+    unsigned long long at = 0;
+    auto take = [&](unsigned long long bytes) {
+        char* p = base + at;
+        at += (bytes + 255ull) & ~255ull;
+        return p;
+    };
+    const unsigned long long cl = (unsigned long long)n, cc = sweep_chunk_cap(m, chunk_log);
+    SweepArgs t;
+    t.ctl = (decltype(t.ctl))take(sizeof(SweepCtl));
+    t.light = (decltype(t.light))take(4ull * 2ull * (unsigned long long)nseg * cl);
+    t.chunk = (decltype(t.chunk))take(8ull * 2ull * (unsigned long long)nseg * cc);
+    t.stamp = (decltype(t.stamp))take(4ull * cl);
+    t.cap_light = (unsigned)cl;
+    t.cap_chunk = (unsigned)cc;
+    if (f) *f = t;
+    return at;
+}
+
+// Default workgroups (16 waves each) of a sweep solve: about one per 128 units
+// of n + m/16, a power of two, at most one per CU; on graphs of short rows
+// (meshes: few vertices per sweep) at most half of that. A workgroup more
+// costs the barrier little, and the sweeps' round trips dominate until a wave
+// has its 64 items. Random graphs, solve in us at 8 / 32 / 128 / 256
+// workgroups: 2k vertices 146 / 127 / - / -, 20k 450 / 247 / 211 / -, 200k - /
+// 839 / 473 / 456; RMAT-20 at 64 / 128 / 256: 1746 / 1214 / 919; a 256 x 256
+// mesh at 64 / 128 / 256: 5433 / 5558 / 6185.
+int sweep_grid(int n, long long m, int max_grid) {
+    const unsigned long long units = (unsigned long long)n + (unsigned long long)m / 16ull;
+    const int cap = short_rows(n, m) ? max_grid / 2 : max_grid;
+    int g = 8;
+    while ((unsigned long long)g * 2ull * 128ull <= units && g * 2 <= cap) g *= 2;
+    return g < max_grid ? g : max_grid;
+}
+
+bq_status sweep_occupancy(int* per_cu) {
+    BQ_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_sweep, SWEEP_WG, 0));
+    if (*per_cu < 1) *per_cu = 1;
+    return BQ_OK;
+}
+
+// workgroups of k_init and k_sweep_init
+unsigned init_blocks(int n, long long m) {
+    const long long big = m > n ? m : n;
+    long long blocks = (big + (long long)INIT_WG * 8 - 1) / ((long long)INIT_WG * 8);
+    if (blocks < 1) blocks = 1;
+    if (blocks > INIT_MAX_BLOCKS) blocks = INIT_MAX_BLOCKS;
+    return (unsigned)blocks;
+}
+
 bq_status launch_solve(const SolveArgs& args, int batch, int grid, hipStream_t s) {
     constexpr int SU = SHORT_ROW_UNROLL;
     const bool sr = short_rows((long long)args.n, (long long)args.m);
@@ -192,6 +261,8 @@ bq_status sssp_ctx_create(int32_t max_n, int64_t max_m, sssp_ctx** out) {
         hipMalloc(&c->ctrl, sizeof(bq::Ctrl) * MAX_Q) != hipSuccess ||
         hipMalloc(&c->chunk_owner, sizeof(unsigned) * chunks) != hipSuccess ||
         hipMalloc(&c->wrange, sizeof(int) * 2 * INIT_MAX_BLOCKS) != hipSuccess ||
+        hipMalloc(&c->sweep_mem, sweep_layout(nullptr, max_n, max_m, MIN_CHUNK_LOG, MAX_SEG,
+                                              nullptr)) != hipSuccess ||
         hipHostMalloc(&c->h_ctrl, sizeof(bq::Ctrl), hipHostMallocDefault) != hipSuccess) {
         sssp_ctx_destroy(c);
         return BQ_ENOMEM;
@@ -219,6 +290,7 @@ bq_status sssp_ctx_destroy(sssp_ctx* c) {
     if (c->ctrl) (void)hipFree(c->ctrl);
     if (c->chunk_owner) (void)hipFree(c->chunk_owner);
     if (c->wrange) (void)hipFree(c->wrange);
+    if (c->sweep_mem) (void)hipFree(c->sweep_mem);
     if (c->h_ctrl) (void)hipHostFree(c->h_ctrl);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
@@ -444,12 +516,21 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
         BQ_HIP_TRY(hipStreamSynchronize(s));
         if (bad) return BQ_EINVAL;
     }
+    const bool sweep = sweeps(L);
     int max_grid = 0;
-    {
+    if (sweep) {
+        if (c->sweep_per_cu == 0) {
+            bq_status st = sweep_occupancy(&c->sweep_per_cu);
+            if (st != BQ_OK) return st;
+        }
+        max_grid = c->sweep_per_cu * bqh::device_cus();
+    } else {
         bq_status st = max_grid_for(c, L.batch, &max_grid);
         if (st != BQ_OK) return st;
     }
-    int grid = L.wg_count > 0 ? L.wg_count : default_grid(n, (long long)m, max_grid);
+    int grid = L.wg_count > 0 ? L.wg_count
+                              : (sweep ? sweep_grid(n, (long long)m, max_grid)
+                                       : default_grid(n, (long long)m, max_grid));
     if (grid > max_grid) grid = max_grid;  // all waves co-resident
     int nseg = L.segments > 0 ? L.segments : (grid < (int)MAX_SEG ? grid : (int)MAX_SEG);
     if (nseg > (int)MAX_SEG) return BQ_EINVAL;
@@ -495,18 +576,21 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
     }
 
     BQ_HIP_TRY(hipEventRecord(c->ev0, s));
-    {
-        const long long big = m > n ? m : n;
-        long long blocks = (big + (long long)INIT_WG * 8 - 1) / ((long long)INIT_WG * 8);
-        if (blocks < 1) blocks = 1;
-        if (blocks > INIT_MAX_BLOCKS) blocks = INIT_MAX_BLOCKS;
-        hipLaunchKernelGGL(k_init, dim3((unsigned)blocks), dim3(INIT_WG), 0, s, q,
+    if (sweep) {
+        SweepArgs f;
+        sweep_layout(c->sweep_mem, n, (long long)m, clog, nseg, &f);
+        hipLaunchKernelGGL(k_sweep_init, dim3(init_blocks(n, (long long)m)), dim3(INIT_WG), 0, s,
+                           a, f, c->wrange);
+        BQ_HIP_TRY(hipGetLastError());
+        BQ_HIP_TRY(hipEventRecord(c->evs0, s));
+        hipLaunchKernelGGL(k_sweep, dim3(grid), dim3(SWEEP_WG), 0, s, a, f);
+        BQ_HIP_TRY(hipGetLastError());
+    } else {
+        hipLaunchKernelGGL(k_init, dim3(init_blocks(n, (long long)m)), dim3(INIT_WG), 0, s, q,
                            (long long*)d_dist, n, src, shift, (const int*)d_w, (long long)m,
                            c->wrange);
         BQ_HIP_TRY(hipGetLastError());
-    }
-    BQ_HIP_TRY(hipEventRecord(c->evs0, s));
-    {
+        BQ_HIP_TRY(hipEventRecord(c->evs0, s));
         bq_status st = launch_solve(a, L.batch, grid, s);
         if (st != BQ_OK) return st;
     }
@@ -539,10 +623,11 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
     c->last.ms = ms;
     c->last.solve_ms = sms;
     c->last.grid = grid;
-    c->last.wg_size = SOLVE_WG_ONE;
+    c->last.wg_size = sweep ? SWEEP_WG : SOLVE_WG_ONE;
     const unsigned long long err = h->error.v;
     const bool neg = h->negcycle.v != 0ull;
-    if (err != 0ull || h->abort.v != 0ull) c->dirty = true;  // queue not quiescent
+    // a stopped asynchronous solve leaves its queue non-quiescent
+    if (!sweep && (err != 0ull || h->abort.v != 0ull)) c->dirty = true;
     if (err == bq::ERR_RANGE) return BQ_ERANGE;
     if (err == bq::ERR_FULL) return BQ_EOVERFLOW;
     if (err != 0ull) return BQ_ETIMEOUT;
@@ -570,7 +655,7 @@ __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 constexpr int NOALLOC_MAX_DEVICES = 64;
 std::mutex g_scratch_mu;
 unsigned char* g_scratch[NOALLOC_MAX_DEVICES];      // device address per device
-int g_scratch_per_cu[NOALLOC_MAX_DEVICES][3];        // occupancy of k_solve<64/128/256>
+int g_scratch_per_cu[NOALLOC_MAX_DEVICES][4];  // occupancy of k_solve<64/128/256>, k_sweep
 
 inline unsigned long long round256(unsigned long long x) { return (x + 255ull) & ~255ull; }
 
@@ -592,17 +677,18 @@ bq_status scratch_of_current_device(int* dev_out, unsigned char** out) {
     return BQ_OK;
 }
 
-bq_status noalloc_max_grid(int dev, int batch, int* out) {
-    const int slot = batch == 1 ? 0 : (batch == 2 ? 1 : 2);
+bq_status noalloc_max_grid(int dev, bool sweep, int batch, int* out) {
+    const int slot = sweep ? 3 : (batch == 1 ? 0 : (batch == 2 ? 1 : 2));
     int per_cu = 0;
     {
         std::lock_guard<std::mutex> lock(g_scratch_mu);
         per_cu = g_scratch_per_cu[dev][slot];
     }
     if (per_cu == 0) {
-        bq_status st = batch == 1 ? occupancy_of_solve<64>(&per_cu)
-                                  : (batch == 2 ? occupancy_of_solve<128>(&per_cu)
-                                                : occupancy_of_solve<256>(&per_cu));
+        bq_status st = slot == 3   ? sweep_occupancy(&per_cu)
+                       : slot == 0 ? occupancy_of_solve<64>(&per_cu)
+                       : slot == 1 ? occupancy_of_solve<128>(&per_cu)
+                                   : occupancy_of_solve<256>(&per_cu);
         if (st != BQ_OK) return st;
         std::lock_guard<std::mutex> lock(g_scratch_mu);
         g_scratch_per_cu[dev][slot] = per_cu;
@@ -641,6 +727,7 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
     bqh::Launch L = bqh::resolve(launch, 0);
     if (L.batch != 1 && L.batch != 2 && L.batch != 4) return BQ_EINVAL;
     if (L.flags & BQ_F_TRACE) return BQ_EINVAL;  // the timeline needs a context
+    const bool sweep = sweeps(L);
     hipStream_t s = bqh::as_stream(stream);
     int dev = 0;
     unsigned char* base = nullptr;
@@ -650,10 +737,12 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
     }
     int max_grid = 0;
     {
-        bq_status st = noalloc_max_grid(dev, L.batch, &max_grid);
+        bq_status st = noalloc_max_grid(dev, sweep, L.batch, &max_grid);
         if (st != BQ_OK) return st;
     }
-    int grid = L.wg_count > 0 ? L.wg_count : default_grid(n, (long long)m, max_grid);
+    int grid = L.wg_count > 0 ? L.wg_count
+                              : (sweep ? sweep_grid(n, (long long)m, max_grid)
+                                       : default_grid(n, (long long)m, max_grid));
     if (grid > max_grid) grid = max_grid;
     int nseg = L.segments > 0 ? L.segments : (grid < (int)MAX_SEG ? grid : (int)MAX_SEG);
     if (nseg > (int)MAX_SEG) return BQ_EINVAL;
@@ -680,15 +769,25 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
     unsigned* chunk_owner = (unsigned*)(base + ctrl_bytes + wr_bytes);
     unsigned long long* slots = (unsigned long long*)(base + ctrl_bytes + wr_bytes + ch_bytes);
 
-    // the array keeps the previous call's contents: clear the control
-    // blocks and the slots this call uses
-    hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, s, (unsigned long long*)ctrl,
-                       (unsigned long long)(ctrl_bytes / 8));
-    BQ_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_zero_words, dim3(grid_for((int)std::min<unsigned long long>(
-                                          slot_words / 8, (unsigned long long)INT_MAX))),
-                       dim3(256), 0, s, slots, slot_words);
-    BQ_HIP_TRY(hipGetLastError());
+    SweepArgs f{};
+    if (sweep) {
+        // the sweep form's buffers instead of slots, behind the partials; any
+        // input that passes the slots' limit above fits with one segment
+        char* at = (char*)base + ctrl_bytes + wr_bytes;
+        const unsigned long long room = NOALLOC_SCRATCH_BYTES - ctrl_bytes - wr_bytes;
+        while (nseg > 1 && sweep_layout(at, n, (long long)m, clog, nseg, &f) > room) nseg /= 2;
+        if (sweep_layout(at, n, (long long)m, clog, nseg, &f) > room) return BQ_EBUSY;
+    } else {
+        // the array keeps the previous call's contents: clear the control
+        // blocks and the slots this call uses
+        hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, s, (unsigned long long*)ctrl,
+                           (unsigned long long)(ctrl_bytes / 8));
+        BQ_HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL(k_zero_words, dim3(grid_for((int)std::min<unsigned long long>(
+                                              slot_words / 8, (unsigned long long)INT_MAX))),
+                           dim3(256), 0, s, slots, slot_words);
+        BQ_HIP_TRY(hipGetLastError());
+    }
 
     Queue q;
     q.slots = (decltype(q.slots))slots;
@@ -698,6 +797,10 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
     q.pad = 0;
     q.N = cap;
     if (L.flags & BQ_F_VALIDATE) {
+        if (sweep) {
+            hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, &ctrl->aux[3].v, 1ull);
+            BQ_HIP_TRY(hipGetLastError());
+        }
         hipLaunchKernelGGL(k_validate_csr,
                            dim3(grid_for((int)(m > n ? (m > INT_MAX ? INT_MAX : m) : n))),
                            dim3(256), 0, s, (const long long*)d_offsets, (const int*)d_cols, n,
@@ -737,17 +840,17 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
     a.tw = nullptr;
     a.orig = nullptr;
     a.pos = nullptr;
-    {
-        const long long big = m > n ? m : n;
-        long long blocks = (big + (long long)INIT_WG * 8 - 1) / ((long long)INIT_WG * 8);
-        if (blocks < 1) blocks = 1;
-        if (blocks > INIT_MAX_BLOCKS) blocks = INIT_MAX_BLOCKS;
-        hipLaunchKernelGGL(k_init, dim3((unsigned)blocks), dim3(INIT_WG), 0, s, q,
+    if (sweep) {
+        hipLaunchKernelGGL(k_sweep_init, dim3(init_blocks(n, (long long)m)), dim3(INIT_WG), 0, s,
+                           a, f, wrange);
+        BQ_HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL(k_sweep, dim3(grid), dim3(SWEEP_WG), 0, s, a, f);
+        BQ_HIP_TRY(hipGetLastError());
+    } else {
+        hipLaunchKernelGGL(k_init, dim3(init_blocks(n, (long long)m)), dim3(INIT_WG), 0, s, q,
                            (long long*)d_dist, n, src, shift, (const int*)d_w, (long long)m,
                            wrange);
         BQ_HIP_TRY(hipGetLastError());
-    }
-    {
         bq_status st = launch_solve(a, L.batch, grid, s);
         if (st != BQ_OK) return st;
     }

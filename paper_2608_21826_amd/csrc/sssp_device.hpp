@@ -440,6 +440,23 @@ __device__ long long min_edge(const SolveArgs& a, unsigned p, unsigned y) {
     return (long long)bq::bcast64((unsigned long long)best);
 }
 
+// Whether the lam parent steps from `hare` close a walk whose lightest edges
+// sum below zero. Wave-uniform.
+__device__ bool closed_walk_is_negative(const SolveArgs& a, unsigned hare, unsigned lam) {
+    const unsigned sent = (1u << (a.shift - 1u)) - 1u;
+    long long sum = 0;
+    unsigned y = hare;
+    for (unsigned i = 0; i < lam; ++i) {
+        const unsigned p = bq::bcast32(parent_of(a, (int)y));
+        if (p == sent) return false;
+        const long long wmin = min_edge(a, p, y);
+        if (wmin == LLONG_MAX) return false;
+        sum += wmin;
+        y = p;
+    }
+    return y == hare && sum < 0;
+}
+
 // Brent's cycle search on the parent pointers from x0; on a cycle, sum the
 // lightest edge of every parent step around it. Returns a vertex of a cycle
 // of negative weight, or -1. Wave-uniform.
@@ -461,18 +478,7 @@ __device__ int walk_finds_negative_cycle(const SolveArgs& a, int x0, unsigned bu
         if ((steps & 255u) == 0u && bq::aborted(a.q)) return -1;
     }
     if (hare == sent) return -1;
-    // verify: follow lam parent steps from hare, they must close the walk
-    long long sum = 0;
-    unsigned y = hare;
-    for (unsigned i = 0; i < lam; ++i) {
-        const unsigned p = bq::bcast32(parent_of(a, (int)y));
-        if (p == sent) return -1;
-        const long long wmin = min_edge(a, p, y);
-        if (wmin == LLONG_MAX) return -1;
-        sum += wmin;
-        y = p;
-    }
-    return (y == hare && sum < 0) ? (int)hare : -1;
+    return closed_walk_is_negative(a, hare, lam) ? (int)hare : -1;
 }
 
 // Per-workgroup parking of idle waves: one wave of the workgroup (the
