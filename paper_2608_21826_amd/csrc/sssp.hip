@@ -14,6 +14,7 @@
 #include "csr_device.hpp"
 #include "host_common.hpp"
 #include "sssp_kernels.hpp"
+#include "sssp_small.hpp"
 #include "sssp_sweep.hpp"
 
 
@@ -144,6 +145,29 @@ bq_status max_grid_for(sssp_ctx* c, int batch, int* out) {
 // or a timeline of the queue.
 bool sweeps(const bqh::Launch& L) {
     return L.bucket_width == 0 && (L.flags & BQ_F_TRACE) == 0;
+}
+
+// Graphs that one workgroup solves: their keys and queue fit one CU's LDS, and
+// one CU scans their edges in less time than the sweeps of a gang take to
+// meet. Solve in us against the gang's sweeps: random graphs of 8 edges per
+// vertex, 1k vertices 40 / 101, 2k 68 / 129, 4k 105 / 150, 5k 135 / 152, 6k
+// 190 / 159; RMAT of scale 10 (16 k edges) 84 / 97, of scale 12 (65 k edges)
+// 324 / 116. Meshes have many short sweeps, so there the limit is the LDS: a 64
+// x 64 grid takes 174 against 856 us, a 64 x 64 road mesh 262 against 1124.
+constexpr long long SMALL_MAX_M = 40960;
+bool is_small(int n, long long m, const bqh::Launch& L) {
+    return (unsigned)n <= SMALL_MAX_N && (m <= SMALL_MAX_M || short_rows(n, m)) &&
+           (L.flags & BQ_F_TRACE) == 0;
+}
+
+bq_status launch_small(const SolveArgs& a, int* pred, bq::Ctrl* h, hipStream_t s) {
+    const size_t lds = small_lds_bytes(a.n);
+    BQ_HIP_TRY(hipFuncSetAttribute((const void*)k_small,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)small_lds_bytes((int)SMALL_MAX_N)));
+    hipLaunchKernelGGL(k_small, dim3(1), dim3(SMALL_WG), lds, s, a, pred, h);
+    BQ_HIP_TRY(hipGetLastError());
+    return BQ_OK;
 }
 
 // Chunk items one buffer's segment holds at most: a row longer than C gives
@@ -516,9 +540,12 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
         BQ_HIP_TRY(hipStreamSynchronize(s));
         if (bad) return BQ_EINVAL;
     }
-    const bool sweep = sweeps(L);
+    const bool small = is_small(n, (long long)m, L);
+    const bool sweep = !small && sweeps(L);
     int max_grid = 0;
-    if (sweep) {
+    if (small) {
+        max_grid = 1;
+    } else if (sweep) {
         if (c->sweep_per_cu == 0) {
             bq_status st = sweep_occupancy(&c->sweep_per_cu);
             if (st != BQ_OK) return st;
@@ -576,7 +603,10 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
     }
 
     BQ_HIP_TRY(hipEventRecord(c->ev0, s));
-    if (sweep) {
+    if (small) {
+        bq_status st = launch_small(a, (int*)d_pred, c->h_ctrl, s);
+        if (st != BQ_OK) return st;
+    } else if (sweep) {
         SweepArgs f;
         sweep_layout(c->sweep_mem, n, (long long)m, clog, nseg, &f);
         hipLaunchKernelGGL(k_sweep_init, dim3(init_blocks(n, (long long)m)), dim3(INIT_WG), 0, s,
@@ -594,12 +624,15 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
         bq_status st = launch_solve(a, L.batch, grid, s);
         if (st != BQ_OK) return st;
     }
-    BQ_HIP_TRY(hipEventRecord(c->evs1, s));
-    hipLaunchKernelGGL(k_unpack, dim3(grid_for(n)), dim3(256), 0, s, (long long*)d_dist,
-                       (int*)d_pred, n, src, shift);
-    BQ_HIP_TRY(hipGetLastError());
+    if (!small) {
+        BQ_HIP_TRY(hipEventRecord(c->evs1, s));
+        hipLaunchKernelGGL(k_unpack, dim3(grid_for(n)), dim3(256), 0, s, (long long*)d_dist,
+                           (int*)d_pred, n, src, shift);
+        BQ_HIP_TRY(hipGetLastError());
+    }
     BQ_HIP_TRY(hipEventRecord(c->ev1, s));
-    BQ_HIP_TRY(hipMemcpyAsync(c->h_ctrl, c->ctrl, sizeof(bq::Ctrl), hipMemcpyDeviceToHost, s));
+    if (!small)
+        BQ_HIP_TRY(hipMemcpyAsync(c->h_ctrl, c->ctrl, sizeof(bq::Ctrl), hipMemcpyDeviceToHost, s));
     c->trace_n = 0;
     if (a.trace) {
         BQ_HIP_TRY(hipMemcpyAsync(c->h_trace, c->trace, sizeof(unsigned long long) * 4 * TRACE_CAP,
@@ -610,7 +643,8 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
     const bq::Ctrl* h = c->h_ctrl;
     float ms = 0.f, sms = 0.f;
     BQ_HIP_TRY(hipEventElapsedTime(&ms, c->ev0, c->ev1));
-    BQ_HIP_TRY(hipEventElapsedTime(&sms, c->evs0, c->evs1));
+    if (small) sms = ms;
+    else BQ_HIP_TRY(hipEventElapsedTime(&sms, c->evs0, c->evs1));
     c->last.dequeued = h->stats[bq::ST_DEQ].v;
     c->last.relaxations = h->stats[bq::ST_RELAX].v;
     c->last.pushes = h->stats[bq::ST_PUSH].v;
@@ -623,11 +657,11 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
     c->last.ms = ms;
     c->last.solve_ms = sms;
     c->last.grid = grid;
-    c->last.wg_size = sweep ? SWEEP_WG : SOLVE_WG_ONE;
+    c->last.wg_size = small ? SMALL_WG : (sweep ? SWEEP_WG : SOLVE_WG_ONE);
     const unsigned long long err = h->error.v;
     const bool neg = h->negcycle.v != 0ull;
     // a stopped asynchronous solve leaves its queue non-quiescent
-    if (!sweep && (err != 0ull || h->abort.v != 0ull)) c->dirty = true;
+    if (!small && !sweep && (err != 0ull || h->abort.v != 0ull)) c->dirty = true;
     if (err == bq::ERR_RANGE) return BQ_ERANGE;
     if (err == bq::ERR_FULL) return BQ_EOVERFLOW;
     if (err != 0ull) return BQ_ETIMEOUT;
@@ -727,7 +761,8 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
     bqh::Launch L = bqh::resolve(launch, 0);
     if (L.batch != 1 && L.batch != 2 && L.batch != 4) return BQ_EINVAL;
     if (L.flags & BQ_F_TRACE) return BQ_EINVAL;  // the timeline needs a context
-    const bool sweep = sweeps(L);
+    const bool small = is_small(n, (long long)m, L);
+    const bool sweep = !small && sweeps(L);
     hipStream_t s = bqh::as_stream(stream);
     int dev = 0;
     unsigned char* base = nullptr;
@@ -777,7 +812,7 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
         const unsigned long long room = NOALLOC_SCRATCH_BYTES - ctrl_bytes - wr_bytes;
         while (nseg > 1 && sweep_layout(at, n, (long long)m, clog, nseg, &f) > room) nseg /= 2;
         if (sweep_layout(at, n, (long long)m, clog, nseg, &f) > room) return BQ_EBUSY;
-    } else {
+    } else if (!small) {
         // the array keeps the previous call's contents: clear the control
         // blocks and the slots this call uses
         hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, s, (unsigned long long*)ctrl,
@@ -797,7 +832,7 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
     q.pad = 0;
     q.N = cap;
     if (L.flags & BQ_F_VALIDATE) {
-        if (sweep) {
+        if (small || sweep) {
             hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, &ctrl->aux[3].v, 1ull);
             BQ_HIP_TRY(hipGetLastError());
         }
@@ -840,7 +875,10 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
     a.tw = nullptr;
     a.orig = nullptr;
     a.pos = nullptr;
-    if (sweep) {
+    if (small) {
+        bq_status st = launch_small(a, (int*)d_pred, ctrl, s);
+        if (st != BQ_OK) return st;
+    } else if (sweep) {
         hipLaunchKernelGGL(k_sweep_init, dim3(init_blocks(n, (long long)m)), dim3(INIT_WG), 0, s,
                            a, f, wrange);
         BQ_HIP_TRY(hipGetLastError());
@@ -854,9 +892,11 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
         bq_status st = launch_solve(a, L.batch, grid, s);
         if (st != BQ_OK) return st;
     }
-    hipLaunchKernelGGL(k_unpack, dim3(grid_for(n)), dim3(256), 0, s, (long long*)d_dist,
-                       (int*)d_pred, n, src, shift);
-    BQ_HIP_TRY(hipGetLastError());
+    if (!small) {
+        hipLaunchKernelGGL(k_unpack, dim3(grid_for(n)), dim3(256), 0, s, (long long*)d_dist,
+                           (int*)d_pred, n, src, shift);
+        BQ_HIP_TRY(hipGetLastError());
+    }
     unsigned long long words[3] = {0, 0, 0};
     BQ_HIP_TRY(hipMemcpyAsync(&words[0], &ctrl->error.v, 8, hipMemcpyDeviceToHost, s));
     BQ_HIP_TRY(hipMemcpyAsync(&words[1], &ctrl->negcycle.v, 8, hipMemcpyDeviceToHost, s));

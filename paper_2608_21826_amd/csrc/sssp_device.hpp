@@ -441,13 +441,15 @@ __device__ long long min_edge(const SolveArgs& a, unsigned p, unsigned y) {
 }
 
 // Whether the lam parent steps from `hare` close a walk whose lightest edges
-// sum below zero. Wave-uniform.
-__device__ bool closed_walk_is_negative(const SolveArgs& a, unsigned hare, unsigned lam) {
+// sum below zero. `parent(x)` reads x's parent. Wave-uniform.
+template <class Parent>
+__device__ bool closed_walk_is_negative(const SolveArgs& a, unsigned hare, unsigned lam,
+                                        const Parent& parent) {
     const unsigned sent = (1u << (a.shift - 1u)) - 1u;
     long long sum = 0;
     unsigned y = hare;
     for (unsigned i = 0; i < lam; ++i) {
-        const unsigned p = bq::bcast32(parent_of(a, (int)y));
+        const unsigned p = bq::bcast32(parent(y));
         if (p == sent) return false;
         const long long wmin = min_edge(a, p, y);
         if (wmin == LLONG_MAX) return false;
@@ -478,8 +480,53 @@ __device__ int walk_finds_negative_cycle(const SolveArgs& a, int x0, unsigned bu
         if ((steps & 255u) == 0u && bq::aborted(a.q)) return -1;
     }
     if (hare == sent) return -1;
-    return closed_walk_is_negative(a, hare, lam) ? (int)hare : -1;
+    const auto parent = [&](unsigned x) { return parent_of(a, (int)x); };
+    return closed_walk_is_negative(a, hare, lam, parent) ? (int)hare : -1;
 }
+
+// Negative cycles in the sweep forms. A label below the certain lower bound is one proof; the
+// other is a closed walk of parent pointers. The last SWEEP_WALKERS waves of
+// the gang search for one from vertices of the current sweep (Brent's cycle
+// finding), a few steps per sweep beside the other waves' round trips, so the
+// search delays no sweep and runs from the start: a cycle whose vertices
+// improve nothing else keeps sweeps of a few items going, which a search that
+// waits for an amount of work finds only after millions of them. `parent(x)`
+// reads x's parent.
+constexpr unsigned SWEEP_WALKERS = 4;
+constexpr unsigned SWEEP_WALK_FROM = 8;   // first sweep
+constexpr unsigned SWEEP_WALK_STEPS = 4;  // per sweep
+
+struct SweepWalk {
+    unsigned tort, hare, power, lam;
+    bool on;
+    template <class Parent>
+    __device__ __forceinline__ void start(unsigned x0, const Parent& parent) {
+        tort = x0;
+        hare = bq::bcast32(parent(x0));
+        power = lam = 1u;
+        on = true;
+    }
+    // a vertex of a negative cycle, or -1
+    template <class Parent>
+    __device__ __forceinline__ int advance(const SolveArgs& a, const Parent& parent) {
+        const unsigned sent = (1u << (a.shift - 1u)) - 1u;
+        for (unsigned s = 0; s < SWEEP_WALK_STEPS && on; ++s) {
+            if (hare == sent || tort == hare) {
+                on = false;
+                if (hare != sent && closed_walk_is_negative(a, hare, lam, parent)) return (int)hare;
+                break;
+            }
+            if (power == lam) {
+                tort = hare;
+                power <<= 1;
+                lam = 0;
+            }
+            hare = bq::bcast32(parent(hare));
+            ++lam;
+        }
+        return -1;
+    }
+};
 
 // Per-workgroup parking of idle waves: one wave of the workgroup (the
 // poller) watches the global queue state with growing sleeps; the other idle

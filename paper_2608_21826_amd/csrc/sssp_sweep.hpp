@@ -294,47 +294,6 @@ __device__ __forceinline__ SweepSlot sweep_slot(unsigned nseg, unsigned pre, uns
     return SweepSlot{seg, g - first};
 }
 
-// Negative cycles. A label below the certain lower bound is one proof; the
-// other is a closed walk of parent pointers. The last SWEEP_WALKERS waves of
-// the gang search for one from vertices of the current sweep (Brent's cycle
-// finding), a few steps per sweep beside the other waves' round trips, so the
-// search delays no sweep and runs from the start: a cycle whose vertices
-// improve nothing else keeps sweeps of a few items going, which a search that
-// waits for an amount of work finds only after millions of them.
-constexpr unsigned SWEEP_WALKERS = 4;
-constexpr unsigned SWEEP_WALK_FROM = 8;   // first sweep
-constexpr unsigned SWEEP_WALK_STEPS = 4;  // per sweep
-
-struct SweepWalk {
-    unsigned tort, hare, power, lam;
-    bool on;
-    __device__ __forceinline__ void start(const SolveArgs& a, unsigned x0) {
-        tort = x0;
-        hare = bq::bcast32(parent_of(a, (int)x0));
-        power = lam = 1u;
-        on = true;
-    }
-    // a vertex of a negative cycle, or -1
-    __device__ __forceinline__ int advance(const SolveArgs& a) {
-        const unsigned sent = (1u << (a.shift - 1u)) - 1u;
-        for (unsigned s = 0; s < SWEEP_WALK_STEPS && on; ++s) {
-            if (hare == sent || tort == hare) {
-                on = false;
-                if (hare != sent && closed_walk_is_negative(a, hare, lam)) return (int)hare;
-                break;
-            }
-            if (power == lam) {
-                tort = hare;
-                power <<= 1;
-                lam = 0;
-            }
-            hare = bq::bcast32(parent_of(a, (int)hare));
-            ++lam;
-        }
-        return -1;
-    }
-};
-
 // One gang's solve of one query. Workgroup `rank` of `gang`; every workgroup
 // calls it with the same arguments otherwise. Returns 1 when the queue ran
 // empty, -1 when the solve was stopped (error or negative cycle).
@@ -551,15 +510,17 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned r
         }
         // ---- negative-cycle search ---------------------------------------
         if (gw + SWEEP_WALKERS >= W && it >= SWEEP_WALK_FROM && ok) {
+            const auto parent = [&](unsigned x) { return parent_of(a, (int)x); };
             if (!walk.on) {
                 const unsigned k = (it + gw) % (NL > 0 ? NL : NC);
                 const SweepSlot at = sweep_slot(a.nseg, NL > 0 ? pre_l : pre_c, k);
-                walk.start(a, bq::bcast32(
+                walk.start(bq::bcast32(
                     NL > 0 ? bq::ld_rlx(&f.light[(part0 + at.seg) * f.cap_light + at.i])
-                           : (unsigned)bq::ld_rlx(&f.chunk[(part0 + at.seg) * f.cap_chunk + at.i])));
+                           : (unsigned)bq::ld_rlx(&f.chunk[(part0 + at.seg) * f.cap_chunk + at.i])),
+                    parent);
                 ++st.walk;
             }
-            const int hit = walk.advance(a);
+            const int hit = walk.advance(a, parent);
             if (hit >= 0) {
                 if (lane == 0 && !flagged) bq::st_rlx(&a.q.ctrl->negcycle.v, 1ull);
                 flagged = true;
