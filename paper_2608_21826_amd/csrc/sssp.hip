@@ -14,8 +14,6 @@
 #include "csr_device.hpp"
 #include "host_common.hpp"
 #include "sssp_kernels.hpp"
-#include "sssp_small.hpp"
-#include "sssp_sweep.hpp"
 
 
 // ---------------------------------------------------------------------------
@@ -29,7 +27,7 @@ struct sssp_ctx {
     unsigned long long* slots;
     bq::Ctrl* ctrl;
     unsigned* chunk_owner;
-    int* wrange;                  // [2 * INIT_MAX_BLOCKS]
+    int* wrange;                  // [3 * INIT_MAX_BLOCKS]: weight ranges, long-row flags
     unsigned long long* trace;    // [4 * TRACE_CAP]
     unsigned long long* h_trace;  // pinned copy
     int trace_n;
@@ -170,34 +168,6 @@ bq_status launch_small(const SolveArgs& a, int* pred, bq::Ctrl* h, hipStream_t s
     return BQ_OK;
 }
 
-// Chunk items one buffer's segment holds at most: a row longer than C gives
-// ceil(degree / C) <= 2 degree / C of them.
-unsigned long long sweep_chunk_cap(long long m, unsigned chunk_log) {
-    return 2ull * ((unsigned long long)m >> chunk_log) + 64ull;
-}
-
-// Memory of a sweep solve, carved from `base` (256-byte aligned): words, the
-// light and chunk items of the two buffers, the stamps. Returns its size.
-unsigned long long sweep_layout(char* base, int n, long long m, unsigned chunk_log, int nseg,
-                                SweepArgs* f) {
-    unsigned long long at = 0;
-    auto take = [&](unsigned long long bytes) {
-        char* p = base + at;
-        at += (bytes + 255ull) & ~255ull;
-        return p;
-    };
-    const unsigned long long cl = (unsigned long long)n, cc = sweep_chunk_cap(m, chunk_log);
-    SweepArgs t;
-    t.ctl = (decltype(t.ctl))take(sizeof(SweepCtl));
-    t.light = (decltype(t.light))take(4ull * 2ull * (unsigned long long)nseg * cl);
-    t.chunk = (decltype(t.chunk))take(8ull * 2ull * (unsigned long long)nseg * cc);
-    t.stamp = (decltype(t.stamp))take(4ull * cl);
-    t.cap_light = (unsigned)cl;
-    t.cap_chunk = (unsigned)cc;
-    if (f) *f = t;
-    return at;
-}
-
 // Default workgroups (16 waves each) of a sweep solve: about one per 128 units
 // of n + m/16, a power of two, at most one per CU; on graphs of short rows
 // (meshes: few vertices per sweep) at most half of that. A workgroup more
@@ -284,7 +254,7 @@ bq_status sssp_ctx_create(int32_t max_n, int64_t max_m, sssp_ctx** out) {
                       hipHostMallocDefault) != hipSuccess ||
         hipMalloc(&c->ctrl, sizeof(bq::Ctrl) * MAX_Q) != hipSuccess ||
         hipMalloc(&c->chunk_owner, sizeof(unsigned) * chunks) != hipSuccess ||
-        hipMalloc(&c->wrange, sizeof(int) * 2 * INIT_MAX_BLOCKS) != hipSuccess ||
+        hipMalloc(&c->wrange, sizeof(int) * 3 * INIT_MAX_BLOCKS) != hipSuccess ||
         hipMalloc(&c->sweep_mem, sweep_layout(nullptr, max_n, max_m, MIN_CHUNK_LOG, MAX_SEG,
                                               nullptr)) != hipSuccess ||
         hipHostMalloc(&c->h_ctrl, sizeof(bq::Ctrl), hipHostMallocDefault) != hipSuccess) {
@@ -609,6 +579,7 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
     } else if (sweep) {
         SweepArgs f;
         sweep_layout(c->sweep_mem, n, (long long)m, clog, nseg, &f);
+        f.longp = (decltype(f.longp))(c->wrange + 2 * INIT_MAX_BLOCKS);
         hipLaunchKernelGGL(k_sweep_init, dim3(init_blocks(n, (long long)m)), dim3(INIT_WG), 0, s,
                            a, f, c->wrange);
         BQ_HIP_TRY(hipGetLastError());
@@ -809,9 +780,12 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
         // the sweep form's buffers instead of slots, behind the partials; any
         // input that passes the slots' limit above fits with one segment
         char* at = (char*)base + ctrl_bytes + wr_bytes;
-        const unsigned long long room = NOALLOC_SCRATCH_BYTES - ctrl_bytes - wr_bytes;
-        while (nseg > 1 && sweep_layout(at, n, (long long)m, clog, nseg, &f) > room) nseg /= 2;
-        if (sweep_layout(at, n, (long long)m, clog, nseg, &f) > room) return BQ_EBUSY;
+        const unsigned long long flags = 4ull * INIT_MAX_BLOCKS;
+        const unsigned long long room = NOALLOC_SCRATCH_BYTES - ctrl_bytes - wr_bytes - flags;
+        while (nseg > 1 && sweep_layout(at + flags, n, (long long)m, clog, nseg, &f) > room)
+            nseg /= 2;
+        if (sweep_layout(at + flags, n, (long long)m, clog, nseg, &f) > room) return BQ_EBUSY;
+        f.longp = (decltype(f.longp))at;
     } else if (!small) {
         // the array keeps the previous call's contents: clear the control
         // blocks and the slots this call uses

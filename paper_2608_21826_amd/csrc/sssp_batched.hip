@@ -1,21 +1,26 @@
 // Batched form: many SSSP queries (different graphs and sources, uneven
-// sizes) in one persistent launch, each query with its own Broker Queue.
+// sizes) in one persistent launch, each query with its own queue.
 //
 // Three kernels, the same for any batch of a given count, so the sequence
 // can be captured once in a hipGraph and replayed:
 //  k_binit   - per "unit" (a slice of one query's vertices and edges): keys,
 //              weight-range partials; a query's first unit also resets its
-//              control block and enqueues its source
-//  k_bsolve  - persistent workgroups claim queries from claim lists (queries
-//              sorted by size, each listed in proportion to its work, so big
-//              queries get several workgroups) and, when their list runs out,
-//              join an unfinished query; each runs the solver loop of the
-//              single-query launch on that query's queue. There is one list
-//              per XCD: a query whose share fits one XCD's workgroups is
-//              listed on one list only, so its keys are cached in one L2
-//              instead of being spread over all eight
+//              control words and puts its source into the queue
+//  k_bsweep  - the workgroups (one per CU) form gangs of equal size, workgroup
+//              i in gang i mod G, so that with 8 or more gangs each lives on
+//              one XCD (workgroups are dispatched to the XCDs in turn). A gang
+//              solves the queries of its list one after another in sweeps
+//              (sssp_sweep.hpp); queries whose keys fit one CU's LDS are
+//              taken one at a time by single workgroups (sssp_small.hpp) as
+//              their gangs finish
 //  k_bunpack - per unit: distances and predecessors; per query: the result
 //              flags
+// With near / far buckets k_bsolve runs in place of k_bsweep: persistent
+// workgroups claim queries from claim lists (queries sorted by size, each
+// listed in proportion to its work, so big queries get several workgroups)
+// and, when their list runs out, join an unfinished query; each runs the
+// asynchronous solver loop on that query's queue. There is one list per XCD: a
+// query whose share fits one XCD's workgroups is listed on one list only.
 #include <hip/hip_runtime.h>
 #include <limits.h>
 #include <stdio.h>
@@ -30,10 +35,14 @@
 
 #include "host_common.hpp"
 #include "sssp_device.hpp"
+#include "sssp_init.hpp"
+#include "sssp_small.hpp"
+#include "sssp_sweep.hpp"
 
 namespace {
 
-constexpr unsigned BDEFAULT_CHUNK_LOG = 10;
+constexpr unsigned BDEFAULT_CHUNK_LOG = 10;  // with buckets
+constexpr unsigned BSWEEP_CHUNK_LOG = 7;
 constexpr unsigned BMIN_CHUNK_LOG = 6;
 constexpr unsigned BMAX_CHUNK_LOG = 16;
 constexpr long long UNIT = 65536;  // vertices or edges per init/unpack unit
@@ -41,6 +50,7 @@ constexpr int BINIT_WG = 256;
 
 struct InstDesc {
     SolveArgs a;
+    SweepArgs f;      // sweep form; f.ctl null: one workgroup in LDS, or k_bsolve
     long long* dist;  // the caller's output (a.key itself unless the key layout is remapped)
     int* pred;
     int orig;        // index in the caller's array
@@ -217,18 +227,20 @@ __global__ void k_rm_rows(const RemapDesc* R, int nr) {
 constexpr int NLIST = 8;
 
 struct BatchCtl {
-    bq::Word cursor[NLIST];  // next entry of each claim list
+    bq::Word cursor[NLIST];  // next entry of each claim list; [0]: the next
+                             // one-workgroup query
     bq::Word stats[bq::ST_N];
 };
 
 __global__ __launch_bounds__(BINIT_WG) void k_binit(const InstDesc* D, const Unit* units,
                                                     int n_units, int* partials, BatchCtl* bc,
-                                                    unsigned long long* reached) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        for (int x = 0; x < NLIST; ++x) bc->cursor[x].v = 0ull;
-        for (int i = 0; i < bq::ST_N; ++i) bc->stats[i].v = 0ull;
+                                                    unsigned long long* reached, int count) {
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < NLIST) bc->cursor[threadIdx.x].v = 0ull;
+        if (threadIdx.x < (unsigned)bq::ST_N) bc->stats[threadIdx.x].v = 0ull;
+        for (int i = (int)threadIdx.x; i < count; i += BINIT_WG) reached[i] = 0ull;
     }
-    __shared__ int slo[BINIT_WG / 64], shi[BINIT_WG / 64];
+    __shared__ int slo[BINIT_WG / 64], shi[BINIT_WG / 64], slong;
     for (int u = blockIdx.x; u < n_units; u += gridDim.x) {
         const Unit un = units[u];
         const InstDesc& d = D[un.inst];
@@ -237,6 +249,18 @@ __global__ __launch_bounds__(BINIT_WG) void k_binit(const InstDesc* D, const Uni
         const long long spos = (long long)pos_of(a, (unsigned)a.src);
         for (long long v = un.v0 + threadIdx.x; v < un.v1; v += blockDim.x)
             a.key[v] = (v == spos) ? srckey : KEY_INF;
+        const bool sweep = d.f.ctl != nullptr;
+        const long long C = 1ll << a.chunk_log;
+        if (threadIdx.x == 0) slong = 0;
+        bool lr = false;
+        if (sweep)
+            for (long long v = un.v0 + threadIdx.x; v < un.v1; v += blockDim.x) {
+                const long long r = (long long)orig_of(a, (unsigned)v);
+                if (a.off[r + 1] - a.off[r] > C) {
+                    lr = true;
+                    d.f.stamp[v] = 0u;
+                }
+            }
         int lo = INT_MAX, hi = INT_MIN;
         for (long long e = un.e0 + threadIdx.x; e < un.e1; e += blockDim.x) {
             const int x = a.w[e];
@@ -253,6 +277,10 @@ __global__ __launch_bounds__(BINIT_WG) void k_binit(const InstDesc* D, const Uni
             shi[threadIdx.x >> 6] = hi;
         }
         __syncthreads();
+        if (lr) slong = 1;
+        if (sweep && u == d.unit_begin)
+            sweep_seed(a, d.f, (unsigned)spos, threadIdx.x, BINIT_WG);
+        __syncthreads();
         if (threadIdx.x == 0) {
             for (int i = 1; i < BINIT_WG / 64; ++i) {
                 lo = slo[i] < lo ? slo[i] : lo;
@@ -260,19 +288,22 @@ __global__ __launch_bounds__(BINIT_WG) void k_binit(const InstDesc* D, const Uni
             }
             partials[2 * u] = lo;
             partials[2 * u + 1] = hi;
+            if (sweep) d.f.longp[u - d.unit_begin] = (unsigned)slong;
             if (u == d.unit_begin) {
-                reached[d.orig] = 0ull;
                 bq::Ctrl* c = a.q.ctrl;
-                c->pending.v = 1ull;
                 c->abort.v = 0ull;
                 c->error.v = 0ull;
                 c->negcycle.v = 0ull;
                 c->aux[0].v = (unsigned long long)(d.unit_end - d.unit_begin);
+                c->aux[4].v = bq::now_ticks();
+            }
+            if (u == d.unit_begin && !sweep) {
+                bq::Ctrl* c = a.q.ctrl;
+                c->pending.v = 1ull;
                 for (unsigned sg = 0; sg < a.nq; ++sg)  // dequeue positions at start
                     c[sg].aux[2].v = c[sg].head.v;
                 c->aux[1].v = (unsigned long long)LLONG_MIN;  // near / far threshold
                 c->busy.v = 0ull;
-                c->aux[4].v = bq::now_ticks();
                 c->aux[5].v = 0ull;  // finished flag
                 for (int i = 0; i < bq::ST_N; ++i) c->stats[i].v = 0ull;
                 const unsigned long long pos = c->tail.v;
@@ -357,6 +388,49 @@ __global__ __launch_bounds__(SOLVE_WG, SSSP_MIN_WAVES) void k_bsolve(const InstD
     flush_stats(bc->stats, st);
 }
 
+// glist: G + 1 offsets, then the descriptor indices of gang g's queries at
+// [glist[g], glist[g + 1]) after that header, then the n_small one-workgroup
+// queries, both biggest first.
+__global__ __launch_bounds__(SWEEP_WG) void k_bsweep(const InstDesc* __restrict__ D,
+                                                     const int* glist, int G, int n_small,
+                                                     BatchCtl* bc, long long* results,
+                                                     unsigned long long* reached) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    __shared__ int s_next;
+    __shared__ unsigned long long s_stats[bq::ST_N];
+    WaveStats st{};
+    const unsigned gang = blockIdx.x % (unsigned)G;
+    const unsigned size = (gridDim.x - gang + (unsigned)G - 1u) / (unsigned)G;
+    const int* list = glist + G + 1;
+    for (int k = glist[gang]; k < glist[gang + 1]; ++k) {
+        const int i = __builtin_amdgcn_readfirstlane(list[k]);
+        const SolveArgs a = D[i].a;
+        const SweepArgs f = D[i].f;
+        sweep_instance<SWEEP_WAVES>(a, f, size, *(SweepLds<SWEEP_WAVES>*)lds, st);
+        __syncthreads();
+    }
+    const int* small = list + glist[G];
+    for (;;) {
+        if (threadIdx.x == 0) s_next = (int)bq::add_rlx(&bc->cursor[0].v, 1ull);
+        __syncthreads();
+        const int k = __builtin_amdgcn_readfirstlane(s_next);
+        if (k >= n_small) break;
+        const int i = __builtin_amdgcn_readfirstlane(small[k]);
+        const SolveArgs a = D[i].a;
+        const SmallResult r =
+            small_instance(a, D[i].dist, D[i].pred, &reached[D[i].orig], lds, st);
+        if (threadIdx.x == 0) results[D[i].orig] = (long long)r.neg | ((long long)r.err << 8);
+        __syncthreads();
+    }
+    sum_stats(s_stats, st);
+    if (threadIdx.x < (unsigned)bq::ST_N && s_stats[threadIdx.x])
+        bq::add_rlx(&bc->stats[threadIdx.x].v, s_stats[threadIdx.x]);
+}
+
+constexpr size_t BSWEEP_LDS = small_lds_bytes_max() > sizeof(SweepLds<SWEEP_WAVES>)
+                                  ? small_lds_bytes_max()
+                                  : sizeof(SweepLds<SWEEP_WAVES>);
+
 // Unpack, and count the query's reached edges (out-degrees of reached
 // vertices) for throughput figures.
 __global__ void k_bunpack(const InstDesc* D, const Unit* units, int n_units,
@@ -399,6 +473,22 @@ unsigned bkey_shift(int n) {
     unsigned pb = 0;
     while ((1ull << pb) < (unsigned long long)n + 1ull) ++pb;
     return pb + 1u;
+}
+
+constexpr int GANG_MIN = 4;  // workgroups
+
+// Work of a query in a gang, in edges of a random graph: a mesh's many short
+// sweeps cost about 16 times its edges (256 x 256 road mesh on 8 workgroups
+// 8.3 ms, random graph of 200k vertices on 16 1.37 ms).
+long long gang_work(int n, long long m) {
+    return ((long long)n + m) * (m < 6ll * n ? 16 : 1);
+}
+
+// Queries that one workgroup solves in LDS. Alone on a CU a query takes about
+// 3 ns per edge, so one that would outlast the rest of the batch goes to a
+// gang.
+bool batch_small(int n, long long m, long long tot_work) {
+    return (unsigned)n <= SMALL_MAX_N && (m <= 40960 || m < 6ll * n || m <= tot_work / 64);
 }
 
 unsigned long long pow2ceil(unsigned long long x) {
@@ -451,42 +541,60 @@ struct sssp_batch {
     std::map<unsigned long long, std::pair<bq_launch, double>> tuned;
     hipGraphExec_t exec;
     hipGraph_t graph;
-    unsigned long long graph_key[8];
+    unsigned long long graph_key[10];
     int per_cu[3];
+    int sweep_per_cu;
+    bool sweeping;      // the started launch is the sweep form
+    unsigned* d_longp;  // per unit: a row longer than C exists
     sssp_stats last;
 };
 
 namespace {
 
-bq_status batch_launch_kernels(sssp_batch* b, int count, int n_units, int n_lists, int grid,
-                               int B, int nr, int rm_tiles) {
+// The shape of one launch sequence; also what a captured graph depends on.
+struct LaunchShape {
+    int count, n_units, n_claim, n_lists, grid, B, nr, rm_tiles;
+    int gangs, n_small;  // gangs > 0: the sweep form
+    void key(unsigned long long* k) const {
+        const int v[10] = {count, n_units, n_claim, n_lists, grid, B, nr, rm_tiles, gangs, n_small};
+        for (int i = 0; i < 10; ++i) k[i] = (unsigned long long)v[i];
+    }
+};
+
+bq_status batch_launch_kernels(sssp_batch* b, const LaunchShape& z) {
     hipStream_t s = b->stream;
-    const int ug = n_units < 2048 ? n_units : 2048;
-    if (nr > 0) {
-        const int tg = rm_tiles < 4096 ? rm_tiles : 4096;
-        hipLaunchKernelGGL(k_rm_hist, dim3(tg), dim3(64), 0, s, b->d_rm, nr, rm_tiles);
-        hipLaunchKernelGGL(k_rm_scan, dim3(nr), dim3(1024), 0, s, b->d_rm, nr);
-        hipLaunchKernelGGL(k_rm_place, dim3(tg), dim3(64), 0, s, b->d_rm, nr, rm_tiles);
-        hipLaunchKernelGGL(k_rm_rows, dim3(2048), dim3(256), 0, s, b->d_rm, nr);
+    const int ug = z.n_units < 2048 ? (z.n_units > 0 ? z.n_units : 1) : 2048;
+    if (z.nr > 0) {
+        const int tg = z.rm_tiles < 4096 ? z.rm_tiles : 4096;
+        hipLaunchKernelGGL(k_rm_hist, dim3(tg), dim3(64), 0, s, b->d_rm, z.nr, z.rm_tiles);
+        hipLaunchKernelGGL(k_rm_scan, dim3(z.nr), dim3(1024), 0, s, b->d_rm, z.nr);
+        hipLaunchKernelGGL(k_rm_place, dim3(tg), dim3(64), 0, s, b->d_rm, z.nr, z.rm_tiles);
+        hipLaunchKernelGGL(k_rm_rows, dim3(2048), dim3(256), 0, s, b->d_rm, z.nr);
     }
-    hipLaunchKernelGGL(k_binit, dim3(ug), dim3(BINIT_WG), 0, s, b->d_desc, b->d_units, n_units,
-                       b->d_partials, b->d_bc, b->d_reached);
-    switch (B) {
-        case 64:
-            hipLaunchKernelGGL(k_bsolve<64>, dim3(grid), dim3(SOLVE_WG), 0, s, b->d_desc, count,
-                               b->d_claim, n_lists, b->d_bc);
-            break;
-        case 128:
-            hipLaunchKernelGGL(k_bsolve<128>, dim3(grid), dim3(SOLVE_WG), 0, s, b->d_desc, count,
-                               b->d_claim, n_lists, b->d_bc);
-            break;
-        default:
-            hipLaunchKernelGGL(k_bsolve<256>, dim3(grid), dim3(SOLVE_WG), 0, s, b->d_desc, count,
-                               b->d_claim, n_lists, b->d_bc);
-            break;
+    hipLaunchKernelGGL(k_binit, dim3(ug), dim3(BINIT_WG), 0, s, b->d_desc, b->d_units, z.n_units,
+                       b->d_partials, b->d_bc, b->d_reached, z.count);
+    if (z.gangs > 0) {
+        hipLaunchKernelGGL(k_bsweep, dim3(z.grid), dim3(SWEEP_WG), BSWEEP_LDS, s, b->d_desc,
+                           b->d_claim, z.gangs, z.n_small, b->d_bc, b->d_results, b->d_reached);
+    } else {
+        switch (z.B) {
+            case 64:
+                hipLaunchKernelGGL(k_bsolve<64>, dim3(z.grid), dim3(SOLVE_WG), 0, s, b->d_desc,
+                                   z.count, b->d_claim, z.n_lists, b->d_bc);
+                break;
+            case 128:
+                hipLaunchKernelGGL(k_bsolve<128>, dim3(z.grid), dim3(SOLVE_WG), 0, s, b->d_desc,
+                                   z.count, b->d_claim, z.n_lists, b->d_bc);
+                break;
+            default:
+                hipLaunchKernelGGL(k_bsolve<256>, dim3(z.grid), dim3(SOLVE_WG), 0, s, b->d_desc,
+                                   z.count, b->d_claim, z.n_lists, b->d_bc);
+                break;
+        }
     }
-    hipLaunchKernelGGL(k_bunpack, dim3(ug), dim3(256), 0, s, b->d_desc, b->d_units, n_units,
-                       b->d_results, b->d_reached);
+    if (z.n_units > 0)
+        hipLaunchKernelGGL(k_bunpack, dim3(ug), dim3(256), 0, s, b->d_desc, b->d_units, z.n_units,
+                           b->d_results, b->d_reached);
     BQ_HIP_TRY(hipGetLastError());
     return BQ_OK;
 }
@@ -505,6 +613,21 @@ int batch_max_grid(sssp_batch* b, int B) {
         if (e != hipSuccess || pc < 1) pc = 1;
     }
     return pc * bqh::device_cus();
+}
+
+// Co-resident workgroups of k_bsweep (its barriers need a gang's workgroups
+// all resident): one per CU, its LDS fills one.
+bq_status sweep_max_grid(sssp_batch* b, int* out) {
+    if (b->sweep_per_cu == 0) {
+        BQ_HIP_TRY(hipFuncSetAttribute((const void*)k_bsweep,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)BSWEEP_LDS));
+        BQ_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b->sweep_per_cu, k_bsweep,
+                                                                SWEEP_WG, BSWEEP_LDS));
+        if (b->sweep_per_cu < 1) b->sweep_per_cu = 1;
+    }
+    *out = b->sweep_per_cu * bqh::device_cus();
+    return BQ_OK;
 }
 
 }  // namespace
@@ -550,6 +673,7 @@ bq_status sssp_batch_create(int32_t max_instances, int64_t max_total_n, int64_t 
         hipMalloc(&b->d_units, sizeof(Unit) * b->max_units) != hipSuccess ||
         hipMalloc(&b->d_claim, sizeof(int) * b->max_claim) != hipSuccess ||
         hipMalloc(&b->d_partials, sizeof(int) * 2 * b->max_units) != hipSuccess ||
+        hipMalloc(&b->d_longp, sizeof(unsigned) * b->max_units) != hipSuccess ||
         hipMalloc(&b->d_results, sizeof(long long) * max_instances) != hipSuccess ||
         hipMalloc(&b->d_reached, sizeof(unsigned long long) * max_instances) != hipSuccess ||
         hipMalloc(&b->d_bc, sizeof(BatchCtl)) != hipSuccess ||
@@ -603,6 +727,7 @@ bq_status sssp_batch_destroy(sssp_batch* b) {
     if (b->d_units) (void)hipFree(b->d_units);
     if (b->d_claim) (void)hipFree(b->d_claim);
     if (b->d_partials) (void)hipFree(b->d_partials);
+    if (b->d_longp) (void)hipFree(b->d_longp);
     if (b->d_results) (void)hipFree(b->d_results);
     if (b->d_reached) (void)hipFree(b->d_reached);
     if (b->d_bc) (void)hipFree(b->d_bc);
@@ -635,7 +760,8 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     bqh::Launch L = bqh::resolve(launch, 0);
     if (L.batch != 1 && L.batch != 2 && L.batch != 4) return BQ_EINVAL;
     const int B = 64 * L.batch;
-    unsigned clog = BDEFAULT_CHUNK_LOG;
+    const bool sweep = L.bucket_width == 0;
+    unsigned clog = sweep ? BSWEEP_CHUNK_LOG : BDEFAULT_CHUNK_LOG;
     if (L.row_chunk > 0) {
         if (L.row_chunk & (L.row_chunk - 1)) return BQ_EINVAL;
         clog = bqh::log2_exact((unsigned long long)L.row_chunk);
@@ -665,27 +791,64 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     for (int i = 0; i < count; ++i) work[i] = h_inst[i].m + h_inst[i].n;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return work[x] > work[y]; });
 
-    const int max_grid = batch_max_grid(b, B);
-    // default: about one workgroup per 16K units of n + m/16 of each query
-    // (the single-query solver's rule), at least one per query; more waves
-    // than the work can feed only raise the relaxations per edge
-    long long want = 0;
-    for (int i = 0; i < count; ++i) {
-        const long long units = (long long)h_inst[i].n + h_inst[i].m / 16;
-        want += units / 16384 > 1 ? units / 16384 : 1;
+    long long tot_work = 0;
+    for (int i = 0; i < count; ++i) tot_work += work[i];
+    int max_grid = 0;
+    if (sweep) {
+        bq_status st = sweep_max_grid(b, &max_grid);
+        if (st != BQ_OK) return st;
+    } else {
+        max_grid = batch_max_grid(b, B);
     }
-    int grid = L.wg_count > 0 ? L.wg_count : (want < max_grid ? (int)want : max_grid);
-    if (grid > max_grid) grid = max_grid;
+    // the sweep form's queries: one workgroup in LDS, or a gang
+    std::vector<char> small(count, 0);
+    long long big_work = 0, big_most = 0;
+    int n_small = 0, n_big = 0, gangs = 0;
+    int grid = 0;
+    if (sweep) {
+        long long want = 0;
+        for (int k = 0; k < count; ++k) {
+            const sssp_instance& x = h_inst[order[k]];
+            small[k] = batch_small(x.n, (long long)x.m, tot_work);
+            n_small += small[k];
+            if (!small[k]) {
+                const long long w = gang_work(x.n, (long long)x.m);
+                big_work += w;
+                big_most = w > big_most ? w : big_most;
+                ++n_big;
+                want += (x.n + x.m / 16) / 128 + 8;
+            }
+        }
+        want += n_small;
+        grid = L.wg_count > 0 ? L.wg_count : (want < max_grid ? (int)want : max_grid);
+        if (grid > max_grid) grid = max_grid;
+        // gangs: as many as the biggest query leaves room for
+        gangs = 1;
+        while (gangs * 2 <= n_big && gangs * 2 * big_most <= big_work &&
+               gangs * 2 * GANG_MIN <= grid)
+            gangs *= 2;
+        if (getenv("BQ_G")) gangs = atoi(getenv("BQ_G"));
+    } else {
+        // about one workgroup per 16K units of n + m/16 of each query, at
+        // least one per query; more waves than the work can feed only raise
+        // the relaxations per edge
+        long long want = 0;
+        for (int i = 0; i < count; ++i) {
+            const long long units = (long long)h_inst[i].n + h_inst[i].m / 16;
+            want += units / 16384 > 1 ? units / 16384 : 1;
+        }
+        grid = L.wg_count > 0 ? L.wg_count : (want < max_grid ? (int)want : max_grid);
+        if (grid > max_grid) grid = max_grid;
+    }
 
     // layout: queue slots, chunk tables, units, claim list
     std::vector<unsigned long long> layout;
     layout.reserve(3 * count + 2);
     size_t slot_off = 0, chunk_off = 0;
     int n_units = 0, n_claim = 0;
-    std::vector<std::vector<int>> lists(NLIST);
-    std::vector<long long> list_work(NLIST, 0);
-    long long tot_work = 0;
-    for (int i = 0; i < count; ++i) tot_work += work[i];
+    std::vector<std::vector<int>> lists(sweep ? gangs : NLIST);
+    std::vector<long long> list_work(lists.size(), 0);
+    std::vector<int> smalls;
     // workgroups per query in proportion to its share of the work (at least
     // one); a query whose share fits one XCD's workgroups is confined to one
     // claim list, a bigger one is spread over all lists
@@ -706,7 +869,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     // have the same home)
     std::vector<unsigned long long> caps(count);
     std::vector<unsigned> nsegs(count, 1u);
-    {
+    if (!sweep) {
         unsigned long long base = 0;
         for (int k = 0; k < count; ++k) {
             const sssp_instance& x = h_inst[order[k]];
@@ -741,6 +904,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
                  std::vector<int>> shared;
         if (!(L.flags & BQ_F_NOREMAP))
             for (int k = 0; k < count; ++k) {
+                if (small[k]) continue;
                 const sssp_instance& x = h_inst[order[k]];
                 shared[std::make_tuple((const void*)x.offsets, (const void*)x.cols,
                                        (const void*)x.w, x.n, (long long)x.m)]
@@ -778,21 +942,49 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
             ++nr;
         }
     }
+    // bytes of the slot arena that the queries after k need with one segment
+    std::vector<unsigned long long> arena_later(count + 1, 0);
+    if (sweep)
+        for (int k = count - 1; k > 0; --k) {
+            const sssp_instance& x = h_inst[order[k]];
+            arena_later[k - 1] =
+                arena_later[k] +
+                (small[k] ? 0ull : sweep_layout(nullptr, x.n, (long long)x.m, clog, 1, nullptr));
+        }
     size_t key_off = 0;
     for (int k = 0; k < count; ++k) {
         const int i = order[k];
         const sssp_instance& x = h_inst[i];
         const unsigned long long cap = caps[k];
-        const unsigned nseg = nsegs[k];
+        unsigned nseg = nsegs[k];
         const size_t chunks = (size_t)((unsigned long long)x.m >> clog) + 1;
         const long long big = x.n > x.m ? x.n : x.m;
-        const int ku = (int)((big + UNIT - 1) / UNIT);
-        if (slot_off + qps * nseg * cap > b->slot_cap || chunk_off + chunks > b->chunk_cap ||
+        const int ku = small[k] ? 0 : (int)((big + UNIT - 1) / UNIT);
+        if ((!sweep && (slot_off + qps * nseg * cap > b->slot_cap ||
+                        chunk_off + chunks > b->chunk_cap)) ||
             (size_t)(n_units + ku) > b->max_units)
             return BQ_EBUSY;
         InstDesc& d = b->h_desc[k];
         memset(&d, 0, sizeof d);
         SolveArgs& a = d.a;
+        if (sweep && !small[k]) {
+            // the sweep form's buffers come from the slot arena (its 96 bytes
+            // per vertex, 1.5 per edge and 96 KiB per query hold one segment
+            // of every query; more segments while they fit)
+            const int gsize = grid / gangs;
+            int ns = gsize / 4 < 1 ? 1 : (gsize / 4 < (int)MAX_SEG ? gsize / 4 : (int)MAX_SEG);
+            char* base = (char*)(b->slots + slot_off);
+            const unsigned long long room = 8ull * (b->slot_cap - slot_off);
+            const unsigned long long later = arena_later[k];
+            while (ns > 1 && sweep_layout(base, x.n, (long long)x.m, clog, ns, nullptr) + later > room)
+                ns /= 2;
+            const unsigned long long bytes =
+                sweep_layout(base, x.n, (long long)x.m, clog, ns, &d.f);
+            if (bytes > room) return BQ_EBUSY;
+            d.f.longp = (decltype(d.f.longp))(b->d_longp + n_units);
+            slot_off += (size_t)(bytes / 8);
+            nseg = (unsigned)ns;
+        }
         a.q.slots = (decltype(a.q.slots))(b->slots + slot_off);
         a.q.ctrl = (decltype(a.q.ctrl))(b->ctrls + (size_t)k * MAX_Q);
         a.q.sig = (decltype(a.q.sig))a.q.ctrl;
@@ -817,7 +1009,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
             a.orig = nullptr;
             a.pos = nullptr;
         }
-        a.chunk_owner = (decltype(a.chunk_owner))(b->chunks + chunk_off);
+        if (!sweep) a.chunk_owner = (decltype(a.chunk_owner))(b->chunks + chunk_off);
         a.wrange = (decltype(a.wrange))(b->d_partials + 2 * n_units);
         a.n = x.n;
         a.src = x.src;
@@ -850,6 +1042,20 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
         }
         n_units += ku;
         d.unit_end = n_units;
+        if (sweep) {
+            // each gang's list: the next biggest query to the gang with the
+            // least work so far
+            if (small[k]) {
+                smalls.push_back(k);
+            } else {
+                int best = 0;
+                for (int l = 1; l < gangs; ++l)
+                    if (list_work[l] < list_work[best]) best = l;
+                lists[best].push_back(k);
+                list_work[best] += gang_work(x.n, (long long)x.m);
+            }
+            continue;
+        }
         // claim entries: biggest queries first (spread ones round the
         // lists), each confined query on the list with the least work so far
         if (confined[k]) {
@@ -871,24 +1077,30 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
         slot_off += qps * nseg * cap;  // vertex queues, chunk lanes (and far queues)
         chunk_off += chunks;
     }
-    // the claim array: list offsets, then the lists one after another
+    // the claim array: list offsets, then the lists one after another, then
+    // the one-workgroup queries
     {
-        size_t total = NLIST + 1;
+        const size_t head = lists.size() + 1;
+        size_t total = head + smalls.size();
         for (const auto& l : lists) total += l.size();
         if (total > b->max_claim) return BQ_EBUSY;
         int pos = 0;
-        for (int l = 0; l < NLIST; ++l) {
+        for (size_t l = 0; l < lists.size(); ++l) {
             b->h_claim[l] = pos;
-            for (int e : lists[l]) b->h_claim[NLIST + 1 + pos++] = e;
+            for (int e : lists[l]) b->h_claim[head + pos++] = e;
         }
-        b->h_claim[NLIST] = pos;
+        b->h_claim[lists.size()] = pos;
+        for (int e : smalls) b->h_claim[head + pos++] = e;
         n_claim = (int)total;
     }
     hipStream_t cs = bqh::as_stream(stream);
     hipStream_t s = b->stream;
-    // queue state is reusable only if every query keeps the same slots and a
-    // clean end; otherwise zero the slots and control blocks first
-    if (b->dirty || layout != b->layout) {
+    // the slots' queue state is reusable only if every query keeps the same
+    // slots and a clean end; otherwise zero them and the control blocks first.
+    // The sweep form's buffers need no clearing, and overwrite the slots.
+    if (sweep) {
+        b->dirty = true;
+    } else if (b->dirty || layout != b->layout) {
         BQ_HIP_TRY(hipMemsetAsync(b->slots, 0, sizeof(unsigned long long) * slot_off, s));
         BQ_HIP_TRY(hipMemsetAsync(b->ctrls, 0, sizeof(bq::Ctrl) * count * MAX_Q, s));
         b->layout = layout;
@@ -896,8 +1108,9 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     }
     BQ_HIP_TRY(hipMemcpyAsync(b->d_desc, b->h_desc, sizeof(InstDesc) * count,
                               hipMemcpyHostToDevice, s));
-    BQ_HIP_TRY(hipMemcpyAsync(b->d_units, b->h_units, sizeof(Unit) * n_units,
-                              hipMemcpyHostToDevice, s));
+    if (n_units > 0)
+        BQ_HIP_TRY(hipMemcpyAsync(b->d_units, b->h_units, sizeof(Unit) * n_units,
+                                  hipMemcpyHostToDevice, s));
     BQ_HIP_TRY(hipMemcpyAsync(b->d_claim, b->h_claim, sizeof(int) * n_claim,
                               hipMemcpyHostToDevice, s));
     if (nr > 0)
@@ -907,13 +1120,12 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     BQ_HIP_TRY(hipEventRecord(b->ev_in, cs));
     BQ_HIP_TRY(hipStreamWaitEvent(s, b->ev_in, 0));
 
+    const LaunchShape shape = {count, n_units, n_claim, n_lists, grid, B,
+                               nr, rm_tiles, gangs, n_small};
     BQ_HIP_TRY(hipEventRecord(b->ev0, s));
     if (L.flags & BQ_F_GRAPH) {
-        const unsigned long long key[8] = {(unsigned long long)count, (unsigned long long)n_units,
-                                           (unsigned long long)n_claim, (unsigned long long)grid,
-                                           (unsigned long long)B, (unsigned long long)n_lists,
-                                           (unsigned long long)nr,
-                                           (unsigned long long)rm_tiles};
+        unsigned long long key[10];
+        shape.key(key);
         if (!b->exec || memcmp(key, b->graph_key, sizeof key) != 0) {
             if (b->exec) {
                 (void)hipGraphExecDestroy(b->exec);
@@ -924,7 +1136,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
                 b->graph = nullptr;
             }
             BQ_HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-            bq_status st = batch_launch_kernels(b, count, n_units, n_lists, grid, B, nr, rm_tiles);
+            bq_status st = batch_launch_kernels(b, shape);
             hipGraph_t g = nullptr;
             hipError_t ce = hipStreamEndCapture(s, &g);
             if (st != BQ_OK) return st;
@@ -935,7 +1147,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
         }
         BQ_HIP_TRY(hipGraphLaunch(b->exec, s));
     } else {
-        bq_status st = batch_launch_kernels(b, count, n_units, n_lists, grid, B, nr, rm_tiles);
+        bq_status st = batch_launch_kernels(b, shape);
         if (st != BQ_OK) return st;
     }
     BQ_HIP_TRY(hipEventRecord(b->ev1, s));
@@ -946,6 +1158,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     BQ_HIP_TRY(hipMemcpyAsync(b->h_bc, b->d_bc, sizeof(BatchCtl), hipMemcpyDeviceToHost, s));
     BQ_HIP_TRY(hipEventRecord(b->ev_done, s));
     b->started = count;
+    b->sweeping = sweep;
     b->last.grid = grid;
     return BQ_OK;
 }
@@ -980,7 +1193,7 @@ bq_status sssp_batch_finish(sssp_batch* b, int32_t* h_neg_cycle, int64_t* h_reac
     b->last.ms = ms;
     b->last.solve_ms = ms;
     b->last.grid = grid;
-    b->last.wg_size = SOLVE_WG;
+    b->last.wg_size = b->sweeping ? SWEEP_WG : SOLVE_WG;
     bq_status ret = BQ_OK;
     for (int i = 0; i < count; ++i) {
         const long long r = b->h_results[i];

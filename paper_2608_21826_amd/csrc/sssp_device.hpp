@@ -653,6 +653,24 @@ __device__ inline void flush_stats(bq::Word* stats, WaveStats& st) {
     st = WaveStats{};
 }
 
+// A workgroup's counters summed in LDS (sum[0..ST_N), any LDS words the caller
+// is done with): one atomic per counter and workgroup instead of one per wave.
+// Whole workgroup.
+__device__ inline void sum_stats(unsigned long long* sum, WaveStats& st) {
+    __syncthreads();
+    if (threadIdx.x < (unsigned)bq::ST_N) sum[threadIdx.x] = 0ull;
+    __syncthreads();
+    for (int off = 32; off > 0; off >>= 1) st.impr += __shfl_xor(st.impr, off, 64);
+    if (bq::lane_id() == 0) {
+        const unsigned long long v[bq::ST_N] = {st.deq,  st.relax, st.push, st.fan,  st.batch,
+                                                st.walk, st.spins, st.impr, st.idle, st.poll};
+        for (int i = 0; i < bq::ST_N; ++i)
+            if (v[i]) atomicAdd(&sum[i], v[i]);
+    }
+    __syncthreads();
+    st = WaveStats{};
+}
+
 // The persistent solver loop of one wave on one query: dequeue a batch,
 // stage it, scan its edges, publish improved vertices; until the query's
 // pending work is 0 (returns 1) or it is stopped (returns -1). The whole

@@ -6,6 +6,9 @@
 #include <limits.h>
 
 #include "sssp_device.hpp"
+#include "sssp_init.hpp"
+#include "sssp_small.hpp"
+#include "sssp_sweep.hpp"
 
 namespace {
 
@@ -13,83 +16,6 @@ namespace {
 // init: keys, the per-block weight range, and (block 0) the control block
 // with the source already enqueued
 // ---------------------------------------------------------------------------
-constexpr int INIT_WG = 256;
-constexpr int INIT_MAX_BLOCKS = 1024;
-
-// Keys of a new solve, in 16-byte stores after a scalar head up to 16-byte
-// alignment and with a scalar tail (the caller's array needs only its
-// element alignment).
-__device__ __forceinline__ void init_keys(long long* key, int n, int src, unsigned shift,
-                                          long long tid, long long stride) {
-    const long long srckey = pack_key(0, (1u << (shift - 1u)) - 1u, shift);
-    const long long head = (((uintptr_t)key & 15u) && n > 0) ? 1 : 0;
-    const long long n2 = (n - head) >> 1;
-    for (long long v = tid; v < head; v += stride) key[v] = (v == src) ? srckey : KEY_INF;
-    longlong2* k2 = (longlong2*)(key + head);
-    for (long long i = tid; i < n2; i += stride) {
-        const long long v0 = head + 2 * i;
-        longlong2 x;
-        x.x = (v0 == src) ? srckey : KEY_INF;
-        x.y = (v0 + 1 == src) ? srckey : KEY_INF;
-        k2[i] = x;
-    }
-    for (long long v = head + 2 * n2 + tid; v < n; v += stride)
-        key[v] = (v == src) ? srckey : KEY_INF;
-}
-
-// A thread's share of the weight range, in 16-byte loads (head and tail as
-// above).
-__device__ __forceinline__ void weight_range(const int* w, long long m, long long tid,
-                                             long long stride, int& lo, int& hi) {
-    lo = INT_MAX;
-    hi = INT_MIN;
-    long long wh = (long long)(((16u - ((uintptr_t)w & 15u)) & 15u) >> 2);
-    if (wh > m) wh = m;
-    const long long m4 = (m - wh) >> 2;
-    for (long long e = tid; e < wh; e += stride) {
-        const int x = w[e];
-        lo = x < lo ? x : lo;
-        hi = x > hi ? x : hi;
-    }
-    const int4* w4 = (const int4*)(w + wh);
-    for (long long i = tid; i < m4; i += stride) {
-        const int4 x = w4[i];
-        const int l01 = x.x < x.y ? x.x : x.y, l23 = x.z < x.w ? x.z : x.w;
-        const int h01 = x.x > x.y ? x.x : x.y, h23 = x.z > x.w ? x.z : x.w;
-        const int l = l01 < l23 ? l01 : l23, h = h01 > h23 ? h01 : h23;
-        lo = l < lo ? l : lo;
-        hi = h > hi ? h : hi;
-    }
-    for (long long e = wh + 4 * m4 + tid; e < m; e += stride) {
-        const int x = w[e];
-        lo = x < lo ? x : lo;
-        hi = x > hi ? x : hi;
-    }
-}
-
-// The block's weight range into its pair of `wrange` (synchronizes).
-__device__ __forceinline__ void block_weight_range(int lo, int hi, int* wrange) {
-    for (int off = 32; off > 0; off >>= 1) {
-        const int a2 = __shfl_xor(lo, off, 64), b2 = __shfl_xor(hi, off, 64);
-        lo = a2 < lo ? a2 : lo;
-        hi = b2 > hi ? b2 : hi;
-    }
-    __shared__ int slo[INIT_WG / 64], shi[INIT_WG / 64];
-    if (bq::lane_id() == 0) {
-        slo[threadIdx.x >> 6] = lo;
-        shi[threadIdx.x >> 6] = hi;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < INIT_WG / 64; ++i) {
-            lo = slo[i] < lo ? slo[i] : lo;
-            hi = shi[i] > hi ? shi[i] : hi;
-        }
-        wrange[2 * blockIdx.x] = lo;
-        wrange[2 * blockIdx.x + 1] = hi;
-    }
-}
-
 __global__ __launch_bounds__(INIT_WG) void k_init(Queue q, long long* key, int n, int src,
                                                   unsigned shift, const int* w, long long m,
                                                   int* wrange /* [2 * gridDim.x] */) {
@@ -149,6 +75,65 @@ __global__ __launch_bounds__(SOLVE_WG_ONE, SSSP_MIN_WAVES) void k_solve(SolveArg
 template <int B, int UU>
 __global__ __launch_bounds__(SOLVE_WG_ONE, SSSP_MIN_WAVES) void k_solve_short(SolveArgs a) {
     solve_kernel_body<B, UU>(a);
+}
+
+// k_init's work (keys, weight range, control words) for the sweep form: also
+// finds whether a row is longer than C, clears the stamps of such rows, and
+// puts the source into the first buffer.
+__global__ __launch_bounds__(INIT_WG) void k_sweep_init(SolveArgs a, SweepArgs f, int* wrange) {
+    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    const long long C = 1ll << a.chunk_log;
+    init_keys((long long*)a.key, a.n, a.src, a.shift, tid, stride);
+    int lo, hi;
+    weight_range((const int*)a.w, a.m, tid, stride, lo, hi);
+    bool lr = false;
+    for (long long v = tid; v < a.n; v += stride)
+        if (a.off[v + 1] - a.off[v] > C) {
+            lr = true;
+            f.stamp[v] = 0u;
+        }
+    __shared__ int slr;
+    if (threadIdx.x == 0) slr = 0;
+    block_weight_range(lo, hi, wrange);  // synchronizes
+    if (lr) slr = 1;
+    __syncthreads();
+    if (threadIdx.x == 0) f.longp[blockIdx.x] = (unsigned)slr;
+    if (blockIdx.x != 0) return;
+    // block 0: control words and the source's items
+    sweep_seed(a, f, (unsigned)a.src, threadIdx.x, INIT_WG);
+    if (threadIdx.x != 0) return;
+    BQ_GLOBAL bq::Ctrl* q = a.q.ctrl;
+    q->abort.v = 0ull;
+    q->error.v = 0ull;
+    q->negcycle.v = 0ull;
+    q->aux[0].v = (unsigned long long)gridDim.x;  // number of partials
+    q->aux[4].v = bq::now_ticks();                // clock at start
+    for (int i = 0; i < bq::ST_N; ++i) q->stats[i].v = 0ull;
+}
+
+__global__ __launch_bounds__(SWEEP_WG) void k_sweep(SolveArgs a, SweepArgs f) {
+    __shared__ SweepLds<SWEEP_WAVES> S;
+    WaveStats st{};
+    sweep_instance<SWEEP_WAVES>(a, f, gridDim.x, S, st);
+    sum_stats(S.stats, st);
+    if (threadIdx.x < (unsigned)bq::ST_N && S.stats[threadIdx.x])
+        bq::add_rlx(&a.q.ctrl->stats[threadIdx.x].v, S.stats[threadIdx.x]);
+}
+
+// One query on one workgroup. `h` is the host's copy of the control block
+// (pinned memory): the result words and counters are stored there directly.
+__global__ __launch_bounds__(SMALL_WG) void k_small(SolveArgs a, int* pred, bq::Ctrl* h) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    WaveStats st{};
+    const SmallResult r = small_instance(a, (long long*)a.key, pred, nullptr, lds, st);
+    SmallLds& S = *(SmallLds*)lds;
+    sum_stats(S.stats, st);
+    if (threadIdx.x < (unsigned)bq::ST_N) h->stats[threadIdx.x].v = S.stats[threadIdx.x];
+    if (threadIdx.x != 0) return;
+    h->error.v = (unsigned long long)r.err;
+    h->negcycle.v = (unsigned long long)r.neg;
+    h->abort.v = 0ull;
 }
 
 // dist[v] = d, pred[v] = parent (INT64_MAX / -1 when unreached; pred[src] = -1;

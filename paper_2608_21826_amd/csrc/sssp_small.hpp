@@ -2,11 +2,12 @@
 // whose keys and queue fit one CU's LDS.
 //
 // Same keys, relaxations and results as the other forms. The keys (8 B per
-// vertex), the row starts (4 B) and both queue buffers (2 B per entry) live in LDS, so lowering a
-// label, publishing and the meeting between sweeps cost LDS round trips and a
-// workgroup barrier instead of memory-side atomics and a
-// barrier over the chip (1.25 against 6.4 us per sweep on a 64 x 64 grid); the CSR is read through the caches. Weight
-// range, solve and unpack are one launch.
+// vertex), the row starts (4 B) and both queue buffers (2 B per entry) live in
+// LDS, so lowering a label, publishing and the meeting between sweeps cost LDS
+// round trips and a workgroup barrier instead of memory-side atomics and a
+// barrier over the chip (1.25 against 6.4 us per sweep on a 64 x 64 grid); the
+// columns and weights are read through the caches. Weight range, solve and
+// unpack are one launch.
 //
 // A sweep gives each item to G lanes, G the power of two at or above the
 // average row length, SMALL_U items per group at a time. A row longer than
@@ -18,7 +19,7 @@
 #include <type_traits>
 
 #include "sssp_device.hpp"
-#include "sssp_kernels.hpp"
+#include "sssp_init.hpp"
 
 namespace {
 
@@ -35,15 +36,16 @@ struct SmallLds {
     unsigned nhub[3];       // long rows left for a sweep
     unsigned hub[2][SMALL_HUBS];
     long long hub_d[2][SMALL_HUBS];  // their sources' packed labels
-    unsigned long long stats[8];
+    unsigned long long stats[bq::ST_N];
     int neg, err;
     unsigned stop;          // 1 + the sweep that stopped the solve, 0 if none
 };
 
 // LDS bytes of a graph of n vertices
-inline size_t small_lds_bytes(int n) {
+constexpr size_t small_lds_bytes(int n) {
     return ((sizeof(SmallLds) + 15) & ~(size_t)15) + 16u * (size_t)n + 32u;
 }
+constexpr size_t small_lds_bytes_max() { return small_lds_bytes((int)SMALL_MAX_N); }
 
 struct SmallResult {
     int neg, err;
@@ -318,6 +320,7 @@ __device__ SmallResult small_instance(const SolveArgs& a, long long* dist, int* 
         }
         __syncthreads();
     }
+    for (int off = 32; off > 0; off >>= 1) st_relax += (unsigned)__shfl_xor((int)st_relax, off, 64);
     st.impr += st_impr;
     st.relax += st_relax;
     // ---- unpack ----------------------------------------------------------
@@ -338,46 +341,6 @@ __device__ SmallResult small_instance(const SolveArgs& a, long long* dist, int* 
         if (lane == 0 && redges) bq::add_rlx(reached, redges);
     }
     return SmallResult{S.neg, S.err};
-}
-
-// The workgroup's work counters, summed in LDS: the totals are in
-// S.stats[0..6] (dequeued, relaxed, pushed, walks, improved) afterwards.
-__device__ __forceinline__ void small_sum_stats(SmallLds& S, WaveStats& st) {
-    __syncthreads();
-    if (threadIdx.x < 8) S.stats[threadIdx.x] = 0ull;
-    __syncthreads();
-    for (int off = 32; off > 0; off >>= 1) {
-        st.impr += __shfl_xor(st.impr, off, 64);
-        st.relax += __shfl_xor(st.relax, off, 64);
-    }
-    if (bq::lane_id() == 0) {
-        atomicAdd(&S.stats[0], st.deq);
-        atomicAdd(&S.stats[1], st.relax);
-        atomicAdd(&S.stats[2], st.push);
-        atomicAdd(&S.stats[3], st.walk);
-        atomicAdd(&S.stats[4], st.impr);
-    }
-    __syncthreads();
-}
-
-// One query on one workgroup. `h` is the host's copy of the control block
-// (pinned memory): the result words and counters are stored there directly.
-__global__ __launch_bounds__(SMALL_WG) void k_small(SolveArgs a, int* pred, bq::Ctrl* h) {
-    extern __shared__ __align__(16) unsigned char lds[];
-    WaveStats st{};
-    const SmallResult r = small_instance(a, (long long*)a.key, pred, nullptr, lds, st);
-    SmallLds& S = *(SmallLds*)lds;
-    small_sum_stats(S, st);
-    if (threadIdx.x != 0) return;
-    h->error.v = (unsigned long long)r.err;
-    h->negcycle.v = (unsigned long long)r.neg;
-    h->abort.v = 0ull;
-    for (int i = 0; i < bq::ST_N; ++i) h->stats[i].v = 0ull;
-    h->stats[bq::ST_DEQ].v = S.stats[0];
-    h->stats[bq::ST_RELAX].v = S.stats[1];
-    h->stats[bq::ST_PUSH].v = S.stats[2];
-    h->stats[bq::ST_WALK].v = S.stats[3];
-    h->stats[bq::ST_IMPROVE].v = S.stats[4];
 }
 
 }  // namespace

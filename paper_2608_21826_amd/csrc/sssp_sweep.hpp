@@ -49,10 +49,12 @@
 #include <limits.h>
 
 #include "sssp_device.hpp"
-#include "sssp_kernels.hpp"
+#include "sssp_init.hpp"
 
 namespace {
 
+constexpr int SWEEP_WG = 1024;
+constexpr int SWEEP_WAVES = SWEEP_WG / 64;
 constexpr int SWEEP_U = 4;         // edges per lane per scan step
 constexpr int SWEEP_OUT = 512;     // LDS push buffer per wave
 constexpr int SWEEP_TILE = 2048;   // edges of a batch mapped to their items at a time
@@ -62,10 +64,10 @@ constexpr unsigned long long SWEEP_STOP = ~0ull;  // barrier epoch: leave
 // Barrier and tail words of one query, each on its own line.
 struct SweepCtl {
     bq::Word tail[3][MAX_SEG];  // chunk items << 32 | light items of a buffer's segment
-    bq::Word arrive[8];         // arrivals of the gang's workgroups, by rank mod 8
-    bq::Word root;              // full groups
-    bq::Word go;                // last epoch released
-    unsigned longp[1024];       // per init block: a row longer than C exists
+    bq::Word arrive[8];         // arrivals of the gang's members, by rank mod 8 (32 bits)
+    bq::Word root;              // full groups (32 bits)
+    bq::Word joined;            // workgroups that have asked to take part
+    bq::Word go;                // last sweep released << 32 | its members
 };
 
 struct SweepArgs {
@@ -73,6 +75,7 @@ struct SweepArgs {
     BQ_GLOBAL unsigned* light;             // [2][nseg][cap_light]
     BQ_GLOBAL unsigned long long* chunk;   // [2][nseg][cap_chunk]
     BQ_GLOBAL unsigned* stamp;             // [n] used for chunked rows only
+    BQ_GLOBAL unsigned* longp;             // per init block: a row longer than C exists
     unsigned cap_light;
     unsigned cap_chunk;
 };
@@ -91,41 +94,95 @@ template <int WAVES>
 struct SweepLds {
     SweepWave w[WAVES];
     long long red[WAVES][3];
-    unsigned long long stats[8];
+    unsigned long long stats[bq::ST_N];
     unsigned nout[WAVES];  // pushes each wave holds at the end of a sweep
     unsigned long long base;
-    int stop;
+    unsigned long long go;
+    unsigned rank;
 };
 
 __device__ __forceinline__ void sweep_stop(const SweepArgs& f) {
     __hip_atomic_fetch_max(&f.ctl->go.v, SWEEP_STOP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// All workgroups of the gang meet; returns false when the solve was stopped.
-// Arrivals go to one word per rank mod 8, the last of a group arrives at the
-// root, the last of the groups releases `go`, which is the only word the
-// waiting workgroups read (polling a word slows the atomics on it). 256
-// workgroups on one word took 4.2 us; 64 took 1.5 us. Every wait ends: past
-// the wait limit or the solve's deadline the waiter raises the timeout and
-// releases everyone with SWEEP_STOP.
+// A gang's members. A workgroup joins a solve when it gets to run and takes
+// part from the next sweep on; nobody waits for one that has not started, so
+// launches that share the chip (other streams, other gangs) cannot hold each
+// other up. The first to join gives the others 10 us before the first sweep.
+struct SweepGang {
+    unsigned rank, members, sweep;
+};
+
+// Join the solve (up to `want` workgroups). False when it is over, or stopped.
+// Every wait ends at the solve's deadline at the latest.
 template <int WAVES>
-__device__ bool gang_barrier(const SolveArgs& a, const SweepArgs& f, unsigned rank, unsigned gang,
-                             unsigned epoch, SweepLds<WAVES>& S, unsigned long long t_start) {
+__device__ bool gang_join(const SolveArgs& a, const SweepArgs& f, unsigned want, SweepGang& g,
+                          SweepLds<WAVES>& S, unsigned long long t_start) {
+    if (threadIdx.x == 0) {
+        BQ_GLOBAL SweepCtl* c = f.ctl;
+        const unsigned rank = (unsigned)bq::add_rlx(&c->joined.v, 1ull);
+        unsigned long long go = SWEEP_STOP;
+        const unsigned long long t0 = bq::now_ticks();
+        if (rank == 0) {
+            unsigned long long j;
+            do j = bq::ld_rlx(&c->joined.v);
+            while (j < want && bq::now_ticks() - t0 < 1000ull);
+            const unsigned long long was = __hip_atomic_fetch_max(
+                &c->go.v, j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            go = was == SWEEP_STOP ? was : j;
+        } else {
+            for (unsigned it = 1;; ++it) {
+                go = bq::ld_rlx(&c->go.v);
+                if (go == SWEEP_STOP || (unsigned)go > rank) break;
+                if ((it & 63u) == 0u && bq::now_ticks() - t_start > a.deadline) {
+                    go = SWEEP_STOP;
+                    break;
+                }
+            }
+        }
+        S.rank = rank;
+        S.go = go;
+    }
+    __syncthreads();
+    g.rank = S.rank;
+    g.members = (unsigned)S.go;
+    g.sweep = (unsigned)(S.go >> 32);
+    const bool in = S.go != SWEEP_STOP;
+    __syncthreads();
+    return in;
+}
+
+// The members meet after a sweep; returns false when the solve was stopped,
+// else g is the next sweep with the members it has. Arrivals go to one
+// self-resetting word per rank mod 8, the last of a group arrives at the root,
+// the last of the groups releases `go`, which is the only word the waiting
+// workgroups read (polling a word slows the atomics on it). 256 workgroups on
+// one word took 4.2 us; 64 took 1.5 us. Every wait ends: past the wait limit
+// or the solve's deadline the waiter raises the timeout and releases everyone
+// with SWEEP_STOP.
+template <int WAVES>
+__device__ bool gang_barrier(const SolveArgs& a, const SweepArgs& f, SweepGang& g,
+                             SweepLds<WAVES>& S, unsigned long long t_start) {
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
         BQ_GLOBAL SweepCtl* c = f.ctl;
-        const unsigned g = rank & 7u;
-        const unsigned ng = gang < 8u ? gang : 8u, gs = (gang + 7u - g) >> 3;
-        if (bq::add_rlx(&c->arrive[g].v, 1ull) + 1ull == (unsigned long long)gs * epoch &&
-            bq::add_rlx(&c->root.v, 1ull) + 1ull == (unsigned long long)ng * epoch)
-            __hip_atomic_fetch_max(&c->go.v, (unsigned long long)epoch, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned grp = g.rank & 7u;
+        const unsigned ng = g.members < 8u ? g.members : 8u, gs = (g.members + 7u - grp) >> 3;
+        const unsigned next = g.sweep + 1u;
+        if (atomicInc((unsigned*)&c->arrive[grp].v, gs - 1u) == gs - 1u) {
+            const unsigned long long j = bq::ld_rlx(&c->joined.v);
+            if (atomicInc((unsigned*)&c->root.v, ng - 1u) == ng - 1u) {
+                const unsigned m = (unsigned)j > g.members ? (unsigned)j : g.members;
+                __hip_atomic_fetch_max(&c->go.v, ((unsigned long long)next << 32) | m,
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
         const unsigned long long t0 = bq::now_ticks();
         unsigned long long go;
         for (unsigned it = 1;; ++it) {
             go = bq::ld_rlx(&c->go.v);
-            if (go >= epoch) break;
+            if ((unsigned)(go >> 32) >= next) break;
             if ((it & 63u) == 0u) {
                 const unsigned long long t = bq::now_ticks();
                 if (t - t0 > a.limit || t - t_start > a.deadline) {
@@ -139,10 +196,12 @@ __device__ bool gang_barrier(const SolveArgs& a, const SweepArgs& f, unsigned ra
             sweep_stop(f);
             go = SWEEP_STOP;
         }
-        S.stop = go == SWEEP_STOP;
+        S.go = go;
     }
     __syncthreads();
-    return S.stop == 0;
+    g.members = (unsigned)S.go;
+    ++g.sweep;
+    return S.go != SWEEP_STOP;
 }
 
 // Publish the wave's improved vertices L.out[0, cnt) for sweep `next`, one
@@ -294,11 +353,11 @@ __device__ __forceinline__ SweepSlot sweep_slot(unsigned nseg, unsigned pre, uns
     return SweepSlot{seg, g - first};
 }
 
-// One gang's solve of one query. Workgroup `rank` of `gang`; every workgroup
-// calls it with the same arguments otherwise. Returns 1 when the queue ran
-// empty, -1 when the solve was stopped (error or negative cycle).
+// One gang's solve of one query; up to `want` workgroups call it with the same
+// arguments. Returns 1 when the queue ran empty, -1 when the solve was stopped
+// (error or negative cycle) or over before this workgroup joined.
 template <int WAVES>
-__device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned rank, unsigned gang,
+__device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned want,
                               SweepLds<WAVES>& S, WaveStats& st) {
     const int lane = bq::lane_id();
     const unsigned wid = (unsigned)bq::bcast32(threadIdx.x >> 6);
@@ -319,7 +378,7 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned r
             const int x = a.wrange[2 * i], y = a.wrange[2 * i + 1];
             lo = x < lo ? x : lo;
             hi = y > hi ? y : hi;
-            lr |= f.ctl->longp[i];
+            lr |= f.longp[i];
         }
         for (int off = 32; off > 0; off >>= 1) {
             const int x = __shfl_xor(lo, off, 64), y = __shfl_xor(hi, off, 64);
@@ -354,16 +413,18 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned r
         lbound = (long long)(a.n - 1) * (wmin < 0 ? wmin : 0ll);
     }
 
-    const unsigned home = rank % a.nseg;
-    const unsigned W = gang * WAVES;
-    // consecutive batches go to different workgroups, so a short sweep
-    // spreads over the gang's CUs
-    const unsigned gw = wid * gang + rank;
+    SweepGang g;
+    if (!gang_join<WAVES>(a, f, want, g, S, t_start)) return -1;
+    const unsigned home = g.rank % a.nseg;
     SweepWalk walk{};
     bool flagged = false;  // marking mode: this wave already raised negcycle
     int result = -1;
 
-    for (unsigned it = 0;; ++it) {
+    while (true) {
+        const unsigned it = g.sweep, W = g.members * WAVES;
+        // consecutive batches go to different workgroups, so a short sweep
+        // spreads over the gang's CUs
+        const unsigned gw = wid * g.members + g.rank;
         // ---- the sweep's items, by segment ------------------------------
         unsigned long long tw = 0;
         if ((unsigned)lane < a.nseg) tw = bq::ld_rlx(&f.ctl->tail[it % 3u][lane].v);
@@ -377,12 +438,13 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned r
             pre_c = (unsigned)incl_c - (unsigned)(tw >> 32);
         }
         if (NL + NC == 0u) {
+            if (g.rank == 0 && threadIdx.x == 0) sweep_stop(f);  // nobody joins any more
             result = 1;
             break;
         }
         // the buffer after next is empty; its words were last read before the
         // latest barrier
-        if (rank == 0 && threadIdx.x < a.nseg)
+        if (g.rank == 0 && threadIdx.x < a.nseg)
             bq::st_rlx(&f.ctl->tail[(it + 2u) % 3u][threadIdx.x].v, 0ull);
         const unsigned long long part0 = (unsigned long long)((it & 1u) * a.nseg);
         // batches: chunk items first (the hubs' rows: most labels fall through
@@ -547,96 +609,59 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned r
             sweep_publish_wg<WAVES>(a, f, S, wid, nout, it + 1u, home, st);
         else if (nout > 0)
             sweep_publish(a, f, L, nout, it + 1u, home, long_rows, st);
-        if (!gang_barrier<WAVES>(a, f, rank, gang, it + 1u, S, t_start)) break;
+        if (!gang_barrier<WAVES>(a, f, g, S, t_start)) break;
     }
     return result;
 }
 
-// Add the workgroup's work counters to a stats block, summed in LDS first:
-// one atomic per word and workgroup.
-template <int WAVES>
-__device__ void sweep_flush_stats(bq::Word* stats, WaveStats& st, SweepLds<WAVES>& S) {
-    __syncthreads();
-    if (threadIdx.x < 8) S.stats[threadIdx.x] = 0ull;
-    __syncthreads();
-    for (int off = 32; off > 0; off >>= 1) st.impr += __shfl_xor(st.impr, off, 64);
-    if (bq::lane_id() == 0) {
-        atomicAdd(&S.stats[0], st.deq);
-        atomicAdd(&S.stats[1], st.relax);
-        atomicAdd(&S.stats[2], st.push);
-        atomicAdd(&S.stats[3], st.fan);
-        atomicAdd(&S.stats[4], st.batch);
-        atomicAdd(&S.stats[5], st.walk);
-        atomicAdd(&S.stats[6], st.impr);
-    }
-    __syncthreads();
-    if (threadIdx.x < 7) {
-        const int to[7] = {bq::ST_DEQ,   bq::ST_RELAX, bq::ST_PUSH,   bq::ST_FANOUT,
-                           bq::ST_BATCH, bq::ST_WALK,  bq::ST_IMPROVE};
-        if (S.stats[threadIdx.x]) bq::add_rlx(&stats[to[threadIdx.x]].v, S.stats[threadIdx.x]);
-    }
-    st = WaveStats{};
-}
-
-// ---------------------------------------------------------------------------
-// single-query launch
-// ---------------------------------------------------------------------------
-constexpr int SWEEP_WG = 1024;
-constexpr int SWEEP_WAVES = SWEEP_WG / 64;
-
-// k_init's work (keys, weight range, control words) for the sweep form: also
-// finds whether a row is longer than C, clears the stamps of such rows, and
-// puts the source into the first buffer.
-__global__ __launch_bounds__(INIT_WG) void k_sweep_init(SolveArgs a, SweepArgs f, int* wrange) {
-    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long stride = (long long)gridDim.x * blockDim.x;
-    const long long C = 1ll << a.chunk_log;
-    init_keys((long long*)a.key, a.n, a.src, a.shift, tid, stride);
-    int lo, hi;
-    weight_range((const int*)a.w, a.m, tid, stride, lo, hi);
-    bool lr = false;
-    for (long long v = tid; v < a.n; v += stride)
-        if (a.off[v + 1] - a.off[v] > C) {
-            lr = true;
-            f.stamp[v] = 0u;
-        }
-    __shared__ int slr;
-    if (threadIdx.x == 0) slr = 0;
-    block_weight_range(lo, hi, wrange);  // synchronizes
-    if (lr) slr = 1;
-    __syncthreads();
-    if (threadIdx.x == 0) f.ctl->longp[blockIdx.x] = (unsigned)slr;
-    if (blockIdx.x != 0) return;
-    // block 0: control words and the source's items
+// Control words of a new solve and the source's items in the first buffer, by
+// `threads` threads of one workgroup (a.src's key position is `spos`).
+__device__ __forceinline__ void sweep_seed(const SolveArgs& a, const SweepArgs& f, unsigned spos,
+                                           unsigned tid, unsigned threads) {
     BQ_GLOBAL SweepCtl* c = f.ctl;
+    const long long C = 1ll << a.chunk_log;
     const long long deg = a.off[a.src + 1] - a.off[a.src];
     const unsigned nch = deg > C ? (unsigned)((deg + C - 1) >> a.chunk_log) : 0u;
-    for (unsigned k = threadIdx.x; k < nch; k += blockDim.x)
-        f.chunk[k] = ((unsigned long long)k << 32) | (unsigned)a.src;
-    if (threadIdx.x < 3 * MAX_SEG) {
-        const bool first = threadIdx.x == 0;
-        c->tail[threadIdx.x / MAX_SEG][threadIdx.x % MAX_SEG].v =
-            first ? (nch ? (unsigned long long)nch << 32 : 1ull) : 0ull;
-    }
-    if (threadIdx.x < 8) c->arrive[threadIdx.x].v = 0ull;
-    if (threadIdx.x != 0) return;
-    if (nch == 0) f.light[0] = (unsigned)a.src;
+    for (unsigned k = tid; k < nch; k += threads)
+        f.chunk[k] = ((unsigned long long)k << 32) | spos;
+    if (tid < 3 * MAX_SEG)
+        c->tail[tid / MAX_SEG][tid % MAX_SEG].v =
+            tid == 0 ? (nch ? (unsigned long long)nch << 32 : 1ull) : 0ull;
+    if (tid < 8) c->arrive[tid].v = 0ull;
+    if (tid != 0) return;
+    if (nch == 0) f.light[0] = spos;
     c->root.v = 0ull;
+    c->joined.v = 0ull;
     c->go.v = 0ull;
-    BQ_GLOBAL bq::Ctrl* q = a.q.ctrl;
-    q->abort.v = 0ull;
-    q->error.v = 0ull;
-    q->negcycle.v = 0ull;
-    q->aux[0].v = (unsigned long long)gridDim.x;  // number of partials
-    q->aux[4].v = bq::now_ticks();                // clock at start
-    for (int i = 0; i < bq::ST_N; ++i) q->stats[i].v = 0ull;
 }
 
-__global__ __launch_bounds__(SWEEP_WG) void k_sweep(SolveArgs a, SweepArgs f) {
-    __shared__ SweepLds<SWEEP_WAVES> S;
-    WaveStats st{};
-    sweep_instance<SWEEP_WAVES>(a, f, blockIdx.x, gridDim.x, S, st);
-    sweep_flush_stats<SWEEP_WAVES>((bq::Word*)a.q.ctrl->stats, st, S);
+// Chunk items one buffer's segment holds at most: a row longer than C gives
+// ceil(degree / C) <= 2 degree / C of them.
+inline unsigned long long sweep_chunk_cap(long long m, unsigned chunk_log) {
+    return 2ull * ((unsigned long long)m >> chunk_log) + 64ull;
+}
+
+// Memory of a sweep solve, carved from `base` (256-byte aligned): words, the
+// light and chunk items of the two buffers, the stamps. Returns its size.
+// f->longp is the caller's.
+inline unsigned long long sweep_layout(char* base, int n, long long m, unsigned chunk_log, int nseg,
+                                       SweepArgs* f) {
+    unsigned long long at = 0;
+    auto take = [&](unsigned long long bytes) {
+        char* p = base + at;
+        at += (bytes + 255ull) & ~255ull;
+        return p;
+    };
+    const unsigned long long cl = (unsigned long long)n, cc = sweep_chunk_cap(m, chunk_log);
+    SweepArgs t{};
+    t.ctl = (decltype(t.ctl))take(sizeof(SweepCtl));
+    t.light = (decltype(t.light))take(4ull * 2ull * (unsigned long long)nseg * cl);
+    t.chunk = (decltype(t.chunk))take(8ull * 2ull * (unsigned long long)nseg * cc);
+    t.stamp = (decltype(t.stamp))take(4ull * cl);
+    t.cap_light = (unsigned)cl;
+    t.cap_chunk = (unsigned)cc;
+    if (f) *f = t;
+    return at;
 }
 
 }  // namespace
