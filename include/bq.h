@@ -62,8 +62,9 @@ typedef struct sssp_rounds_ctx sssp_rounds_ctx;
 /* Launch shape. Zero fields mean "library default". */
 typedef struct {
     int32_t wg_size;      /* threads per workgroup, multiple of 64 (<= 1024) */
-    int32_t wg_count;     /* workgroups; 0 = the call's default: queue
-                             benchmarks fill the chip (occupancy x CUs);
+    int32_t wg_count;     /* workgroups; 0 = the call's default: Global Mixed
+                             runs one per CU, the bulk queue operations at
+                             most 4 per CU;
                              sssp_bf takes about one (of 16 waves) per 128
                              units of n + m/16, at most one per CU; with
                              buckets or a timeline one (of 2 waves) per 8K
@@ -201,24 +202,21 @@ bq_status bq_destroy(bq_queue* q);
  * zeroed). Needed after BQ_ETIMEOUT. */
 bq_status bq_reset(bq_queue* q, void* stream);
 
-/* ENQUEUE of n values d_vals[0..n) by a launch of wave-aggregated lanes (a
- * wave moves chunks of 64*b values, b = launch->ticket_batch, 64*b <=
- * capacity; BQ_F_BWD selects the single-shot broker check).
- * Each value is Successful or Full (Alg. 1); with no concurrent dequeuer the
- * first min(n, capacity - size) positions taken succeed. *d_n_ok (device,
- * uint64, overwritten) receives the number of successes. Which values
- * succeed, and their order in the queue, depend on the schedule, except for
- * launch->wg_count = 1 and wg_size = 64 (one wave), which enqueues in array
- * order. launch may be NULL. n = 0 launches nothing and writes 0 to *d_n_ok
+/* ENQUEUE of n values d_vals[0..n) by a launch that has the queue to itself
+ * and reserves for all of them at once (launch: wg_size and wg_count shape it;
+ * ticket_batch needs 64*b <= capacity as in the benchmarks below and BQ_F_BWD
+ * is accepted, without effect on the result). Each value is Successful or Full
+ * (Alg. 1): the first min(n, capacity - size) values are enqueued, in array
+ * order. *d_n_ok (device or pinned host memory, uint64, overwritten) receives
+ * the number of successes. launch may be NULL. n = 0 writes 0 to *d_n_ok
  * (d_vals may then be NULL). BQ_EINVAL for a NULL queue or d_n_ok, a NULL
  * d_vals with n > 0, or a launch shape the queue cannot take.
  * Synchronous (returns after completion). */
 bq_status bq_enqueue(bq_queue* q, const int32_t* d_vals, uint64_t n, uint64_t* d_n_ok,
                      const bq_launch* launch, void* stream);
 
-/* DEQUEUE up to n values into d_out[0..*d_n_ok) (compacted; Empty for the
- * rest). With one wave (see bq_enqueue) the values come out in queue order.
- * Arguments and n = 0 as for bq_enqueue (d_out may be NULL when n = 0).
+/* DEQUEUE up to n values into d_out[0..*d_n_ok), in queue order (Empty for the
+ * rest). Arguments and n = 0 as for bq_enqueue (d_out may be NULL when n = 0).
  * Synchronous. */
 bq_status bq_dequeue(bq_queue* q, int32_t* d_out, uint64_t n, uint64_t* d_n_ok,
                      const bq_launch* launch, void* stream);

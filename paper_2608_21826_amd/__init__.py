@@ -245,6 +245,11 @@ class Queue:
         _check(lib().bq_create(capacity, 0, _stream(stream), ctypes.byref(h)), "bq_create")
         self.handle = h
         self.capacity = capacity
+        # the success count of a call: the kernel stores it to pinned host
+        # memory (the calls return after completion, one at a time per queue)
+        import torch
+        self._ok = torch.zeros(1, dtype=torch.int64, pin_memory=True)
+        self._ok_np = self._ok.numpy()
 
     def close(self):
         if self.handle:
@@ -259,19 +264,16 @@ class Queue:
     def enqueue(self, vals, launch=None, stream=None) -> int:
         import torch
         _need(vals, torch.int32, "vals")
-        ok = torch.zeros(1, dtype=torch.int64, device=vals.device)
-        _check(lib().bq_enqueue(self.handle, _ptr(vals), vals.numel(), _ptr(ok), _launch(launch),
-                                _stream(stream)), "bq_enqueue")
-        return int(ok.item())
+        _check(lib().bq_enqueue(self.handle, _ptr(vals), vals.numel(), _ptr(self._ok),
+                                _launch(launch), _stream(stream)), "bq_enqueue")
+        return int(self._ok_np[0])
 
     def dequeue(self, n: int, launch=None, stream=None, device="cuda"):
         import torch
         out = torch.empty(max(n, 1), dtype=torch.int32, device=device)
-        ok = torch.zeros(1, dtype=torch.int64, device=device)
-        _check(lib().bq_dequeue(self.handle, _ptr(out), n, _ptr(ok), _launch(launch),
+        _check(lib().bq_dequeue(self.handle, _ptr(out), n, _ptr(self._ok), _launch(launch),
                                 _stream(stream)), "bq_dequeue")
-        k = int(ok.item())
-        return out[:k]
+        return out[:int(self._ok_np[0])]
 
     def bench_enqdeq(self, n_ops: int, launch=None, stream=None):
         """Section IV "Global Enqueue-Dequeue": returns (enqueue stats, dequeue stats)."""

@@ -2,8 +2,11 @@
 // and the "Global Mixed" benchmark of Section IV, for gfx950.
 //
 // Kernels:
-//  k_bulk_enqueue  - ENQUEUE of an array of values, wave-aggregated
-//  k_bulk_dequeue  - DEQUEUE of up to n values into a compacted array
+//  k_transfer      - ENQUEUE of an array of values, or DEQUEUE of up to n values
+//                    into a compacted array, by a launch that has the queue to
+//                    itself
+//  k_bulk          - the same operations by waves that contend for the queue
+//                    ("Global Enqueue-Dequeue")
 //  k_bench_mixed   - even workgroups enqueue, odd workgroups dequeue,
 //                    concurrently, each lane retrying Full/Empty attempts
 #include <hip/hip_runtime.h>
@@ -48,10 +51,9 @@ __device__ __forceinline__ Queue view(unsigned long long* sl, bq::Ctrl* c, uint3
 }
 
 // One wave moves one chunk of `cnt` operations (cnt <= 64*b). ENQ: item j
-// enqueues vals[first + j] (or first + j when vals is NULL); !ENQ: item j
-// dequeues into out[] at an index taken from *n_out (compacted, position
-// order within a reservation). Successful items are always a prefix of the
-// chunk, so one wave keeps array order.
+// enqueues the value first + j. With `log` the value written at (read from)
+// position P is stored at log[P]. Successful items are always a prefix of the
+// chunk, so one wave keeps their order.
 //
 // After a reservation that did not cover the rest of the chunk:
 //  - Broker Queue (Alg. 1 ENQUEUE / DEQUEUE): look at head and tail; if the
@@ -64,11 +66,9 @@ __device__ __forceinline__ Queue view(unsigned long long* sl, bq::Ctrl* c, uint3
 // Returns the number done; *fails counts Full / Empty returns.
 template <bool ENQ>
 __device__ unsigned long long chunk_op(const Queue& q, unsigned long long first,
-                                       unsigned long long cnt, const int32_t* vals, int32_t* out,
-                                       unsigned long long* n_out, int32_t* log,
-                                       bool bwd, bool retry, unsigned long long limit,
-                                       unsigned long long& spins, unsigned long long& fails,
-                                       bool& bad) {
+                                       unsigned long long cnt, int32_t* log, bool bwd, bool retry,
+                                       unsigned long long limit, unsigned long long& spins,
+                                       unsigned long long& fails, bool& bad) {
     const int lane = bq::lane_id();
     unsigned long long done = 0;
     int level = 0;
@@ -76,39 +76,31 @@ __device__ unsigned long long chunk_op(const Queue& q, unsigned long long first,
     wd.arm(limit);
     while (done < cnt) {
         uint32_t e = 0;
-        unsigned long long base = 0, obase = 0;
+        unsigned long long base = 0;
         if (lane == 0) {
             const uint32_t want = (uint32_t)(cnt - done);
             e = ENQ ? bq::reserve_enqueue(q, want) : bq::reserve_dequeue(q, want);
-            if (e) {
+            if (e)
                 base = bq::add_rlx(ENQ ? &q.ctrl->tail.v : &q.ctrl->head.v, (unsigned long long)e);
-                if (!ENQ && n_out) obase = bq::add_rlx(n_out, (unsigned long long)e);
-            }
         }
         e = bq::bcast32(e);
         base = bq::bcast64(base);
-        obase = bq::bcast64(obase);
+        // One slice of 64 at a time: with both kinds of chunk under way the slots
+        // are seldom ready far ahead, and reading several slices' words together
+        // (as the rounds do) only adds loads to the lines that the other side
+        // writes (4 Mi operations at b = 64, 256 workgroups
+        // of 256: 113 us with one slice, 135 with two, 158 with four).
         for (uint32_t j0 = 0; j0 < e; j0 += 64) {
             const uint32_t j = j0 + (uint32_t)lane;
             const bool act = j < e;
             const unsigned long long pos = base + j;
-            const unsigned long long item = first + done + j;
-            if (ENQ) {
-                const uint32_t val = act ? (vals ? (uint32_t)vals[item] : (uint32_t)item) : 0u;
-                if (!bq::put_slots(q, act, pos, val, limit, spins)) {
-                    bad = true;
-                    return done;
-                }
-                if (act && log) log[pos] = (int32_t)val;
-            } else {
-                uint32_t val = 0;
-                if (!bq::read_slots(q, act, pos, val, limit, spins)) {
-                    bad = true;
-                    return done;
-                }
-                if (act && out) out[obase + j] = (int32_t)val;
-                if (act && log) log[pos] = (int32_t)val;
+            uint32_t val = (uint32_t)(first + done + j);
+            if (!(ENQ ? bq::put_slots(q, act, pos, val, limit, spins)
+                      : bq::read_slots(q, act, pos, val, limit, spins))) {
+                bad = true;
+                return done;
             }
+            if (act && log) log[pos] = (int32_t)val;
         }
         done += e;
         if (done == cnt) break;
@@ -139,6 +131,48 @@ __device__ unsigned long long chunk_op(const Queue& q, unsigned long long first,
     return done;
 }
 
+// ENQUEUE (ENQ) or DEQUEUE of n values by a launch that has the queue to
+// itself (calls on one queue do not overlap): one reservation for the whole
+// launch. Every workgroup reads the same count and tail (head), so value i has
+// position tail + i and no wave draws a ticket; every slot's ticket still
+// passes through its states, which are certain here: a reserved position's
+// slot is free for an enqueue and full for a dequeue. The last workgroup to
+// finish moves tail (head) and count, after all have read them. So a million
+// values cost one pass over values and slots; drawing 64 per ticket, 16,000
+// waves queued up on the count and tail words at 12 ns an atomic (enqueue
+// and dequeue of 2^20 values with default launches 1.2 ms).
+template <bool ENQ>
+__global__ void k_transfer(unsigned long long* slots, bq::Ctrl* ctrl, uint32_t logN,
+                           const int32_t* vals, int32_t* out, unsigned long long n,
+                           unsigned long long* n_ok) {
+    const unsigned long long N = 1ull << logN;
+    const unsigned long long base = bq::ld_rlx(ENQ ? &ctrl->tail.v : &ctrl->head.v);
+    const long long have = (long long)bq::ld_rlx(&ctrl->count.v);
+    const unsigned long long room = (unsigned long long)(ENQ ? (long long)N - have : have);
+    const unsigned long long e = n < room ? n : room;
+    const unsigned long long stride = (unsigned long long)gridDim.x * blockDim.x;
+    for (unsigned long long i = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x; i < e;
+         i += stride) {
+        const unsigned long long pos = base + i;
+        const uint32_t t = 2u * (uint32_t)(pos >> logN);
+        unsigned long long* slot = &slots[pos & (N - 1ull)];
+        if (ENQ) {
+            *slot = bq::slot_word(t + 1u, (uint32_t)vals[i]);
+        } else {
+            out[i] = (int32_t)(uint32_t)*slot;
+            *slot = bq::slot_word(t + 2u, 0u);
+        }
+    }
+    __syncthreads();  // the whole workgroup has read the words
+    if (threadIdx.x != 0) return;
+    if (bq::add_rlx(&ctrl->aux[5].v, 1ull) + 1ull != gridDim.x) return;
+    ctrl->aux[5].v = 0ull;
+    if (ENQ) ctrl->tail.v = base + e;
+    else ctrl->head.v = base + e;
+    ctrl->count.v = (unsigned long long)(have + (ENQ ? (long long)e : -(long long)e));
+    *n_ok = e;
+}
+
 // ENQUEUE (ENQ) or DEQUEUE of n operations, grid-stride over chunks of
 // 64*b; every operation makes one attempt (Successful / Full, data / Empty).
 // With lseg > 0 the queue is split into 2^lseg segments (see bq_queue):
@@ -146,9 +180,8 @@ __device__ unsigned long long chunk_op(const Queue& q, unsigned long long first,
 // [s n / 2^lseg, (s+1) n / 2^lseg).
 template <bool ENQ>
 __global__ void k_bulk(unsigned long long* slots, bq::Ctrl* ctrl, uint32_t logN,
-                       const int32_t* vals, int32_t* out, unsigned long long n,
-                       unsigned long long* n_ok, unsigned long long* stats,
-                       unsigned long long limit, unsigned b, int bwd, unsigned lseg) {
+                       unsigned long long n, unsigned long long* stats, unsigned long long limit,
+                       unsigned b, int bwd, unsigned lseg) {
     const unsigned S = 1u << lseg;
     const unsigned seg = blockIdx.x & (S - 1u);
     const Queue q = view(slots + ((unsigned long long)seg << (logN - lseg)), ctrl + seg,
@@ -164,13 +197,11 @@ __global__ void k_bulk(unsigned long long* slots, bq::Ctrl* ctrl, uint32_t logN,
     for (unsigned long long c = wave; c * K < per && !bad; c += waves) {
         const unsigned long long first = lo + c * K;
         const unsigned long long cnt = (per - c * K) < K ? (per - c * K) : K;
-        ok += chunk_op<ENQ>(q, first, cnt, vals, out, n_ok, nullptr, bwd != 0, false, limit, spins,
-                            fails, bad);
+        ok += chunk_op<ENQ>(q, first, cnt, nullptr, bwd != 0, false, limit, spins, fails, bad);
     }
     if (bq::lane_id() == 0) {
-        if (ENQ && ok) bq::add_rlx(n_ok, ok);
-        if (stats && fails) bq::add_rlx(&stats[ENQ ? 2 : 3], fails);
-        if (stats && ok) bq::add_rlx(&stats[ENQ ? 0 : 1], ok);
+        if (fails) bq::add_rlx(&stats[ENQ ? 2 : 3], fails);
+        if (ok) bq::add_rlx(&stats[ENQ ? 0 : 1], ok);
     }
 }
 
@@ -210,10 +241,8 @@ __global__ void k_bench_mixed(unsigned long long* slots, bq::Ctrl* ctrl, uint32_
     for (unsigned long long c = wave; c * K < per && !bad; c += waves) {
         const unsigned long long first = lo + c * K;
         const unsigned long long cnt = (per - c * K) < K ? (per - c * K) : K;
-        ok += enq ? chunk_op<true>(q, first, cnt, nullptr, nullptr, nullptr, elog, bwd != 0,
-                                   true, limit, spins, fails, bad)
-                  : chunk_op<false>(q, first, cnt, nullptr, nullptr, nullptr, dlog, bwd != 0,
-                                    true, limit, spins, fails, bad);
+        ok += enq ? chunk_op<true>(q, first, cnt, elog, bwd != 0, true, limit, spins, fails, bad)
+                  : chunk_op<false>(q, first, cnt, dlog, bwd != 0, true, limit, spins, fails, bad);
     }
     if (bq::lane_id() == 0) {
         if (ok) bq::add_rlx(&stats[enq ? 0 : 1], ok);
@@ -354,14 +383,11 @@ bq_status bq_counters(bq_queue* q, void* stream, uint64_t* h_head, uint64_t* h_t
     return BQ_OK;
 }
 
-// error words of every segment (the unsegmented queue uses block 0)
+// the error word (block 0's serves every segment: it is their `sig`)
 static bq_status check_error_and_reset(bq_queue* q, hipStream_t s) {
-    unsigned long long errs[MAX_QSEG];
-    for (unsigned i = 0; i < MAX_QSEG; ++i)
-        BQ_HIP_TRY(hipMemcpyAsync(&errs[i], &q->ctrl[i].error.v, 8, hipMemcpyDeviceToHost, s));
-    BQ_HIP_TRY(hipStreamSynchronize(s));
     unsigned long long err = 0;
-    for (unsigned i = 0; i < MAX_QSEG; ++i) err |= errs[i];
+    BQ_HIP_TRY(hipMemcpyAsync(&err, &q->ctrl->error.v, 8, hipMemcpyDeviceToHost, s));
+    BQ_HIP_TRY(hipStreamSynchronize(s));
     if (err != 0ull) {
         queue_zero(q, s);
         BQ_HIP_TRY(hipStreamSynchronize(s));
@@ -370,55 +396,75 @@ static bq_status check_error_and_reset(bq_queue* q, hipStream_t s) {
     return BQ_OK;
 }
 
-static bq_status bulk(bq_queue* q, bool enq, const int32_t* vals, int32_t* out, uint64_t n,
-                      uint64_t* d_n_ok, unsigned long long* d_stats, const bq_launch* launch,
-                      hipStream_t s, bool reset_count, unsigned lseg) {
-    bqh::Launch L = bqh::resolve(launch, 4 * bqh::device_cus());
-    if (L.wg_size % 64 || L.wg_size > 1024 || L.batch < 1 ||
-        64ull * (unsigned long long)L.batch > (unsigned long long)(q->capacity >> lseg))
+// launch shape of the bulk operations and of "Global Enqueue-Dequeue"
+static bq_status bulk_shape(const bq_queue* q, const bq_launch* launch, unsigned lseg,
+                            bqh::Launch* out) {
+    *out = bqh::resolve(launch, 4 * bqh::device_cus());
+    if (out->wg_size % 64 || out->wg_size > 1024 || out->batch < 1 ||
+        64ull * (unsigned long long)out->batch > (unsigned long long)(q->capacity >> lseg))
         return BQ_EINVAL;
-    if (reset_count) BQ_HIP_TRY(hipMemsetAsync(d_n_ok, 0, 8, s));
-    if (n) {
-        const unsigned long long S = 1ull << lseg;
-        const unsigned long long K = 64ull * (unsigned long long)L.batch;
-        const unsigned long long chunks = S * (((n >> lseg) + K - 1) / K);
-        const unsigned long long wpb = (unsigned long long)(L.wg_size / 64);
-        unsigned long long g = (chunks + wpb - 1) / wpb;
-        if (g > (unsigned long long)L.wg_count) g = (unsigned long long)L.wg_count;
-        g -= g % S;  // every segment gets the same number of workgroups
-        if (g < S) g = S;
-        const int bwd = (L.flags & BQ_F_BWD) ? 1 : 0;
-        if (enq)
-            hipLaunchKernelGGL(k_bulk<true>, dim3((unsigned)g), dim3(L.wg_size), 0, s, q->slots,
-                               q->ctrl, q->logN, vals, (int32_t*)nullptr, (unsigned long long)n,
-                               (unsigned long long*)d_n_ok, d_stats, L.limit,
-                               (unsigned)L.batch, bwd, lseg);
-        else
-            hipLaunchKernelGGL(k_bulk<false>, dim3((unsigned)g), dim3(L.wg_size), 0, s, q->slots,
-                               q->ctrl, q->logN, (const int32_t*)nullptr, out,
-                               (unsigned long long)n, (unsigned long long*)d_n_ok, d_stats,
-                               L.limit, (unsigned)L.batch, bwd, lseg);
-        BQ_HIP_TRY(hipGetLastError());
-    }
+    return BQ_OK;
+}
+
+static bq_status bulk(bq_queue* q, bool enq, uint64_t n, unsigned long long* d_stats,
+                      const bq_launch* launch, hipStream_t s, unsigned lseg) {
+    bqh::Launch L;
+    bq_status st = bulk_shape(q, launch, lseg, &L);
+    if (st != BQ_OK) return st;
+    const unsigned long long S = 1ull << lseg;
+    const unsigned long long K = 64ull * (unsigned long long)L.batch;
+    const unsigned long long chunks = S * (((n >> lseg) + K - 1) / K);
+    const unsigned long long wpb = (unsigned long long)(L.wg_size / 64);
+    unsigned long long g = (chunks + wpb - 1) / wpb;
+    if (g > (unsigned long long)L.wg_count) g = (unsigned long long)L.wg_count;
+    g -= g % S;  // every segment gets the same number of workgroups
+    if (g < S) g = S;
+    const int bwd = (L.flags & BQ_F_BWD) ? 1 : 0;
+    if (enq)
+        hipLaunchKernelGGL(k_bulk<true>, dim3((unsigned)g), dim3(L.wg_size), 0, s, q->slots,
+                           q->ctrl, q->logN, (unsigned long long)n, d_stats, L.limit,
+                           (unsigned)L.batch, bwd, lseg);
+    else
+        hipLaunchKernelGGL(k_bulk<false>, dim3((unsigned)g), dim3(L.wg_size), 0, s, q->slots,
+                           q->ctrl, q->logN, (unsigned long long)n, d_stats, L.limit,
+                           (unsigned)L.batch, bwd, lseg);
+    BQ_HIP_TRY(hipGetLastError());
+    return BQ_OK;
+}
+
+// bq_enqueue / bq_dequeue: 4 values per thread, at most the launch's grid
+static bq_status transfer(bq_queue* q, bool enq, const int32_t* vals, int32_t* out, uint64_t n,
+                          uint64_t* d_n_ok, const bq_launch* launch, hipStream_t s) {
+    bqh::Launch L;
+    bq_status st = bulk_shape(q, launch, 0, &L);
+    if (st != BQ_OK) return st;
+    const unsigned long long per = 4ull * (unsigned long long)L.wg_size;
+    unsigned long long g = (n + per - 1) / per;
+    if (g > (unsigned long long)L.wg_count) g = (unsigned long long)L.wg_count;
+    if (g < 1) g = 1;
+    if (enq)
+        hipLaunchKernelGGL(k_transfer<true>, dim3((unsigned)g), dim3(L.wg_size), 0, s, q->slots,
+                           q->ctrl, q->logN, vals, (int32_t*)nullptr, (unsigned long long)n,
+                           (unsigned long long*)d_n_ok);
+    else
+        hipLaunchKernelGGL(k_transfer<false>, dim3((unsigned)g), dim3(L.wg_size), 0, s, q->slots,
+                           q->ctrl, q->logN, (const int32_t*)nullptr, out, (unsigned long long)n,
+                           (unsigned long long*)d_n_ok);
+    BQ_HIP_TRY(hipGetLastError());
+    BQ_HIP_TRY(hipStreamSynchronize(s));
     return BQ_OK;
 }
 
 bq_status bq_enqueue(bq_queue* q, const int32_t* d_vals, uint64_t n, uint64_t* d_n_ok,
                      const bq_launch* launch, void* stream) {
     if (!q || !d_n_ok || (n && !d_vals)) return BQ_EINVAL;
-    hipStream_t s = bqh::as_stream(stream);
-    bq_status st = bulk(q, true, d_vals, nullptr, n, d_n_ok, nullptr, launch, s, true, 0);
-    if (st != BQ_OK) return st;
-    return check_error_and_reset(q, s);
+    return transfer(q, true, d_vals, nullptr, n, d_n_ok, launch, bqh::as_stream(stream));
 }
 
 bq_status bq_dequeue(bq_queue* q, int32_t* d_out, uint64_t n, uint64_t* d_n_ok,
                      const bq_launch* launch, void* stream) {
     if (!q || !d_n_ok || (n && !d_out)) return BQ_EINVAL;
-    hipStream_t s = bqh::as_stream(stream);
-    bq_status st = bulk(q, false, nullptr, d_out, n, d_n_ok, nullptr, launch, s, true, 0);
-    if (st != BQ_OK) return st;
-    return check_error_and_reset(q, s);
+    return transfer(q, false, nullptr, d_out, n, d_n_ok, launch, bqh::as_stream(stream));
 }
 
 bq_status bq_bench_enqdeq(bq_queue* q, uint64_t n_ops, const bq_launch* launch,
@@ -432,18 +478,15 @@ bq_status bq_bench_enqdeq(bq_queue* q, uint64_t n_ops, const bq_launch* launch,
     if (st != BQ_OK) return st;
     BQ_HIP_TRY(hipMemsetAsync(q->scratch, 0, 128, s));
     unsigned long long* stats = q->scratch;
-    unsigned long long* cursor = q->scratch + 8;
     const unsigned long long half = n_ops / 2;
     hipEvent_t e0 = q->ev0, e1 = q->ev1;
     hipEvent_t e2;
     BQ_HIP_TRY(hipEventCreate(&e2));
     BQ_HIP_TRY(hipEventRecord(e0, s));
-    st = bulk(q, true, nullptr, nullptr, half, (uint64_t*)cursor, stats, launch, s, false,
-              (unsigned)lseg);
+    st = bulk(q, true, half, stats, launch, s, (unsigned)lseg);
     if (st != BQ_OK) return st;
     BQ_HIP_TRY(hipEventRecord(e1, s));
-    st = bulk(q, false, nullptr, nullptr, half, (uint64_t*)(cursor + 1), stats, launch, s,
-              false, (unsigned)lseg);
+    st = bulk(q, false, half, stats, launch, s, (unsigned)lseg);
     if (st != BQ_OK) return st;
     BQ_HIP_TRY(hipEventRecord(e2, s));
     unsigned long long h[4];
@@ -476,7 +519,12 @@ bq_status bq_bench_mixed(bq_queue* q, uint64_t n_ops, const bq_launch* launch,
     int per_cu = 0;
     BQ_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_bench_mixed, L.wg_size, 0));
     const int max_grid = per_cu * bqh::device_cus();
-    int grid = L.wg_count > 0 ? L.wg_count : max_grid;
+    // Default: one workgroup per CU. More waves only queue up on the broker
+    // words and, on a small ring, on Full and Empty (4M operations, 16 items
+    // per lane, 64 Ki slots: 235 us with 64 to 512 workgroups, 300 with the
+    // co-resident 2,048; 1 Mi slots: 137-170).
+    const int fill = bqh::device_cus() < max_grid ? bqh::device_cus() : max_grid;
+    int grid = L.wg_count > 0 ? L.wg_count : (fill < S2 ? max_grid : fill);
     if (grid > max_grid) grid = max_grid;
     grid -= grid % S2;
     if (grid < S2) return BQ_EINVAL;
