@@ -370,9 +370,10 @@ bq_status sssp_rounds_destroy(sssp_rounds_ctx* ctx);
  * pred unspecified unless BQ_F_NEGINF is set), except:
  *  - BQ_ERANGE when (n+1) * (m+1) * max|w| >= 2^62 (the distances after n
  *    rounds must not overflow int64);
- *  - launch: wg_size 64..1024 (power of two), wg_count 0 = 2 per CU
- *    (clamped to the co-resident maximum), ticket_batch b = 1..64 edge ids
- *    per lane per queue operation (0 = 16), BQ_F_BWD and BQ_F_VALIDATE as
+ *  - launch: wg_size 64..1024 (power of two), wg_count 0 = one per 16 Ki
+ *    edges, 1 to 4 per CU (clamped to the co-resident maximum), ticket_batch
+ *    b = 1..64 edge ids per lane per queue operation (0 = about one operation
+ *    per wave and round), BQ_F_BWD and BQ_F_VALIDATE as
  *    for sssp_bf, and BQ_F_NEGINF (minus-infinity marking, see the flag);
  *    row_chunk, queue_scale and segments are ignored;
  *  - BQ_ETIMEOUT when one wait exceeds timeout_us or the whole solve

@@ -352,4 +352,73 @@ __device__ __forceinline__ bool read_slots(const Queue& q, bool active, unsigned
     return true;
 }
 
+// PUT_DATA for `cnt` consecutive positions from `pos`, value j being val(j)
+// (lane l holds l, 64 + l, ...). The slot words of K slices of 64 are read
+// together and the slices that are ready at the front are done at once, so a
+// chunk costs one round trip per K slices instead of one per slice; the first
+// slice with a slot that is not ready waits for it, and the words after it
+// are read again.
+template <int K, class Val>
+__device__ __forceinline__ bool put_chunk(const Queue& q, unsigned long long pos, uint32_t cnt,
+                                          const Val& val, unsigned long long limit,
+                                          unsigned long long& spins) {
+    const uint32_t lane = (uint32_t)lane_id();
+    for (uint32_t j0 = 0; j0 < cnt;) {
+        unsigned long long w[K];
+#pragma unroll
+        for (int r = 0; r < K; ++r) {
+            const uint32_t j = j0 + 64u * r + lane;
+            w[r] = j < cnt ? ld_rlx(&q.slots[(pos + j) & (q.N - 1ull)]) : 0ull;
+        }
+        uint32_t done = 0;
+#pragma unroll
+        for (int r = 0; r < K; ++r) {
+            const uint32_t j = j0 + 64u * r + lane;
+            const uint32_t t = 2u * round_of(q, pos + j);
+            if (done == 64u * r && j0 + done < cnt &&
+                __all(j >= cnt || (uint32_t)(w[r] >> 32) == t)) {
+                if (j < cnt) st_rlx(&q.slots[(pos + j) & (q.N - 1ull)], slot_word(t + 1u, val(j)));
+                done += 64u;
+            }
+        }
+        if (done == 0) {
+            const uint32_t j = j0 + lane;
+            if (!put_slots(q, j < cnt, pos + j, j < cnt ? val(j) : 0u, limit, spins)) return false;
+            done = 64u;
+        }
+        j0 += done;
+    }
+    return true;
+}
+
+// READ_DATA for up to K * 64 positions at once, the values kept by slice.
+template <int K>
+__device__ __forceinline__ bool read_slots_many(const Queue& q, unsigned long long pos,
+                                                uint32_t cnt, uint32_t (&val)[K],
+                                                unsigned long long limit,
+                                                unsigned long long& spins) {
+    const uint32_t lane = (uint32_t)lane_id();
+    unsigned long long w[K];
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+        const uint32_t j = 64u * r + lane;
+        w[r] = j < cnt ? ld_rlx(&q.slots[(pos + j) & (q.N - 1ull)]) : 0ull;
+        val[r] = 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+        if (64u * r >= cnt) break;
+        const uint32_t j = 64u * r + lane;
+        const bool act = j < cnt;
+        const uint32_t t = 2u * round_of(q, pos + j) + 1u;
+        if (__all(!act || (uint32_t)(w[r] >> 32) == t)) {
+            val[r] = (uint32_t)w[r];
+            if (act) st_rlx(&q.slots[(pos + j) & (q.N - 1ull)], slot_word(t + 1u, 0u));
+        } else if (!read_slots(q, act, pos + j, val[r], limit, spins)) {
+            return false;
+        }
+    }
+    return true;
+}
+
 }  // namespace bq

@@ -39,13 +39,13 @@ using bq::Queue;
 constexpr long long DINF = LLONG_MAX;
 constexpr int PREP_WG = 256;
 constexpr int ROUND_MAX_WG = 1024;
+constexpr int U = 8;  // slices of 64 items a wave has in flight
 
 // control words used here (bq::Ctrl): head / tail / count are the queue's;
-// aux[0] changes in the current round, aux[1] done, aux[2] dequeue position
-// where the current round's items start, aux[3] CSR defect, aux[4] max |w|,
-// aux[5] rounds run, stats[ST_IMPROVE] changes over all rounds,
+// aux[0] changes in the current round, aux[1] done, aux[3] CSR defect, aux[4]
+// max |w|, aux[5] rounds run, stats[ST_IMPROVE] changes over all rounds,
 // stats[ST_SPIN] ticket waits.
-enum : int { A_CHANGES = 0, A_DONE = 1, A_BASE = 2, A_BAD = 3, A_WMAX = 4, A_ROUNDS = 5 };
+enum : int { A_CHANGES = 0, A_DONE = 1, A_BAD = 3, A_WMAX = 4, A_ROUNDS = 5 };
 
 struct RoundArgs {
     Queue q;
@@ -70,7 +70,6 @@ __global__ void k_reset(bq::Ctrl* c) {
     c->negcycle.v = 0ull;
     c->aux[A_CHANGES].v = 0ull;
     c->aux[A_DONE].v = 0ull;
-    c->aux[A_BASE].v = c->head.v;
     c->aux[A_WMAX].v = 0ull;
     c->aux[A_ROUNDS].v = 0ull;
     for (int i = 0; i < bq::ST_N; ++i) c->stats[i].v = 0ull;
@@ -157,8 +156,14 @@ __global__ __launch_bounds__(PREP_WG) void k_edge_src(const long long* off, int 
     }
 }
 
-// One round: enqueue every edge id (grid-stride chunks of `items`), then
-// dequeue and relax until the round's m items have all been taken.
+// One round: every edge id is enqueued (grid-stride chunks of `items`) and
+// dequeued and relaxed once. A wave follows each chunk that it enqueues by a
+// dequeue of as many items, whichever they are: the items reserved for
+// dequeue never exceed those reserved for enqueue, so every dequeue's ENSURE
+// succeeds at once, no wave looks for work that is not there, and all m items
+// have a taker when the last wave is done. (Waves that first enqueued all and
+// then took what they found spent most of a round polling the count: a round
+// of 160k edges 450 us with 512 workgroups, 60 with 128.)
 __global__ __launch_bounds__(ROUND_MAX_WG) void k_round(RoundArgs a) {
     const Queue& q = a.q;
     bq::Ctrl* c = q.ctrl;
@@ -168,10 +173,11 @@ __global__ __launch_bounds__(ROUND_MAX_WG) void k_round(RoundArgs a) {
     const long long gw = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const long long K = a.items;
     unsigned long long spins = 0;
+    unsigned long long improved = 0;
 
-    // ---- ENQUEUE: ENSURE on count, positions from tail, PUT_DATA -------
     for (long long c0 = gw * K; c0 < a.m; c0 += waves * K) {
         const unsigned cnt = (unsigned)(a.m - c0 < K ? a.m - c0 : K);
+        // ---- ENQUEUE: ENSURE on count, positions from tail, PUT_DATA ---
         unsigned long long base = 0;
         unsigned ok = 0;
         if (lane == 0) {
@@ -181,77 +187,69 @@ __global__ __launch_bounds__(ROUND_MAX_WG) void k_round(RoundArgs a) {
         ok = bq::bcast32(ok);
         if (ok != cnt) {
             if (lane == 0) bq::raise_error(q, bq::ERR_FULL);
-            return;
+            break;
         }
         base = bq::bcast64(base);
-        for (unsigned i0 = 0; i0 < cnt; i0 += 64) {
-            const unsigned i = i0 + lane;
-            if (!bq::put_slots(q, i < cnt, base + i, (unsigned)(c0 + i), a.limit, spins)) return;
-        }
-    }
-
-    // ---- DEQUEUE and relax ---------------------------------------------
-    const unsigned long long end = bq::bcast64(bq::ld_rlx(&c->aux[A_BASE].v)) +
-                                   (unsigned long long)a.m;
-    bool optimistic = true;
-    // After a failed take a wave takes again only once the count shows
-    // items: a BWD take is blind, and a crowd of idle waves taking blindly
-    // would hold the count below zero and starve each other.
-    bool look = false;
-    bq::Watch idle;
-    idle.arm(a.limit);
-    int level = 0;
-    while (true) {
+        bool bad = !bq::put_chunk<U>(
+            q, base, cnt, [&](uint32_t j) { return (uint32_t)(c0 + j); }, a.limit, spins);
+        if (bad) break;
+        // ---- DEQUEUE as many and relax ---------------------------------
         unsigned e = 0;
-        unsigned long long base = 0;
-        if (lane == 0 && (!look || bq::ld_rlx((BQ_GLOBAL const long long*)(&c->count.v)) > 0)) {
-            e = bq::ensure_dequeue(q, (unsigned)K, optimistic, a.bwd != 0);
+        if (lane == 0) {
+            e = bq::ensure_dequeue(q, cnt, true, a.bwd != 0);
             if (e) base = bq::add_rlx(&c->head.v, (unsigned long long)e);
         }
         e = bq::bcast32(e);
-        optimistic = e == (unsigned)K;
-        look = e == 0;
-        if (e == 0) {
-            // the round is over for this wave once every item has a taker
-            if (bq::bcast64(bq::ld_rlx(&c->head.v)) >= end) break;
-            if (bq::aborted(q)) break;
-            if (idle.expired()) {
-                if (lane == 0) bq::raise_error(q, bq::ERR_TIMEOUT);
-                break;
-            }
-            bq::idle_backoff(level < 6 ? level++ : level, 64u);
-            continue;
+        if (e != cnt) {  // cannot happen, see above
+            if (lane == 0) bq::raise_error(q, bq::ERR_FULL);
+            break;
         }
-        level = 0;
-        idle.arm(a.limit);
         base = bq::bcast64(base);
-        unsigned improved = 0;
-        for (unsigned i0 = 0; i0 < e; i0 += 64) {
-            const unsigned i = i0 + lane;
-            unsigned id = 0;
-            if (!bq::read_slots(q, i < e, base + i, id, a.limit, spins)) {
-                i0 = e;  // aborted: leave with the wave
+        // U slices of 64 at a time: slot words, edges, labels and atomics of
+        // all of them are in flight together
+        for (unsigned i0 = 0; i0 < e; i0 += 64 * U) {
+            uint32_t id[U];
+            if (!bq::read_slots_many<U>(q, base + i0, e - i0, id, a.limit, spins)) {
+                bad = true;
                 break;
             }
-            bool lower = false;
-            if (i < e) {
-                const int u = a.esrc[id], v = a.col[id];
-                const long long du = bq::ld_rlx(&a.dist[u]);
-                if (du != DINF) {
-                    const long long cand = du + (long long)a.w[id];
-                    if (cand < bq::ld_rlx(&a.dist[v])) {
+            int u[U], v[U], w[U];
+            bool act[U];
+            long long du[U], dv[U];
+#pragma unroll
+            for (int r = 0; r < U; ++r) {
+                act[r] = i0 + 64u * r + (unsigned)lane < e;
+                u[r] = v[r] = w[r] = 0;
+                if (act[r]) {
+                    u[r] = a.esrc[id[r]];
+                    v[r] = a.col[id[r]];
+                    w[r] = a.w[id[r]];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < U; ++r) {
+                du[r] = act[r] ? bq::ld_rlx(&a.dist[u[r]]) : DINF;
+                dv[r] = act[r] ? bq::ld_rlx(&a.dist[v[r]]) : LLONG_MIN;
+            }
+            bool lower[U];
+#pragma unroll
+            for (int r = 0; r < U; ++r) {
+                lower[r] = false;
+                if (du[r] != DINF) {
+                    const long long cand = du[r] + (long long)w[r];
+                    if (cand < dv[r]) {
                         const long long old = __hip_atomic_fetch_min(
-                            &a.dist[v], cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        lower = cand < old;
+                            &a.dist[v[r]], cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        lower[r] = cand < old;
                     }
                 }
             }
-            improved += (unsigned)__popcll(bq::ballot(lower));
+#pragma unroll
+            for (int r = 0; r < U; ++r) improved += (unsigned long long)__popcll(bq::ballot(lower[r]));
         }
-        if (lane == 0 && improved)
-            bq::add_rlx(&c->aux[A_CHANGES].v, (unsigned long long)improved);
-        if (bq::aborted(q)) break;
+        if (bad || bq::aborted(q)) break;
     }
+    if (lane == 0 && improved) bq::add_rlx(&c->aux[A_CHANGES].v, improved);
     if (lane == 0 && spins) bq::add_rlx(&c->stats[bq::ST_SPIN].v, spins);
 }
 
@@ -277,7 +275,6 @@ __global__ void k_check(bq::Ctrl* c, long long round, int n, long long m) {
     c->aux[A_CHANGES].v = 0ull;
     c->stats[bq::ST_IMPROVE].v += changes;
     c->aux[A_ROUNDS].v = (unsigned long long)round + 1ull;
-    c->aux[A_BASE].v += (unsigned long long)m;
     if (changes == 0ull) {
         c->aux[A_DONE].v = 1ull;
     } else if (round == (long long)n - 1) {
@@ -476,7 +473,6 @@ bq_status sssp_bf_rounds(sssp_rounds_ctx* c, int32_t n, int64_t m, const int64_t
     if (n > c->max_n || m > c->max_m) return BQ_EBUSY;
     hipStream_t s = bqh::as_stream(stream);
     bqh::Launch L = bqh::resolve(launch, 0);
-    if (!launch || launch->ticket_batch <= 0) L.batch = 16;
     if (L.batch < 1 || L.batch > 64) return BQ_EINVAL;
     int wsi = -1;
     for (int i = 0; i < 5; ++i)
@@ -503,8 +499,24 @@ bq_status sssp_bf_rounds(sssp_rounds_ctx* c, int32_t n, int64_t m, const int64_t
         if (per_cu < 1) per_cu = 1;
     }
     const int max_grid = per_cu * bqh::device_cus();
-    int grid = L.wg_count > 0 ? L.wg_count : 2 * bqh::device_cus();
+    // Default grid: one workgroup of four waves per 16 Ki edges, from one to
+    // four per CU: 64 items per lane and queue operation at most, one operation
+    // per wave and round (RMAT-18 with 256 / 512 / 1,024 workgroups 1.07 / 1.20
+    // / 2.09 ms, RMAT-20 4.8 / 4.0 / 3.7 ms).
+    const long long cus = bqh::device_cus();
+    const long long per = ((long long)m + 16383) / 16384;
+    int grid = L.wg_count > 0 ? L.wg_count
+                              : (int)(per < cus ? cus : (per > 4 * cus ? 4 * cus : per));
     if (grid > max_grid) grid = max_grid;  // waits need every wave resident
+    // Default b: about one queue operation per wave and round, so that the
+    // rounds of small graphs reach every wave and those of large ones draw
+    // few tickets (RMAT-18 with 16 and 64 items per lane 2.57 and 1.16 ms, a
+    // random graph of 300 vertices with 1, 16 and 64 145, 198 and 335 us).
+    if (!launch || launch->ticket_batch <= 0) {
+        const long long waves = (long long)grid * (L.wg_size / 64);
+        L.batch = 1;
+        while (L.batch < 64 && 64ll * L.batch * waves < (long long)m) L.batch *= 2;
+    }
 
     RoundArgs a;
     a.q.slots = (decltype(a.q.slots))c->slots;
