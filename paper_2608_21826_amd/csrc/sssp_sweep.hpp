@@ -58,7 +58,8 @@ constexpr int SWEEP_WAVES = SWEEP_WG / 64;
 constexpr int SWEEP_U = 4;         // edges per lane per scan step
 constexpr int SWEEP_OUT = 512;     // LDS push buffer per wave
 constexpr int SWEEP_TILE = 2048;   // edges of a batch mapped to their items at a time
-constexpr unsigned SWEEP_CHUNKS_PER_BATCH = 32;
+constexpr unsigned SWEEP_LIGHT = 16;  // light and chunk items of a batch at most:
+constexpr unsigned SWEEP_CHUNKS = 4;  // see sweep_instance
 constexpr unsigned long long SWEEP_STOP = ~0ull;  // barrier epoch: leave
 
 // Barrier and tail words of one query, each on its own line.
@@ -448,11 +449,16 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned w
             bq::st_rlx(&f.ctl->tail[(it + 2u) % 3u][threadIdx.x].v, 0ull);
         const unsigned long long part0 = (unsigned long long)((it & 1u) * a.nseg);
         // batches: chunk items first (the hubs' rows: most labels fall through
-        // them), then light items; sized so that every wave has one
+        // them), then light items; sized so that every wave has one, and small
+        // enough that the labels, which are read when a batch begins, are fresh
+        // when its last row is scanned: with up to 64 light and 32 chunk items
+        // RMAT-20 relaxed 2.97 times its edges and took 916 us, with 16 and 4
+        // 2.27 times and 796 us (a random graph of 1M vertices 3.67 and 1,110
+        // against 3.32 and 1,049); 8 and 4 scan no faster (2.21, 806 us).
         unsigned cbs = (NC + W - 1u) / W;
-        cbs = cbs > SWEEP_CHUNKS_PER_BATCH ? SWEEP_CHUNKS_PER_BATCH : cbs;
+        cbs = cbs > SWEEP_CHUNKS ? SWEEP_CHUNKS : cbs;
         unsigned lbs = (NL + W - 1u) / W;
-        lbs = lbs > 64u ? 64u : lbs;
+        lbs = lbs > SWEEP_LIGHT ? SWEEP_LIGHT : lbs;
         const unsigned nbc = cbs ? (NC + cbs - 1u) / cbs : 0u;
         const unsigned nbl = lbs ? (NL + lbs - 1u) / lbs : 0u;
         // a sweep of few items relaxes without the look at the key before the
