@@ -15,7 +15,8 @@
 //              their gangs finish
 //  k_bunpack - per unit: distances and predecessors; per query: the result
 //              flags
-// With near / far buckets k_bsolve runs in place of k_bsweep: persistent
+// With near / far buckets, and when very many queries share one graph (see
+// crowded), k_bsolve runs in place of k_bsweep: persistent
 // workgroups claim queries from claim lists (queries sorted by size, each
 // listed in proportion to its work, so big queries get several workgroups)
 // and, when their list runs out, join an unfinished query; each runs the
@@ -180,44 +181,100 @@ __global__ void k_rm_place(const RemapDesc* R, int nr, int total_tiles) {
 // Every row of every remapped graph, reordered by the class of its targets
 // (stable, so each class keeps the row's order), into tcol (target key
 // positions) and tw (weights): a wave's lanes then read the keys of the
-// most pointed-at targets first and side by side. One wave per row.
-__global__ void k_rm_rows(const RemapDesc* R, int nr) {
+// most pointed-at targets first and side by side. A row of the first RM_LONG
+// classes, which are the first key positions, takes a workgroup, whose waves
+// count and then place a share of it each; any other takes a wave. (With
+// one wave for every row the reordering of RMAT-20 took 3.0 ms, most of it for
+// its longest row; now 1.2 ms.)
+constexpr int RM_LONG = 6;  // rows of 1,023 edges and more
+constexpr int RM_WG = 1024;
+constexpr int RM_U = 4;  // steps of 64 edges whose loads are in flight together
+
+// Counts (PLACE false) or placements of edges [e0, e1) of a row, by one wave:
+// next[k] grows by the edges of class k.
+template <bool PLACE>
+__device__ __forceinline__ void rm_part(const RemapDesc& d, long long e0, long long e1,
+                                        long long (&next)[RM_CLASSES]) {
     const int lane = bq::lane_id();
-    const long long waves = (long long)gridDim.x * (blockDim.x >> 6);
-    const long long wave = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    for (long long s = e0; s < e1; s += 64 * RM_U) {
+        int v[RM_U], c[RM_U], w[RM_U];
+        unsigned p[RM_U];
+#pragma unroll
+        for (int r = 0; r < RM_U; ++r) {
+            const long long i = s + 64 * r + lane;
+            v[r] = i < e1 ? d.col[i] : -1;
+            w[r] = PLACE && i < e1 ? d.w[i] : 0;
+        }
+#pragma unroll
+        for (int r = 0; r < RM_U; ++r) {
+            c[r] = v[r] >= 0 ? (int)d.cls[v[r]] : -1;
+            p[r] = PLACE && v[r] >= 0 ? d.pos[v[r]] : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < RM_U; ++r) {
+            long long at = 0;
+            for (int k = 0; k < RM_CLASSES; ++k) {
+                const unsigned long long mk = bq::ballot(c[r] == k);
+                if (PLACE && c[r] == k) at = next[k] + bq::rank_in(mk);
+                next[k] += __popcll(mk);
+            }
+            if (PLACE && c[r] >= 0) {
+                d.tcol[at] = p[r];
+                d.tw[at] = w[r];
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(RM_WG) void k_rm_rows(const RemapDesc* R, int nr) {
+    constexpr int WAVES = RM_WG / 64;
+    __shared__ int part[RM_CLASSES][WAVES];  // counts, then offsets in the row
+    const int lane = bq::lane_id(), wid = threadIdx.x >> 6;
     for (int r = 0; r < nr; ++r) {
         const RemapDesc& d = R[r];
-        for (long long u = wave; u < d.n; u += waves) {
+        const int n_long = d.hist[RM_LONG];  // first position of class RM_LONG
+        for (int x = blockIdx.x; x < n_long; x += gridDim.x) {
+            const unsigned u = d.orig[x];
             const long long s = d.off[u], e = d.off[u + 1];
-            int cnt[RM_CLASSES];
-            for (int k = 0; k < RM_CLASSES; ++k) cnt[k] = 0;
-            for (long long e0 = s; e0 < e; e0 += 64) {
-                const long long i = e0 + lane;
-                const int c = i < e ? (int)d.cls[d.col[i]] : -1;
-                for (int k = 0; k < RM_CLASSES; ++k) cnt[k] += __popcll(bq::ballot(c == k));
+            const long long share = (((e - s) + WAVES - 1) / WAVES + 63) & ~63ll;
+            const long long e0 = s + wid * share < e ? s + wid * share : e;
+            const long long e1 = e0 + share < e ? e0 + share : e;
+            long long next[RM_CLASSES];
+            for (int k = 0; k < RM_CLASSES; ++k) next[k] = 0;
+            rm_part<false>(d, e0, e1, next);
+            if (lane == 0)
+                for (int k = 0; k < RM_CLASSES; ++k) part[k][wid] = (int)next[k];
+            __syncthreads();
+            if (wid == 0) {  // exclusive scan in (class, wave) order, 4 counts per lane
+                int* f = &part[0][0];
+                static_assert(RM_CLASSES * WAVES == 256, "4 counts per lane");
+                const int a0 = f[4 * lane], a1 = f[4 * lane + 1], a2 = f[4 * lane + 2],
+                          a3 = f[4 * lane + 3];
+                const int before = bq::wave_incl_scan(a0 + a1 + a2 + a3) - (a0 + a1 + a2 + a3);
+                f[4 * lane] = before;
+                f[4 * lane + 1] = before + a0;
+                f[4 * lane + 2] = before + a0 + a1;
+                f[4 * lane + 3] = before + a0 + a1 + a2;
             }
-            int base[RM_CLASSES];
-            int run = 0;
+            __syncthreads();
+            for (int k = 0; k < RM_CLASSES; ++k) next[k] = s + part[k][wid];
+            rm_part<true>(d, e0, e1, next);
+            __syncthreads();  // part is written again for the next row
+        }
+        const int waves = (int)gridDim.x * WAVES;
+        for (long long u = (long long)blockIdx.x * WAVES + wid; u < d.n; u += waves) {
+            const long long s = d.off[u], e = d.off[u + 1];
+            if (e - s >= (1ll << (RM_CLASSES - RM_LONG)) - 1) continue;
+            long long next[RM_CLASSES];
+            for (int k = 0; k < RM_CLASSES; ++k) next[k] = 0;
+            rm_part<false>(d, s, e, next);
+            long long run = s;
             for (int k = 0; k < RM_CLASSES; ++k) {
-                base[k] = run;
-                run += cnt[k];
+                const long long c = next[k];
+                next[k] = run;
+                run += c;
             }
-            for (long long e0 = s; e0 < e; e0 += 64) {
-                const long long i = e0 + lane;
-                const bool live = i < e;
-                const int v = live ? d.col[i] : 0;
-                const int c = live ? (int)d.cls[v] : -1;
-                long long at = 0;
-                for (int k = 0; k < RM_CLASSES; ++k) {
-                    const unsigned long long mk = bq::ballot(c == k);
-                    if (c == k) at = s + base[k] + bq::rank_in(mk);
-                    base[k] += __popcll(mk);
-                }
-                if (live) {
-                    d.tcol[at] = d.pos[v];
-                    d.tw[at] = d.w[i];
-                }
-            }
+            rm_part<true>(d, s, e, next);
         }
     }
 }
@@ -279,7 +336,7 @@ __global__ __launch_bounds__(BINIT_WG) void k_binit(const InstDesc* D, const Uni
         __syncthreads();
         if (lr) slong = 1;
         if (sweep && u == d.unit_begin)
-            sweep_seed(a, d.f, (unsigned)spos, threadIdx.x, BINIT_WG);
+            sweep_seed(a, d.f, threadIdx.x, BINIT_WG);
         __syncthreads();
         if (threadIdx.x == 0) {
             for (int i = 1; i < BINIT_WG / 64; ++i) {
@@ -475,7 +532,13 @@ unsigned bkey_shift(int n) {
     return pb + 1u;
 }
 
-constexpr int GANG_MIN = 4;  // workgroups
+// Workgroups of a gang at least: 4, twice that when a query has more than
+// GANG_MIN_N vertices (64 sources of RMAT-18 with 64 and 32 gangs on 256
+// workgroups 13.4 and 11.1 ms, 64 random graphs of 500k vertices 45.7 and 41.7;
+// of RMAT-16 3.3 and 3.6).
+constexpr int GANG_MIN = 4;
+constexpr int GANG_MIN_N = 1 << 17;
+constexpr int CROWD_CHUNK = 512;  // rows' chunk items of a crowded batch
 
 // Work of a query in a gang, in edges of a random graph: a mesh's many short
 // sweeps cost about 16 times its edges (256 x 256 road mesh on 8 workgroups
@@ -489,6 +552,26 @@ long long gang_work(int n, long long m) {
 // gang.
 bool batch_small(int n, long long m, long long tot_work) {
     return (unsigned)n <= SMALL_MAX_N && (m <= 40960 || m < 6ll * n || m <= tot_work / 64);
+}
+
+// Whether so many queries share one graph that their keys leave no room in the
+// last-level cache (256 MiB) for anything else. Such a batch is bound by the
+// keys' lines: k_bsolve on remapped keys (the lines that most edges want side
+// by side) with its fewer waves relaxes less and hits more. 64 sources of
+// RMAT-20 39.5 ms against 51.8 by k_bsweep, 32 of RMAT-20 21.7 / 27.9, 128 of
+// RMAT-18 20.1 / 23.2, but 16 of RMAT-20 13.6 / 13.1 and 64 of RMAT-16 4.4 /
+// 3.3. A graph without hubs gains nothing (48 of a random graph of 1M vertices
+// 46.6 / 39.8), which n and m do not tell; meshes would lose half.
+bool crowded(const sssp_instance* x, int count) {
+    std::map<std::tuple<const void*, const void*, const void*, int, long long>, long long> keys;
+    for (int i = 0; i < count; ++i) {
+        if (x[i].m < 6ll * x[i].n) continue;
+        long long& k = keys[std::make_tuple((const void*)x[i].offsets, (const void*)x[i].cols,
+                                            (const void*)x[i].w, x[i].n, (long long)x[i].m)];
+        k += 8ll * x[i].n;
+        if (k > 128ll << 20) return true;
+    }
+    return false;
 }
 
 unsigned long long pow2ceil(unsigned long long x) {
@@ -569,7 +652,7 @@ bq_status batch_launch_kernels(sssp_batch* b, const LaunchShape& z) {
         hipLaunchKernelGGL(k_rm_hist, dim3(tg), dim3(64), 0, s, b->d_rm, z.nr, z.rm_tiles);
         hipLaunchKernelGGL(k_rm_scan, dim3(z.nr), dim3(1024), 0, s, b->d_rm, z.nr);
         hipLaunchKernelGGL(k_rm_place, dim3(tg), dim3(64), 0, s, b->d_rm, z.nr, z.rm_tiles);
-        hipLaunchKernelGGL(k_rm_rows, dim3(2048), dim3(256), 0, s, b->d_rm, z.nr);
+        hipLaunchKernelGGL(k_rm_rows, dim3(512), dim3(RM_WG), 0, s, b->d_rm, z.nr);
     }
     hipLaunchKernelGGL(k_binit, dim3(ug), dim3(BINIT_WG), 0, s, b->d_desc, b->d_units, z.n_units,
                        b->d_partials, b->d_bc, b->d_reached, z.count);
@@ -758,9 +841,15 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     if (b->started) return BQ_EBUSY;
     if (count > b->max_inst) return BQ_EBUSY;
     bqh::Launch L = bqh::resolve(launch, 0);
+    const bool crowd =
+        L.bucket_width == 0 && !(L.flags & BQ_F_NOREMAP) && crowded(h_inst, count);
+    if (crowd) {
+        if (!launch || launch->ticket_batch <= 0) L.batch = 4;
+        if (L.row_chunk <= 0) L.row_chunk = CROWD_CHUNK;
+    }
     if (L.batch != 1 && L.batch != 2 && L.batch != 4) return BQ_EINVAL;
     const int B = 64 * L.batch;
-    const bool sweep = L.bucket_width == 0;
+    const bool sweep = L.bucket_width == 0 && !crowd;
     unsigned clog = sweep ? BSWEEP_CHUNK_LOG : BDEFAULT_CHUNK_LOG;
     if (L.row_chunk > 0) {
         if (L.row_chunk & (L.row_chunk - 1)) return BQ_EINVAL;
@@ -803,7 +892,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     // the sweep form's queries: one workgroup in LDS, or a gang
     std::vector<char> small(count, 0);
     long long big_work = 0, big_most = 0;
-    int n_small = 0, n_big = 0, gangs = 0;
+    int n_small = 0, n_big = 0, big_n = 0, gangs = 0;
     int grid = 0;
     if (sweep) {
         long long want = 0;
@@ -816,18 +905,20 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
                 big_work += w;
                 big_most = w > big_most ? w : big_most;
                 ++n_big;
+                big_n = x.n > big_n ? x.n : big_n;
                 want += (x.n + x.m / 16) / 128 + 8;
             }
         }
         want += n_small;
         grid = L.wg_count > 0 ? L.wg_count : (want < max_grid ? (int)want : max_grid);
         if (grid > max_grid) grid = max_grid;
-        // gangs: as many as the biggest query leaves room for
+        // gangs: as many as the biggest query leaves room for; of big queries
+        // fewer, so that the keys in use stay in the caches
         gangs = 1;
+        const int least = big_n > GANG_MIN_N ? 2 * GANG_MIN : GANG_MIN;
         while (gangs * 2 <= n_big && gangs * 2 * big_most <= big_work &&
-               gangs * 2 * GANG_MIN <= grid)
+               gangs * 2 * least <= grid)
             gangs *= 2;
-        if (getenv("BQ_G")) gangs = atoi(getenv("BQ_G"));
     } else {
         // about one workgroup per 16K units of n + m/16 of each query, at
         // least one per query; more waves than the work can feed only raise
@@ -891,20 +982,21 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
             spare -= qps * extra * caps[k];
         }
     }
-    // Graphs that two or more queries share get the degree-class key layout:
-    // their queries keep keys in the workspace at key positions ordered by
+    // In k_bsolve graphs that two or more queries share get the degree-class key
+    // layout: their queries keep keys in the workspace at key positions ordered by
     // out-degree class, highest first, then by vertex id, so that the keys
     // most edges point at pack into few cache lines. Queries on a graph of
-    // their own keep their keys in their dist buffers.
+    // their own keep their keys in their dist buffers, and so do all of the
+    // sweep form (16 sources of RMAT-20 12.7 ms without, 12.6 with the layout
+    // and 1.7 to build it).
     std::vector<int> rm_of(count, -1);
     int nr = 0, rm_tiles = 0;
     {
         size_t rm_m = 0, rm_n = 0, key_need = 0;
         std::map<std::tuple<const void*, const void*, const void*, int, long long>,
                  std::vector<int>> shared;
-        if (!(L.flags & BQ_F_NOREMAP))
+        if (!sweep && !(L.flags & BQ_F_NOREMAP))
             for (int k = 0; k < count; ++k) {
-                if (small[k]) continue;
                 const sssp_instance& x = h_inst[order[k]];
                 shared[std::make_tuple((const void*)x.offsets, (const void*)x.cols,
                                        (const void*)x.w, x.n, (long long)x.m)]

@@ -101,7 +101,7 @@ __global__ __launch_bounds__(INIT_WG) void k_sweep_init(SolveArgs a, SweepArgs f
     if (threadIdx.x == 0) f.longp[blockIdx.x] = (unsigned)slr;
     if (blockIdx.x != 0) return;
     // block 0: control words and the source's items
-    sweep_seed(a, f, (unsigned)a.src, threadIdx.x, INIT_WG);
+    sweep_seed(a, f, threadIdx.x, INIT_WG);
     if (threadIdx.x != 0) return;
     BQ_GLOBAL bq::Ctrl* q = a.q.ctrl;
     q->abort.v = 0ull;

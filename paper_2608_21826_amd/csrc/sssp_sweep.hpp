@@ -84,7 +84,7 @@ struct SweepArgs {
 struct SweepWave {
     long long du[64];
     long long eb[64];      // row start minus the item's first position in the batch
-    unsigned pu[64];       // original id (parent field of candidates)
+    unsigned pu[64];       // vertex (parent field of candidates)
     int fan[64];
     unsigned hv[64];
     unsigned out[SWEEP_OUT];
@@ -223,8 +223,7 @@ __device__ __forceinline__ void sweep_publish(const SolveArgs& a, const SweepArg
         int nch = 0;
         if (long_rows) {
             if (live) {
-                const unsigned ov = orig_of(a, v);
-                const long long deg = a.off[ov + 1] - a.off[ov];
+                const long long deg = a.off[v + 1] - a.off[v];
                 if (deg > (1ll << a.chunk_log))
                     nch = (int)((deg + (1ll << a.chunk_log) - 1) >> a.chunk_log);
             }
@@ -488,16 +487,15 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned w
                 }
                 const long long old = __hip_atomic_fetch_and(
                     &a.key[v], ~1ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const unsigned ov = orig_of(a, v);
-                long long t = a.off[ov + 1];
-                eb = a.off[ov];
+                long long t = a.off[v + 1];
+                eb = a.off[v];
                 if (j >= 0) {
                     eb += j << a.chunk_log;
                     t = t < eb + C ? t : eb + C;
                 }
                 cnt = (int)(t - eb);
                 L.du[lane] = old >> shift;
-                L.pu[lane] = ov;
+                L.pu[lane] = v;
             }
             const int incl = bq::wave_incl_scan(cnt);
             const int pre = incl - cnt;
@@ -524,8 +522,8 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned w
                         if (live[r]) {
                             idx[r] = (int)L.own[t];
                             const long long edge = L.eb[idx[r]] + (T0 + t);
-                            tv[r] = target_of(a, edge);
-                            w[r] = weight_of(a, edge);
+                            tv[r] = a.col[edge];
+                            w[r] = a.w[edge];
                         }
                     }
 #pragma unroll
@@ -621,21 +619,21 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned w
 }
 
 // Control words of a new solve and the source's items in the first buffer, by
-// `threads` threads of one workgroup (a.src's key position is `spos`).
-__device__ __forceinline__ void sweep_seed(const SolveArgs& a, const SweepArgs& f, unsigned spos,
-                                           unsigned tid, unsigned threads) {
+// `threads` threads of one workgroup.
+__device__ __forceinline__ void sweep_seed(const SolveArgs& a, const SweepArgs& f, unsigned tid,
+                                           unsigned threads) {
     BQ_GLOBAL SweepCtl* c = f.ctl;
     const long long C = 1ll << a.chunk_log;
     const long long deg = a.off[a.src + 1] - a.off[a.src];
     const unsigned nch = deg > C ? (unsigned)((deg + C - 1) >> a.chunk_log) : 0u;
     for (unsigned k = tid; k < nch; k += threads)
-        f.chunk[k] = ((unsigned long long)k << 32) | spos;
+        f.chunk[k] = ((unsigned long long)k << 32) | (unsigned)a.src;
     if (tid < 3 * MAX_SEG)
         c->tail[tid / MAX_SEG][tid % MAX_SEG].v =
             tid == 0 ? (nch ? (unsigned long long)nch << 32 : 1ull) : 0ull;
     if (tid < 8) c->arrive[tid].v = 0ull;
     if (tid != 0) return;
-    if (nch == 0) f.light[0] = spos;
+    if (nch == 0) f.light[0] = (unsigned)a.src;
     c->root.v = 0ull;
     c->joined.v = 0ull;
     c->go.v = 0ull;
