@@ -337,6 +337,8 @@ __global__ __launch_bounds__(BINIT_WG) void k_binit(const InstDesc* D, const Uni
         if (lr) slong = 1;
         if (sweep && u == d.unit_begin)
             sweep_seed(a, d.f, threadIdx.x, BINIT_WG);
+        if (sweep && d.f.p.ctl != nullptr)
+            strip_seed(d.f.p, a.n, un.v0, un.v1, u == d.unit_begin, threadIdx.x, BINIT_WG);
         __syncthreads();
         if (threadIdx.x == 0) {
             for (int i = 1; i < BINIT_WG / 64; ++i) {
@@ -463,7 +465,10 @@ __global__ __launch_bounds__(SWEEP_WG) void k_bsweep(const InstDesc* __restrict_
         const int i = __builtin_amdgcn_readfirstlane(list[k]);
         const SolveArgs a = D[i].a;
         const SweepArgs f = D[i].f;
-        sweep_instance<SWEEP_WAVES>(a, f, size, *(SweepLds<SWEEP_WAVES>*)lds, st);
+        if (f.p.ctl == nullptr || strip_instance(a, f.p, *(StripLds*)lds, st) == 0) {
+            __syncthreads();
+            sweep_instance<SWEEP_WAVES>(a, f, size, *(SweepLds<SWEEP_WAVES>*)lds, st);
+        }
         __syncthreads();
     }
     const int* small = list + glist[G];
@@ -484,9 +489,8 @@ __global__ __launch_bounds__(SWEEP_WG) void k_bsweep(const InstDesc* __restrict_
         bq::add_rlx(&bc->stats[threadIdx.x].v, s_stats[threadIdx.x]);
 }
 
-constexpr size_t BSWEEP_LDS = small_lds_bytes_max() > sizeof(SweepLds<SWEEP_WAVES>)
-                                  ? small_lds_bytes_max()
-                                  : sizeof(SweepLds<SWEEP_WAVES>);
+constexpr size_t BSWEEP_LDS =
+    std::max({small_lds_bytes_max(), sizeof(SweepLds<SWEEP_WAVES>), sizeof(StripLds)});
 
 // Unpack, and count the query's reached edges (out-degrees of reached
 // vertices) for throughput figures.
@@ -541,10 +545,11 @@ constexpr int GANG_MIN_N = 1 << 17;
 constexpr int CROWD_CHUNK = 512;  // rows' chunk items of a crowded batch
 
 // Work of a query in a gang, in edges of a random graph: a mesh's many short
-// sweeps cost about 16 times its edges (256 x 256 road mesh on 8 workgroups
-// 8.3 ms, random graph of 200k vertices on 16 1.37 ms).
+// steps cost about 4 times its edges (256 x 256 road mesh on 8 workgroups in
+// strips 1.44 ms, random graph of 200k vertices on 16 1.37 ms; where the ids do
+// not follow the mesh, in sweeps, 8.3 ms).
 long long gang_work(int n, long long m) {
-    return ((long long)n + m) * (m < 6ll * n ? 16 : 1);
+    return ((long long)n + m) * (m < 6ll * n ? 4 : 1);
 }
 
 // Queries that one workgroup solves in LDS. Alone on a CU a query takes about
@@ -906,7 +911,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
                 big_most = w > big_most ? w : big_most;
                 ++n_big;
                 big_n = x.n > big_n ? x.n : big_n;
-                want += (x.n + x.m / 16) / 128 + 8;
+                want += x.m < 6ll * x.n ? x.n / 8192 + 1 : (x.n + x.m / 16) / 128 + 8;
             }
         }
         want += n_small;
@@ -1036,12 +1041,17 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     }
     // bytes of the slot arena that the queries after k need with one segment
     std::vector<unsigned long long> arena_later(count + 1, 0);
+    const int gsize = sweep ? grid / gangs : 0;
+    const auto strips = [&](const sssp_instance& x) {
+        return x.m > 0 && x.m < 6ll * x.n && x.n <= (long long)gsize * (long long)STRIP_MAX_N;
+    };
     if (sweep)
         for (int k = count - 1; k > 0; --k) {
             const sssp_instance& x = h_inst[order[k]];
             arena_later[k - 1] =
                 arena_later[k] +
-                (small[k] ? 0ull : sweep_layout(nullptr, x.n, (long long)x.m, clog, 1, nullptr));
+                (small[k] ? 0ull : sweep_layout(nullptr, x.n, (long long)x.m, clog, 1, nullptr)) +
+                (!small[k] && strips(x) ? strip_layout(nullptr, x.n, nullptr) : 0ull);
         }
     size_t key_off = 0;
     for (int k = 0; k < count; ++k) {
@@ -1063,16 +1073,22 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
             // the sweep form's buffers come from the slot arena (its 96 bytes
             // per vertex, 1.5 per edge and 96 KiB per query hold one segment
             // of every query; more segments while they fit)
-            const int gsize = grid / gangs;
             int ns = gsize / 4 < 1 ? 1 : (gsize / 4 < (int)MAX_SEG ? gsize / 4 : (int)MAX_SEG);
             char* base = (char*)(b->slots + slot_off);
             const unsigned long long room = 8ull * (b->slot_cap - slot_off);
             const unsigned long long later = arena_later[k];
             while (ns > 1 && sweep_layout(base, x.n, (long long)x.m, clog, ns, nullptr) + later > room)
                 ns /= 2;
-            const unsigned long long bytes =
-                sweep_layout(base, x.n, (long long)x.m, clog, ns, &d.f);
+            unsigned long long bytes = sweep_layout(base, x.n, (long long)x.m, clog, ns, &d.f);
             if (bytes > room) return BQ_EBUSY;
+            if (strips(x) && bytes + strip_layout(nullptr, x.n, nullptr) + later <= room) {
+                bytes += strip_layout(base + bytes, x.n, &d.f.p);
+                // one workgroup per 8,192 vertices, as many as the keys need
+                const int need = (int)((x.n + STRIP_MAX_N - 1) / STRIP_MAX_N);
+                const int most = gsize < (int)STRIP_MAX_MEMBERS ? gsize : (int)STRIP_MAX_MEMBERS;
+                const int w = x.n / 8192 < most ? x.n / 8192 : most;
+                d.f.p.want = (unsigned)(w < need ? need : w);
+            }
             d.f.longp = (decltype(d.f.longp))(b->d_longp + n_units);
             slot_off += (size_t)(bytes / 8);
             nseg = (unsigned)ns;

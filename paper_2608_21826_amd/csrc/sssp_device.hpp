@@ -162,7 +162,16 @@ struct SolveArgs {
     BQ_GLOBAL const int* tw;
     BQ_GLOBAL const unsigned* orig;
     BQ_GLOBAL const unsigned* pos;
+    // Null, or the word in which an earlier launch says whether it has solved
+    // the query (neither 0 nor all ones: this form has nothing to do).
+    BQ_GLOBAL const unsigned long long* taken;
 };
+
+__device__ __forceinline__ bool solved_before(const SolveArgs& a) {
+    if (a.taken == nullptr) return false;
+    const unsigned long long x = *a.taken;
+    return x != 0ull && x != ~0ull;
+}
 
 // original vertex of key position t, and key position of original vertex v
 __device__ __forceinline__ unsigned orig_of(const SolveArgs& a, unsigned t) {
@@ -508,9 +517,10 @@ struct SweepWalk {
     }
     // a vertex of a negative cycle, or -1
     template <class Parent>
-    __device__ __forceinline__ int advance(const SolveArgs& a, const Parent& parent) {
+    __device__ __forceinline__ int advance(const SolveArgs& a, const Parent& parent,
+                                           unsigned steps) {
         const unsigned sent = (1u << (a.shift - 1u)) - 1u;
-        for (unsigned s = 0; s < SWEEP_WALK_STEPS && on; ++s) {
+        for (unsigned s = 0; s < steps && on; ++s) {
             if (hare == sent || tort == hare) {
                 on = false;
                 if (hare != sent && closed_walk_is_negative(a, hare, lam, parent)) return (int)hare;

@@ -50,6 +50,18 @@ __global__ __launch_bounds__(INIT_WG) void k_init(Queue q, long long* key, int n
 
 template <int B, int UU>
 __device__ __forceinline__ void solve_kernel_body(const SolveArgs& a) {
+    if (solved_before(a)) {
+        // take back the source that k_init has enqueued
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            bq::Ctrl* c = (bq::Ctrl*)a.q.ctrl;
+            const unsigned long long pos = c->tail.v - 1ull;
+            a.q.slots[pos & (a.q.N - 1ull)] =
+                bq::slot_word(2u * ((uint32_t)(pos >> a.q.logN) + 1u), 0u);
+            c->head.v = pos + 1ull;
+            c->count.v = 0ull;
+        }
+        return;
+    }
     __shared__ WaveLds<B> lds[WAVES_PER_WG_ONE];
     __shared__ WgShared S;
     WaveLds<B>& L = lds[threadIdx.x >> 6];
@@ -93,6 +105,7 @@ __global__ __launch_bounds__(INIT_WG) void k_sweep_init(SolveArgs a, SweepArgs f
             lr = true;
             f.stamp[v] = 0u;
         }
+    if (f.p.ctl != nullptr) strip_seed(f.p, a.n, 0, a.n, true, tid, stride);
     __shared__ int slr;
     if (threadIdx.x == 0) slr = 0;
     block_weight_range(lo, hi, wrange);  // synchronizes
@@ -114,8 +127,26 @@ __global__ __launch_bounds__(INIT_WG) void k_sweep_init(SolveArgs a, SweepArgs f
 
 __global__ __launch_bounds__(SWEEP_WG) void k_sweep(SolveArgs a, SweepArgs f) {
     __shared__ SweepLds<SWEEP_WAVES> S;
+    if (solved_before(a)) return;
     WaveStats st{};
     sweep_instance<SWEEP_WAVES>(a, f, gridDim.x, S, st);
+    sum_stats(S.stats, st);
+    if (threadIdx.x < (unsigned)bq::ST_N && S.stats[threadIdx.x])
+        bq::add_rlx(&a.q.ctrl->stats[threadIdx.x].v, S.stats[threadIdx.x]);
+}
+
+// The words of a strip solve whose query falls to the asynchronous solver if
+// the strip form refuses it.
+__global__ __launch_bounds__(INIT_WG) void k_strip_init(StripArgs p, int n) {
+    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    strip_seed(p, n, 0, n, true, tid, (long long)gridDim.x * blockDim.x);
+}
+
+__global__ __launch_bounds__(STRIP_WG) void k_strip(SolveArgs a, StripArgs p) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    StripLds& S = *(StripLds*)lds;
+    WaveStats st{};
+    strip_instance(a, p, S, st);
     sum_stats(S.stats, st);
     if (threadIdx.x < (unsigned)bq::ST_N && S.stats[threadIdx.x])
         bq::add_rlx(&a.q.ctrl->stats[threadIdx.x].v, S.stats[threadIdx.x]);

@@ -294,7 +294,7 @@ __device__ SmallResult small_instance(const SolveArgs& a, long long* dist, int* 
                 walk.start(bq::bcast32((unsigned)q[it % NL]), parent);
                 ++st.walk;
             }
-            const int hit = walk.advance(a, parent);
+            const int hit = walk.advance(a, parent, SWEEP_WALK_STEPS);
             if (hit >= 0) {
                 if (lane == 0) {
                     S.neg = 1;

@@ -50,6 +50,7 @@
 
 #include "sssp_device.hpp"
 #include "sssp_init.hpp"
+#include "sssp_strip.hpp"
 
 namespace {
 
@@ -79,6 +80,7 @@ struct SweepArgs {
     BQ_GLOBAL unsigned* longp;             // per init block: a row longer than C exists
     unsigned cap_light;
     unsigned cap_chunk;
+    StripArgs p;  // of the strip form, which is tried first; p.ctl null: it is not
 };
 
 struct SweepWave {
@@ -586,7 +588,7 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned w
                     parent);
                 ++st.walk;
             }
-            const int hit = walk.advance(a, parent);
+            const int hit = walk.advance(a, parent, SWEEP_WALK_STEPS);
             if (hit >= 0) {
                 if (lane == 0 && !flagged) bq::st_rlx(&a.q.ctrl->negcycle.v, 1ull);
                 flagged = true;
