@@ -447,9 +447,13 @@ __global__ __launch_bounds__(SOLVE_WG, SSSP_MIN_WAVES) void k_bsolve(const InstD
     flush_stats(bc->stats, st);
 }
 
+// STRIPS: some query may try the strip form. A batch without such queries runs
+// a kernel without its code, whose registers cost the sweeps 14 % (256 random
+// graphs 9.2 against 8.1 ms).
 // glist: G + 1 offsets, then the descriptor indices of gang g's queries at
 // [glist[g], glist[g + 1]) after that header, then the n_small one-workgroup
 // queries, both biggest first.
+template <bool STRIPS>
 __global__ __launch_bounds__(SWEEP_WG) void k_bsweep(const InstDesc* __restrict__ D,
                                                      const int* glist, int G, int n_small,
                                                      BatchCtl* bc, long long* results,
@@ -465,11 +469,15 @@ __global__ __launch_bounds__(SWEEP_WG) void k_bsweep(const InstDesc* __restrict_
         const int i = __builtin_amdgcn_readfirstlane(list[k]);
         const SolveArgs a = D[i].a;
         const SweepArgs f = D[i].f;
-        if (f.p.ctl == nullptr || strip_instance(a, f.p, *(StripLds*)lds, st) == 0) {
+        bool done = false;
+        if (STRIPS && f.p.ctl != nullptr) {
+            done = strip_instance(a, f.p, *(StripLds*)lds, st) != 0;
             __syncthreads();
-            sweep_instance<SWEEP_WAVES>(a, f, size, *(SweepLds<SWEEP_WAVES>*)lds, st);
         }
-        __syncthreads();
+        if (!done) {
+            sweep_instance<SWEEP_WAVES>(a, f, size, *(SweepLds<SWEEP_WAVES>*)lds, st);
+            __syncthreads();
+        }
     }
     const int* small = list + glist[G];
     for (;;) {
@@ -536,10 +544,10 @@ unsigned bkey_shift(int n) {
     return pb + 1u;
 }
 
-// Workgroups of a gang at least: 4, twice that when a query has more than
-// GANG_MIN_N vertices (64 sources of RMAT-18 with 64 and 32 gangs on 256
-// workgroups 13.4 and 11.1 ms, 64 random graphs of 500k vertices 45.7 and 41.7;
-// of RMAT-16 3.3 and 3.6).
+// Workgroups of a gang at least: 4, twice that when the queries of the gangs
+// have more than GANG_MIN_N vertices on average (64 sources of RMAT-18 with 64
+// and 32 gangs on 256 workgroups 13.4 and 11.1 ms, 64 random graphs of 500k
+// vertices 45.7 and 41.7; of RMAT-16 3.3 and 3.6).
 constexpr int GANG_MIN = 4;
 constexpr int GANG_MIN_N = 1 << 17;
 constexpr int CROWD_CHUNK = 512;  // rows' chunk items of a crowded batch
@@ -629,7 +637,7 @@ struct sssp_batch {
     std::map<unsigned long long, std::pair<bq_launch, double>> tuned;
     hipGraphExec_t exec;
     hipGraph_t graph;
-    unsigned long long graph_key[10];
+    unsigned long long graph_key[11];
     int per_cu[3];
     int sweep_per_cu;
     bool sweeping;      // the started launch is the sweep form
@@ -643,9 +651,12 @@ namespace {
 struct LaunchShape {
     int count, n_units, n_claim, n_lists, grid, B, nr, rm_tiles;
     int gangs, n_small;  // gangs > 0: the sweep form
+    int strips;          // whether a query tries the strip form first
+    static constexpr int KEY = 11;
     void key(unsigned long long* k) const {
-        const int v[10] = {count, n_units, n_claim, n_lists, grid, B, nr, rm_tiles, gangs, n_small};
-        for (int i = 0; i < 10; ++i) k[i] = (unsigned long long)v[i];
+        const int v[KEY] = {count, n_units, n_claim, n_lists, grid,   B,
+                            nr,    rm_tiles, gangs,  n_small, strips};
+        for (int i = 0; i < KEY; ++i) k[i] = (unsigned long long)v[i];
     }
 };
 
@@ -662,7 +673,8 @@ bq_status batch_launch_kernels(sssp_batch* b, const LaunchShape& z) {
     hipLaunchKernelGGL(k_binit, dim3(ug), dim3(BINIT_WG), 0, s, b->d_desc, b->d_units, z.n_units,
                        b->d_partials, b->d_bc, b->d_reached, z.count);
     if (z.gangs > 0) {
-        hipLaunchKernelGGL(k_bsweep, dim3(z.grid), dim3(SWEEP_WG), BSWEEP_LDS, s, b->d_desc,
+        const auto kernel = z.strips ? k_bsweep<true> : k_bsweep<false>;
+        hipLaunchKernelGGL(kernel, dim3(z.grid), dim3(SWEEP_WG), BSWEEP_LDS, s, b->d_desc,
                            b->d_claim, z.gangs, z.n_small, b->d_bc, b->d_results, b->d_reached);
     } else {
         switch (z.B) {
@@ -703,15 +715,14 @@ int batch_max_grid(sssp_batch* b, int B) {
     return pc * bqh::device_cus();
 }
 
-// Co-resident workgroups of k_bsweep (its barriers need a gang's workgroups
-// all resident): one per CU, its LDS fills one.
+// Co-resident workgroups of k_bsweep: one per CU, its LDS fills one.
 bq_status sweep_max_grid(sssp_batch* b, int* out) {
     if (b->sweep_per_cu == 0) {
-        BQ_HIP_TRY(hipFuncSetAttribute((const void*)k_bsweep,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)BSWEEP_LDS));
-        BQ_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b->sweep_per_cu, k_bsweep,
-                                                                SWEEP_WG, BSWEEP_LDS));
+        for (const void* k : {(const void*)k_bsweep<true>, (const void*)k_bsweep<false>})
+            BQ_HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)BSWEEP_LDS));
+        BQ_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &b->sweep_per_cu, k_bsweep<true>, SWEEP_WG, BSWEEP_LDS));
         if (b->sweep_per_cu < 1) b->sweep_per_cu = 1;
     }
     *out = b->sweep_per_cu * bqh::device_cus();
@@ -897,7 +908,8 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     // the sweep form's queries: one workgroup in LDS, or a gang
     std::vector<char> small(count, 0);
     long long big_work = 0, big_most = 0;
-    int n_small = 0, n_big = 0, big_n = 0, gangs = 0;
+    long long big_n = 0;
+    int n_small = 0, n_big = 0, gangs = 0;
     int grid = 0;
     if (sweep) {
         long long want = 0;
@@ -910,7 +922,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
                 big_work += w;
                 big_most = w > big_most ? w : big_most;
                 ++n_big;
-                big_n = x.n > big_n ? x.n : big_n;
+                big_n += x.n;
                 want += x.m < 6ll * x.n ? x.n / 8192 + 1 : (x.n + x.m / 16) / 128 + 8;
             }
         }
@@ -920,7 +932,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
         // gangs: as many as the biggest query leaves room for; of big queries
         // fewer, so that the keys in use stay in the caches
         gangs = 1;
-        const int least = big_n > GANG_MIN_N ? 2 * GANG_MIN : GANG_MIN;
+        const int least = big_n > (long long)n_big * GANG_MIN_N ? 2 * GANG_MIN : GANG_MIN;
         while (gangs * 2 <= n_big && gangs * 2 * big_most <= big_work &&
                gangs * 2 * least <= grid)
             gangs *= 2;
@@ -1054,6 +1066,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
                 (!small[k] && strips(x) ? strip_layout(nullptr, x.n, nullptr) : 0ull);
         }
     size_t key_off = 0;
+    int n_strips = 0;
     for (int k = 0; k < count; ++k) {
         const int i = order[k];
         const sssp_instance& x = h_inst[i];
@@ -1088,6 +1101,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
                 const int most = gsize < (int)STRIP_MAX_MEMBERS ? gsize : (int)STRIP_MAX_MEMBERS;
                 const int w = x.n / 8192 < most ? x.n / 8192 : most;
                 d.f.p.want = (unsigned)(w < need ? need : w);
+                ++n_strips;
             }
             d.f.longp = (decltype(d.f.longp))(b->d_longp + n_units);
             slot_off += (size_t)(bytes / 8);
@@ -1229,10 +1243,10 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     BQ_HIP_TRY(hipStreamWaitEvent(s, b->ev_in, 0));
 
     const LaunchShape shape = {count, n_units, n_claim, n_lists, grid, B,
-                               nr, rm_tiles, gangs, n_small};
+                               nr, rm_tiles, gangs, n_small, n_strips > 0 ? 1 : 0};
     BQ_HIP_TRY(hipEventRecord(b->ev0, s));
     if (L.flags & BQ_F_GRAPH) {
-        unsigned long long key[10];
+        unsigned long long key[LaunchShape::KEY];
         shape.key(key);
         if (!b->exec || memcmp(key, b->graph_key, sizeof key) != 0) {
             if (b->exec) {
