@@ -42,10 +42,10 @@ constexpr int ROUND_MAX_WG = 1024;
 constexpr int U = 8;  // slices of 64 items a wave has in flight
 
 // control words used here (bq::Ctrl): head / tail / count are the queue's;
-// aux[0] changes in the current round, aux[1] done, aux[3] CSR defect, aux[4]
-// max |w|, aux[5] rounds run, stats[ST_IMPROVE] changes over all rounds,
+// aux[0] changes in the current round, aux[1] done, aux[2] workgroups that have
+// left the current round, aux[3] CSR defect, aux[4] max |w|, aux[5] rounds run, stats[ST_IMPROVE] changes over all rounds,
 // stats[ST_SPIN] ticket waits.
-enum : int { A_CHANGES = 0, A_DONE = 1, A_BAD = 3, A_WMAX = 4, A_ROUNDS = 5 };
+enum : int { A_CHANGES = 0, A_DONE = 1, A_LEFT = 2, A_BAD = 3, A_WMAX = 4, A_ROUNDS = 5 };
 
 struct RoundArgs {
     Queue q;
@@ -70,6 +70,7 @@ __global__ void k_reset(bq::Ctrl* c) {
     c->negcycle.v = 0ull;
     c->aux[A_CHANGES].v = 0ull;
     c->aux[A_DONE].v = 0ull;
+    c->aux[A_LEFT].v = 0ull;
     c->aux[A_WMAX].v = 0ull;
     c->aux[A_ROUNDS].v = 0ull;
     for (int i = 0; i < bq::ST_N; ++i) c->stats[i].v = 0ull;
@@ -91,7 +92,13 @@ __global__ __launch_bounds__(PREP_WG) void k_prep(const int* w, int n, long long
         const unsigned long long y = __shfl_xor(wmax, o, 64);
         wmax = y > wmax ? y : wmax;
     }
-    if (bq::lane_id() == 0 && wmax)
+    // one maximum per workgroup (one per wave took 98 us on one word)
+    __shared__ unsigned long long part[PREP_WG / 64];
+    if (bq::lane_id() == 0) part[threadIdx.x >> 6] = wmax;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int i = 1; i < PREP_WG / 64; ++i) wmax = part[i] > wmax ? part[i] : wmax;
+    if (wmax > bq::ld_rlx(&ctrl->aux[A_WMAX].v))
         __hip_atomic_fetch_max(&ctrl->aux[A_WMAX].v, wmax, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -156,6 +163,36 @@ __global__ __launch_bounds__(PREP_WG) void k_edge_src(const long long* off, int 
     }
 }
 
+// End of round i (Alg. 3's test after each pass): no change -> done;
+// a change in round n-1 -> negative cycle. Before the first decision, the
+// range precondition: after n rounds |d| <= n * m * max|w|, which must stay
+// below 2^62 so that no d[u] + w overflows. By one thread of the last
+// workgroup to leave the round.
+__device__ void end_round(bq::Ctrl* c, long long round, int n, long long m) {
+    if (bq::ld_rlx(&c->error.v) != 0ull || bq::ld_rlx(&c->abort.v) != 0ull) {
+        c->aux[A_DONE].v = 1ull;
+        return;
+    }
+    if (round == 0) {
+        const double bound = ((double)n + 1.0) * ((double)m + 1.0) * (double)c->aux[A_WMAX].v;
+        if (bound >= 4611686018427387904.0) {  // 2^62
+            c->error.v = (unsigned long long)bq::ERR_RANGE;
+            c->aux[A_DONE].v = 1ull;
+            return;
+        }
+    }
+    const unsigned long long changes = bq::ld_rlx(&c->aux[A_CHANGES].v);
+    c->aux[A_CHANGES].v = 0ull;
+    c->stats[bq::ST_IMPROVE].v += changes;
+    c->aux[A_ROUNDS].v = (unsigned long long)round + 1ull;
+    if (changes == 0ull) {
+        c->aux[A_DONE].v = 1ull;
+    } else if (round == (long long)n - 1) {
+        c->negcycle.v = 1ull;
+        c->aux[A_DONE].v = 1ull;
+    }
+}
+
 // One round: every edge id is enqueued (grid-stride chunks of `items`) and
 // dequeued and relaxed once. A wave follows each chunk that it enqueues by a
 // dequeue of as many items, whichever they are: the items reserved for
@@ -164,7 +201,7 @@ __global__ __launch_bounds__(PREP_WG) void k_edge_src(const long long* off, int 
 // have a taker when the last wave is done. (Waves that first enqueued all and
 // then took what they found spent most of a round polling the count: a round
 // of 160k edges 450 us with 512 workgroups, 60 with 128.)
-__global__ __launch_bounds__(ROUND_MAX_WG) void k_round(RoundArgs a) {
+__global__ __launch_bounds__(ROUND_MAX_WG) void k_round(RoundArgs a, long long round) {
     const Queue& q = a.q;
     bq::Ctrl* c = q.ctrl;
     if (bq::bcast64(bq::ld_rlx(&c->aux[A_DONE].v)) != 0ull) return;
@@ -251,36 +288,14 @@ __global__ __launch_bounds__(ROUND_MAX_WG) void k_round(RoundArgs a) {
     }
     if (lane == 0 && improved) bq::add_rlx(&c->aux[A_CHANGES].v, improved);
     if (lane == 0 && spins) bq::add_rlx(&c->stats[bq::ST_SPIN].v, spins);
-}
-
-// End of round i (Alg. 3's test after each pass): no change -> done;
-// a change in round n-1 -> negative cycle. Before the first decision, the
-// range precondition: after n rounds |d| <= n * m * max|w|, which must stay
-// below 2^62 so that no d[u] + w overflows.
-__global__ void k_check(bq::Ctrl* c, long long round, int n, long long m) {
-    if (threadIdx.x != 0 || c->aux[A_DONE].v != 0ull) return;
-    if (c->error.v != 0ull || c->abort.v != 0ull) {
-        c->aux[A_DONE].v = 1ull;
-        return;
-    }
-    if (round == 0) {
-        const double bound = ((double)n + 1.0) * ((double)m + 1.0) * (double)c->aux[A_WMAX].v;
-        if (bound >= 4611686018427387904.0) {  // 2^62
-            c->error.v = (unsigned long long)bq::ERR_RANGE;
-            c->aux[A_DONE].v = 1ull;
-            return;
-        }
-    }
-    const unsigned long long changes = c->aux[A_CHANGES].v;
-    c->aux[A_CHANGES].v = 0ull;
-    c->stats[bq::ST_IMPROVE].v += changes;
-    c->aux[A_ROUNDS].v = (unsigned long long)round + 1ull;
-    if (changes == 0ull) {
-        c->aux[A_DONE].v = 1ull;
-    } else if (round == (long long)n - 1) {
-        c->negcycle.v = 1ull;
-        c->aux[A_DONE].v = 1ull;
-    }
+    // the last workgroup to leave decides what follows (a kernel of its own
+    // for that cost each round 6 us)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    if (bq::add_rlx(&c->aux[A_LEFT].v, 1ull) + 1ull != gridDim.x) return;
+    c->aux[A_LEFT].v = 0ull;
+    end_round(c, round, a.n, a.m);
 }
 
 // pred[v] = smallest u over edges (u, v, w) with d[u] finite and
@@ -560,9 +575,7 @@ bq_status sssp_bf_rounds(sssp_rounds_ctx* c, int32_t n, int64_t m, const int64_t
     while (round < n) {
         const long long stop = round + group < (long long)n ? round + group : (long long)n;
         for (; round < stop; ++round) {
-            hipLaunchKernelGGL(k_round, dim3(grid), dim3(L.wg_size), 0, s, a);
-            BQ_HIP_TRY(hipGetLastError());
-            hipLaunchKernelGGL(k_check, dim3(1), dim3(64), 0, s, c->ctrl, round, n, (long long)m);
+            hipLaunchKernelGGL(k_round, dim3(grid), dim3(L.wg_size), 0, s, a, round);
             BQ_HIP_TRY(hipGetLastError());
         }
         BQ_HIP_TRY(hipMemcpyAsync(c->h_ctrl, c->ctrl, sizeof(bq::Ctrl), hipMemcpyDeviceToHost, s));
