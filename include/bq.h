@@ -63,8 +63,8 @@ typedef struct sssp_rounds_ctx sssp_rounds_ctx;
 typedef struct {
     int32_t wg_size;      /* threads per workgroup, multiple of 64 (<= 1024) */
     int32_t wg_count;     /* workgroups; 0 = the call's default: Global Mixed
-                             runs one per CU, the bulk queue operations at
-                             most 4 per CU;
+                             runs one per CU (4 from ticket_batch 64 on), the
+                             bulk queue operations at most 4 per CU;
                              sssp_bf takes about one (of 16 waves) per 128
                              units of n + m/16, at most one per CU; with
                              buckets or a timeline one (of 2 waves) per 8K

@@ -522,8 +522,12 @@ bq_status bq_bench_mixed(bq_queue* q, uint64_t n_ops, const bq_launch* launch,
     // Default: one workgroup per CU. More waves only queue up on the broker
     // words and, on a small ring, on Full and Empty (4M operations, 16 items
     // per lane, 64 Ki slots: 235 us with 64 to 512 workgroups, 300 with the
-    // co-resident 2,048; 1 Mi slots: 137-170).
-    const int fill = bqh::device_cus() < max_grid ? bqh::device_cus() : max_grid;
+    // co-resident 2,048; 1 Mi slots: 137-170). From 64 items per lane the words
+    // are no bound and four per CU move the slots faster (2^26 operations, 256
+    // per lane, 1 Mi slots: 510 against 620 us; 4M operations, 64 per lane, 64
+    // Ki slots: 115 with both).
+    const int cus = bqh::device_cus() * (L.batch >= 64 ? 4 : 1);
+    const int fill = cus < max_grid ? cus : max_grid;
     int grid = L.wg_count > 0 ? L.wg_count : (fill < S2 ? max_grid : fill);
     if (grid > max_grid) grid = max_grid;
     grid -= grid % S2;
