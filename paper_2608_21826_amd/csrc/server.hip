@@ -58,6 +58,7 @@ struct Lane {
     sssp_batch* batch;
     hipStream_t stream;  // uploads, ordered before the lane's launch
     bool busy;
+    bool wide;  // the launch holds a wide request
     std::vector<int> reqs;
     std::vector<uint64_t> blocks;  // arena offsets to free at completion
     std::vector<int32_t> neg;
@@ -83,6 +84,19 @@ struct bq_server {
     uint64_t arena_size;
     bq_arena* arena;
 };
+
+namespace {
+
+// A mesh whose strips need more than a quarter of the CUs' LDS: two at a time
+// would keep each other from the workgroups they need.
+bool is_wide(const bq_server* s, const bq_request& r, long long n, long long m) {
+    const bq_launch& l = r.graph >= 0 && s->graphs[r.graph].has_launch
+                             ? s->graphs[r.graph].launch
+                             : s->launch;
+    return l.bucket_width == 0 && m < 6 * n && n > 1 << 20;
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -263,18 +277,23 @@ bq_status bq_server_run(bq_server* s, int32_t count, const bq_request* reqs,
             L.reqs.clear();
             L.blocks.clear();
             int64_t sn = 0, sm = 0;
+            bool wide_busy = false;
+            for (const Lane& o : s->lanes) wide_busy = wide_busy || (o.busy && o.wide);
+            L.wide = false;
             // size classes: a large request (one that can feed LARGE_WGS or
             // more workgroups on its own) is launched alone, so it runs with the
             // whole queue-segment set and small requests do not wait for it;
             // small requests are batched together in arrival order, passing
             // over large ones, which keep their place at the front; a lane
-            // reserved for small requests passes over every large one
+            // reserved for small requests passes over every large one. Of wide
+            // requests one runs at a time.
             std::size_t scan = 0;
             while (scan < pending.size() && (int)L.reqs.size() < s->max_batch) {
                 const int i = pending[scan];
                 const Need& nd = need[i];
                 const bool large = ((long long)nd.n + nd.m / 16) / 16384 >= LARGE_WGS;
-                if (large && (small_only || !L.reqs.empty())) {
+                const bool wide = large && is_wide(s, reqs[i], nd.n, nd.m);
+                if (large && (small_only || !L.reqs.empty() || (wide && wide_busy))) {
                     ++scan;
                     continue;
                 }
@@ -343,6 +362,7 @@ bq_status bq_server_run(bq_server* s, int32_t count, const bq_request* reqs,
                 inst.push_back(q);
                 L.reqs.push_back(i);
                 resp[i].wait_us = now_us() - r.arrival_us;
+                L.wide = wide;
                 if (large) break;
             }
             if (inst.empty()) continue;

@@ -908,7 +908,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     // the sweep form's queries: one workgroup in LDS, or a gang
     std::vector<char> small(count, 0);
     long long big_work = 0, big_most = 0;
-    long long big_n = 0;
+    long long big_n = 0, mesh_n = 0;
     int n_small = 0, n_big = 0, gangs = 0;
     int grid = 0;
     if (sweep) {
@@ -923,6 +923,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
                 big_most = w > big_most ? w : big_most;
                 ++n_big;
                 big_n += x.n;
+                if (x.m < 6ll * x.n && x.n > mesh_n) mesh_n = x.n;
                 want += x.m < 6ll * x.n ? x.n / 8192 + 1 : (x.n + x.m / 16) / 128 + 8;
             }
         }
@@ -936,6 +937,11 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
         while (gangs * 2 <= n_big && gangs * 2 * big_most <= big_work &&
                gangs * 2 * least <= grid)
             gangs *= 2;
+        // as big as the strips of the biggest mesh need, if they can be: a 2048
+        // x 2048 road mesh takes 13.4 ms in strips, 160-200 in sweeps
+        while (gangs > 1 && mesh_n <= (long long)grid * STRIP_MAX_N &&
+               mesh_n > (long long)(grid / gangs) * STRIP_MAX_N)
+            gangs /= 2;
     } else {
         // about one workgroup per 16K units of n + m/16 of each query, at
         // least one per query; more waves than the work can feed only raise

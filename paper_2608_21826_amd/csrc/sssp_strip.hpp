@@ -28,7 +28,7 @@
 // workgroup looks at a sample of rows and refuses such a graph, as it does one
 // with too few workgroups to hold the keys, and the caller's other form solves
 // it. The members are those that run when the solve starts, so no launch waits
-// for workgroups that other launches keep from running.
+// for good for workgroups that other launches keep from running.
 //
 // Memory ordering: keys in memory, ring words and rings are read and written
 // by agent-scope atomics; an entry is valid once its tag is the one of its
@@ -193,11 +193,19 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
         S.rank = (unsigned)bq::add_rlx(&ctl->joined.v, 1ull);
         S.rows = S.far = 0u;
         if (S.rank == 0) {
-            // the others get 10 us
+            // The others get 10 us; as many as hold the keys get up to 20 us each,
+            // which other launches on the chip may take to end, times 1 to 4,
+            // so that two solves that share the chip do not give up together.
             const unsigned long long t0 = bq::now_ticks();
-            unsigned long long j;
-            do j = bq::ld_rlx(&ctl->joined.v);
-            while (j < p.want && bq::now_ticks() - t0 < 1000ull);
+            const unsigned long long need =
+                ((unsigned long long)a.n + STRIP_MAX_N - 1ull) / STRIP_MAX_N;
+            const unsigned long long most = 1000ull + 2000ull * need * (1ull + (t_start & 3ull));
+            unsigned long long j, t;
+            do {
+                j = bq::ld_rlx(&ctl->joined.v);
+                t = bq::now_ticks();
+            } while (j < p.want && t - t0 < (j < need ? most : 1000ull) &&
+                     t - t_start < a.deadline);
             S.go = j < p.want ? j : p.want;
         }
     }
