@@ -529,6 +529,7 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
         if (st != BQ_OK) return st;
     }
     const Queue q = ctx_queue(c);
+    const bool small = is_small(n, (long long)m, L);
     if (L.flags & BQ_F_VALIDATE) {
         BQ_HIP_TRY(hipMemsetAsync(&c->ctrl->aux[3].v, 0, 8, s));
         hipLaunchKernelGGL(k_validate_csr,
@@ -536,12 +537,13 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
                            dim3(256), 0, s, (const long long*)d_offsets, (const int*)d_cols, n,
                            (long long)m, &c->ctrl->aux[3].v);
         BQ_HIP_TRY(hipGetLastError());
-        unsigned long long bad = 0;
-        BQ_HIP_TRY(hipMemcpyAsync(&bad, &c->ctrl->aux[3].v, 8, hipMemcpyDeviceToHost, s));
-        BQ_HIP_TRY(hipStreamSynchronize(s));
-        if (bad) return BQ_EINVAL;
+        if (!small) {
+            unsigned long long bad = 0;
+            BQ_HIP_TRY(hipMemcpyAsync(&bad, &c->ctrl->aux[3].v, 8, hipMemcpyDeviceToHost, s));
+            BQ_HIP_TRY(hipStreamSynchronize(s));
+            if (bad) return BQ_EINVAL;
+        }
     }
-    const bool small = is_small(n, (long long)m, L);
     const bool sweep = !small && sweeps(L);
     int max_grid = 0;
     if (small) {
@@ -606,6 +608,7 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
 
     BQ_HIP_TRY(hipEventRecord(c->ev0, s));
     if (small) {
+        if (L.flags & BQ_F_VALIDATE) a.taken = (decltype(a.taken))&c->ctrl->aux[3].v;
         bq_status st = launch_small(a, (int*)d_pred, c->h_ctrl, s);
         if (st != BQ_OK) return st;
     } else if (sweep) {
@@ -667,6 +670,7 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
     }
     BQ_HIP_TRY(hipStreamSynchronize(s));
     const bq::Ctrl* h = c->h_ctrl;
+    if (small && h->aux[3].v != 0ull) return BQ_EINVAL;
     float ms = 0.f, sms = 0.f;
     BQ_HIP_TRY(hipEventElapsedTime(&ms, c->ev0, c->ev1));
     if (small) sms = ms;
@@ -876,10 +880,12 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
                            dim3(256), 0, s, (const long long*)d_offsets, (const int*)d_cols, n,
                            (long long)m, &ctrl->aux[3].v);
         BQ_HIP_TRY(hipGetLastError());
-        unsigned long long bad = 0;
-        BQ_HIP_TRY(hipMemcpyAsync(&bad, &ctrl->aux[3].v, 8, hipMemcpyDeviceToHost, s));
-        BQ_HIP_TRY(hipStreamSynchronize(s));
-        if (bad) return BQ_EINVAL;
+        if (!small) {
+            unsigned long long bad = 0;
+            BQ_HIP_TRY(hipMemcpyAsync(&bad, &ctrl->aux[3].v, 8, hipMemcpyDeviceToHost, s));
+            BQ_HIP_TRY(hipStreamSynchronize(s));
+            if (bad) return BQ_EINVAL;
+        }
     }
     const unsigned shift = key_shift(n);
     SolveArgs a;
@@ -912,6 +918,7 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
     a.pos = nullptr;
     a.taken = f.p.ctl ? (decltype(a.taken))&f.p.ctl->go.v : nullptr;
     if (small) {
+        if (L.flags & BQ_F_VALIDATE) a.taken = (decltype(a.taken))&ctrl->aux[3].v;
         bq_status st = launch_small(a, (int*)d_pred, ctrl, s);
         if (st != BQ_OK) return st;
     } else if (sweep) {
@@ -952,11 +959,14 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
                            (int*)d_pred, n, src, shift);
         BQ_HIP_TRY(hipGetLastError());
     }
-    unsigned long long words[3] = {0, 0, 0};
+    unsigned long long words[4] = {0, 0, 0, 0};
     BQ_HIP_TRY(hipMemcpyAsync(&words[0], &ctrl->error.v, 8, hipMemcpyDeviceToHost, s));
     BQ_HIP_TRY(hipMemcpyAsync(&words[1], &ctrl->negcycle.v, 8, hipMemcpyDeviceToHost, s));
     BQ_HIP_TRY(hipMemcpyAsync(&words[2], &ctrl->abort.v, 8, hipMemcpyDeviceToHost, s));
+    if (small)
+        BQ_HIP_TRY(hipMemcpyAsync(&words[3], &ctrl->aux[3].v, 8, hipMemcpyDeviceToHost, s));
     BQ_HIP_TRY(hipStreamSynchronize(s));
+    if (words[3] != 0ull) return BQ_EINVAL;
     if (words[0] == bq::ERR_RANGE) return BQ_ERANGE;
     if (words[0] == bq::ERR_FULL) return BQ_EOVERFLOW;
     if (words[0] != 0ull) return BQ_ETIMEOUT;

@@ -163,7 +163,8 @@ struct SolveArgs {
     BQ_GLOBAL const unsigned* orig;
     BQ_GLOBAL const unsigned* pos;
     // Null, or the word in which an earlier launch says whether it has solved
-    // the query (neither 0 nor all ones: this form has nothing to do).
+    // the query (neither 0 nor all ones: this form has nothing to do), or, for
+    // the one-workgroup form, found defects in the CSR.
     BQ_GLOBAL const unsigned long long* taken;
 };
 

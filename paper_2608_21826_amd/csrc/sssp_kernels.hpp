@@ -156,6 +156,11 @@ __global__ __launch_bounds__(STRIP_WG) void k_strip(SolveArgs a, StripArgs p) {
 // (pinned memory): the result words and counters are stored there directly.
 __global__ __launch_bounds__(SMALL_WG) void k_small(SolveArgs a, int* pred, bq::Ctrl* h) {
     extern __shared__ __align__(16) unsigned char lds[];
+    // the CSR check of the same call comes before the solve in the stream, and
+    // the host reads its word with the result (waiting for it first cost 20 us)
+    const unsigned long long defects = a.taken != nullptr ? *a.taken : 0ull;
+    if (threadIdx.x == 0) h->aux[3].v = defects;
+    if (defects != 0ull) return;
     WaveStats st{};
     const SmallResult r = small_instance(a, (long long*)a.key, pred, nullptr, lds, st);
     SmallLds& S = *(SmallLds*)lds;

@@ -31,6 +31,14 @@ CALIB_BYTES = 1 << 30
 
 KERNEL_SOURCES = ("bq_device.hpp", "sssp_device.hpp", "sssp_kernels.hpp")
 SOURCES_OF = {  # kernel-name substring -> the sources its code comes from
+    "k_sweep": ("bq_device.hpp", "sssp_device.hpp", "sssp_init.hpp", "sssp_sweep.hpp",
+                "sssp_kernels.hpp"),
+    "k_strip": ("bq_device.hpp", "sssp_device.hpp", "sssp_strip.hpp", "sssp_kernels.hpp"),
+    "k_small": ("bq_device.hpp", "sssp_device.hpp", "sssp_small.hpp", "sssp_kernels.hpp"),
+    "k_bsweep": ("bq_device.hpp", "sssp_device.hpp", "sssp_init.hpp", "sssp_sweep.hpp",
+                 "sssp_strip.hpp", "sssp_small.hpp", "sssp_batched.hip"),
+    "k_round": ("bq_device.hpp", "sssp_rounds.hip"),
+    "k_transfer": ("bq_device.hpp", "bq_queue.hip"),
     "k_bsolve": ("bq_device.hpp", "sssp_device.hpp", "sssp_batched.hip"),
     "k_bench_mixed": ("bq_device.hpp", "bq_queue.hip"),
 }
