@@ -43,7 +43,8 @@ QUEUE_OPS = 1 << 26
 # algorithmic bytes per unit of work (per dequeued item: row offsets 16 B,
 # key RMW 8 B, slot 4 B, ticket read+write 8 B, queue bookkeeping 4 B; per
 # scanned edge: col 4 B + weight 4 B + 8 B key atomic; per enqueue: slot 4 B,
-# ticket 8 B, key already counted with the edge, 4 B bookkeeping)
+# ticket 8 B, key already counted with the edge, 4 B bookkeeping: Alg. 1's
+# queue; the sweep form's items have no tickets)
 BYTES_PER_DEQ = 40
 BYTES_PER_EDGE = 16
 BYTES_PER_PUSH = 16
@@ -759,7 +760,7 @@ def main():
                     help='fixed launch of the batched legs as JSON (no autotuning), '
                          'e.g. {"wg_count":512,"ticket_batch":1}')
     ap.add_argument("--batched-only", choices=("rmat20x64", "er256"), default=None,
-                    help="run only this batched workload (for counter passes on k_bsolve)")
+                    help="run only this batched workload (for counter passes)")
     args = ap.parse_args()
     if args.gpus != 1:
         print(f"bench.py runs on one GPU only (asked for {args.gpus}); the multi-GPU form of "
@@ -983,9 +984,11 @@ def run_main_legs(args, pkg, torch, dev, g, rec, off, col, w, ctx, q, only_timed
                        "work_ratio_k": round(rel / m_reached, 3),
                        "relax_per_s_G": round(rel / (k_ms.mean() * 1e-3) / 1e9, 3),
                        "grid": int(ss[-1]["grid"])}
-        # the solver kernel's instantiation for this launch (64 * b items
-        # per dequeue); committed counter summaries are per instantiation
-        kname = f"k_solve<{64 * max(1, int(sssp_launch.get('ticket_batch') or 1))}>"
+        # the solver kernel of this launch: the sweep form, or with buckets the
+        # queue solver's instantiation for 64 * b items per dequeue
+        kname = "k_sweep"
+        if sssp_launch.get("bucket_width"):
+            kname = f"k_solve<{64 * max(1, int(sssp_launch.get('ticket_batch') or 1))}>"
 
         def counter(path, key):
             # the committed counters were taken at the fixed RMAT-20 launch

@@ -97,6 +97,14 @@ def _counter(db: str, cname: str, last: int = 0):
     return agg
 
 
+def _pick(values: dict, kernel: str):
+    """The kernel of that name (without "void " and template arguments), else
+    the first whose name holds it."""
+    exact = [v for k, v in values.items()
+             if k.removeprefix("void ").split("<")[0] == kernel]
+    return exact[0] if exact else [v for k, v in values.items() if kernel in k][0]
+
+
 def pmc(fetch_db: str, write_db: str, kernel: str, last: int = 0) -> str:
     f = _counter(fetch_db, "FETCH_SIZE", last)
     w = _counter(write_db, "WRITE_SIZE", last)
@@ -104,8 +112,8 @@ def pmc(fetch_db: str, write_db: str, kernel: str, last: int = 0) -> str:
     cw = [v for k, v in w.items() if "k_probe_copy" in k][0][0]
     fscale = CALIB_BYTES / (cf * 1024.0)
     wscale = CALIB_BYTES / (cw * 1024.0)
-    kf = [v for k, v in f.items() if kernel in k][0]
-    kw = [v for k, v in w.items() if kernel in k][0]
+    kf = _pick(f, kernel)
+    kw = _pick(w, kernel)
     fb = sum(kf) / len(kf) * 1024.0 * fscale
     wb = sum(kw) / len(kw) * 1024.0 * wscale
     out = [
@@ -130,7 +138,7 @@ def counters(db: str, kernel: str, names, last: int = 0) -> str:
     out = [f"kernel = {kernel}"]
     means = {}
     for cname in names:
-        vals = [v for k, v in _counter(db, cname, last).items() if kernel in k][0]
+        vals = _pick(_counter(db, cname, last), kernel)
         means[cname] = sum(vals) / len(vals)
         out.append(f"{cname}_per_dispatch = {[round(x) for x in vals]}")
         out.append(f"{cname}_mean = {means[cname]:.0f}")
