@@ -68,21 +68,28 @@ typedef struct {
                              sssp_bf takes about one (of 16 waves) per 128
                              units of n + m/16, at most one per CU; with
                              buckets or a timeline one (of 2 waves) per 8K
-                             units; sssp_bf_batched about one per 16K units
+                             units; on a mesh whose ids follow it one per 8K
+                             vertices, and never fewer than one per 16K (its
+                             keys live in the workgroups' LDS);
+                             sssp_bf_batched the sum of its queries', up to
+                             one per CU; with buckets about one per 16K units
                              (per query, at least one), up to the co-resident
                              maximum */
     int32_t ticket_batch; /* b: a wave dequeues up to 64*b items per ticket;
                              0 = 1; the solvers take 1, 2 or 4 (BQ_EINVAL
                              otherwise: their LDS staging grows with b); the
-                             sweeps of sssp_bf size their batches themselves */
+                             sweeps and strips of sssp_bf size their batches
+                             themselves; a batch whose queries crowd one graph
+                             takes 4 for 0 */
     uint32_t flags;       /* BQ_F_* */
     uint64_t timeout_us;  /* watchdog for a single wait; 0 = 2 s. A solve
                              running longer than 10x this is stopped too
                              (BQ_ETIMEOUT), so no launch runs unbounded. */
     int32_t row_chunk;    /* solver: rows longer than this many edges are split
                              into queue items of this size (power of two,
-                             64..65536); 0 = 128 for sssp_bf, 1024 for
-                             the batched form */
+                             64..65536); 0 = 128; in the batched form 1024
+                             with buckets and 512 when very many queries
+                             share one graph */
     int32_t queue_scale;  /* batched solver: each query's queue holds
                              pow2(queue_scale * (n + m/row_chunk + 1)) slots,
                              1 or 2; 0 = 2 */
@@ -105,7 +112,10 @@ typedef struct {
                              (at least 1).
                              Same results, fewer relabels on large-diameter
                              graphs; the autotuner tries it. Needs one more
-                             queue per segment. Other calls ignore it. */
+                             queue per segment. A mesh whose ids follow it is
+                             solved in label order whatever k is. In
+                             sssp_bf_batched k > 0 selects the queue solver.
+                             Other calls ignore it. */
 } bq_launch;
 
 #define BQ_F_VALIDATE 1u  /* sssp_bf: check the CSR on the device first */
@@ -287,7 +297,10 @@ bq_status sssp_ctx_destroy(sssp_ctx* ctx);
  * 0 <= m <= max_m, 0 <= src < n; with BQ_F_VALIDATE the CSR itself is
  * checked (BQ_EINVAL). BQ_ERANGE when n * max|w| does not fit the packed
  * 64-bit key (bits for the distance = 62 - ceil(log2(n+1))).
- * Synchronous: returns when the outputs are final. launch may be NULL. */
+ * Synchronous: returns when the outputs are final. launch may be NULL. The
+ * outputs do not depend on the form that solves the query: one workgroup
+ * (small graphs), strips (meshes whose ids follow them), sweeps, or the
+ * asynchronous queue solver (buckets, timelines). */
 bq_status sssp_bf(sssp_ctx* ctx, int32_t n, int64_t m, const int64_t* d_offsets,
                   const int32_t* d_cols, const int32_t* d_w, int32_t src, int64_t* d_dist,
                   int32_t* d_pred, int32_t* h_neg_cycle, const bq_launch* launch,
@@ -432,15 +445,16 @@ bq_status sssp_batch_destroy(sssp_batch* b);
 /* Solve `count` independent queries (each its own CSR graph, source and
  * outputs, all device pointers; graphs may be shared between queries) in one
  * launch: every query gets the result sssp_bf would give it alone (dist,
- * pred, h_neg_cycle[i]). Queries are ordered by size; persistent workgroups
- * claim them biggest first, each query getting workgroups in proportion to
- * its edges + vertices, and workgroups whose claims are used up join
- * unfinished queries. Claims come from one list per XCD (workgroup i takes
- * from list i mod 8): a query whose share fits one XCD's workgroups is
- * listed on one list only and keeps one queue segment; a bigger query is
- * spread over all lists, and one with (n + m/16) / 16384 >= 16 gets up to 8
- * queue segments (as sssp_bf) while the workspace's slots allow, biggest
- * first. With BQ_F_GRAPH the init / solve / unpack kernels run
+ * pred, h_neg_cycle[i]). Queries are ordered by size. The workgroups (one per
+ * CU) form gangs of equal size, workgroup i of G gangs in gang i mod G; each
+ * gang solves the queries of its list one after another, biggest first, and
+ * queries that fit one CU's LDS are then taken one at a time by single
+ * workgroups. With buckets, and when the queries of one graph have more than
+ * 128 MiB of keys, persistent workgroups of four waves claim queries biggest
+ * first instead, each query getting workgroups in proportion to its edges +
+ * vertices, from one list per XCD; graphs that queries share then get a key
+ * layout ordered by degree (not with BQ_F_NOREMAP, which also keeps such a
+ * batch in gangs). With BQ_F_GRAPH the init / solve / unpack kernels run
  * as one replayed hipGraph on the batch's own stream (ordered after the
  * caller's stream). Synchronous. Errors: BQ_EINVAL (a bad query), BQ_EBUSY
  * (batch larger than the workspace), BQ_ERANGE / BQ_ETIMEOUT (first failing

@@ -285,12 +285,16 @@ bq_status sssp_ctx_create(int32_t max_n, int64_t max_m, sssp_ctx** out) {
         hipMalloc(&c->ctrl, sizeof(bq::Ctrl) * MAX_Q) != hipSuccess ||
         hipMalloc(&c->chunk_owner, sizeof(unsigned) * chunks) != hipSuccess ||
         hipMalloc(&c->wrange, sizeof(int) * 3 * INIT_MAX_BLOCKS) != hipSuccess ||
-        hipMalloc(&c->sweep_mem,
-                  sweep_layout(nullptr, max_n, max_m, MIN_CHUNK_LOG, MAX_SEG, nullptr) +
-                      strip_layout(nullptr, max_n, nullptr)) != hipSuccess ||
         hipHostMalloc(&c->h_ctrl, sizeof(bq::Ctrl), hipHostMallocDefault) != hipSuccess) {
         sssp_ctx_destroy(c);
         return BQ_ENOMEM;
+    }
+    // without room for the sweep and strip forms every query takes the queue solver
+    if (hipMalloc(&c->sweep_mem,
+                  sweep_layout(nullptr, max_n, max_m, MIN_CHUNK_LOG, MAX_SEG, nullptr) +
+                      strip_layout(nullptr, max_n, nullptr)) != hipSuccess) {
+        c->sweep_mem = nullptr;
+        (void)hipGetLastError();
     }
     BQ_HIP_TRY(hipEventCreate(&c->ev0));
     BQ_HIP_TRY(hipEventCreate(&c->ev1));
@@ -544,7 +548,7 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
             if (bad) return BQ_EINVAL;
         }
     }
-    const bool sweep = !small && sweeps(L);
+    const bool sweep = !small && sweeps(L) && c->sweep_mem;
     int max_grid = 0;
     if (small) {
         max_grid = 1;
@@ -633,7 +637,7 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
         BQ_HIP_TRY(hipGetLastError());
     } else {
         StripArgs p{};
-        if (strips(n, (long long)m, L)) {
+        if (strips(n, (long long)m, L) && c->sweep_mem) {
             strip_layout(c->sweep_mem, n, &p);
             p.want = strip_want(n, L);
             a.taken = (decltype(a.taken))&p.ctl->go.v;
