@@ -159,3 +159,37 @@ def test_batches(graph):
                 assert np.array_equal(d.cpu().numpy(), d_ref)
                 assert np.array_equal(p.cpu().numpy(), p_ref)
     batch.close()
+
+
+def test_solves_that_compete_for_the_chip():
+    # each needs more than half of the CUs for its strips: at most one at a time
+    # gets them, the others wait their time out and take the other forms
+    import threading
+    gs = [mesh(1500, 1450, 20 + i, shifted=False) for i in range(3)]
+    got, errors = [None] * 3, []
+
+    def work(i):
+        try:
+            csr, st = csr_of(gs[i]), torch.cuda.Stream()
+            ctx = pkg.SsspContext(gs[i].n, gs[i].m)
+            with torch.cuda.stream(st):
+                for launch in ({"bucket_width": 4}, {"bucket_width": 4, "wg_count": 32}):
+                    d, p, neg = ctx.solve(*csr, gs[i].src, launch=launch, stream=st)
+                    assert not neg
+                    got[i] = (d.cpu().numpy(), p.cpu().numpy())
+            ctx.close()
+        except Exception as e:  # reported by the main thread
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors
+    for i in range(3):  # alone, in strips
+        ctx = pkg.SsspContext(gs[i].n, gs[i].m)
+        d, p, _ = ctx.solve(*csr_of(gs[i]), gs[i].src)
+        ctx.close()
+        assert np.array_equal(d.cpu().numpy(), got[i][0])
+        assert np.array_equal(p.cpu().numpy(), got[i][1])
