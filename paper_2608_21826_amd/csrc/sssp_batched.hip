@@ -185,7 +185,8 @@ __global__ void k_rm_place(const RemapDesc* R, int nr, int total_tiles) {
 // classes, which are the first key positions, takes a workgroup, whose waves
 // count and then place a share of it each; any other takes a wave. (With
 // one wave for every row the reordering of RMAT-20 took 3.0 ms, most of it for
-// its longest row; now 1.2 ms.)
+// its longest row; with a workgroup for long rows 1.2 ms, and with one pass over
+// rows of at most 64 edges 0.8 ms.)
 constexpr int RM_LONG = 6;  // rows of 1,023 edges and more
 constexpr int RM_WG = 1024;
 constexpr int RM_U = 4;  // steps of 64 edges whose loads are in flight together
@@ -261,20 +262,63 @@ __global__ __launch_bounds__(RM_WG) void k_rm_rows(const RemapDesc* R, int nr) {
             rm_part<true>(d, e0, e1, next);
             __syncthreads();  // part is written again for the next row
         }
-        const int waves = (int)gridDim.x * WAVES;
-        for (long long u = (long long)blockIdx.x * WAVES + wid; u < d.n; u += waves) {
-            const long long s = d.off[u], e = d.off[u + 1];
-            if (e - s >= (1ll << (RM_CLASSES - RM_LONG)) - 1) continue;
-            long long next[RM_CLASSES];
-            for (int k = 0; k < RM_CLASSES; ++k) next[k] = 0;
-            rm_part<false>(d, s, e, next);
-            long long run = s;
+        // four rows at a time: those of at most 16 edges take 16 lanes each and one
+        // pass, the place of an edge being the number of edges before it in
+        // (class, position) order; those of at most 64 edges one pass by the wave
+        const long long waves = (long long)gridDim.x * WAVES;
+        for (long long u0 = ((long long)blockIdx.x * WAVES + wid) * 4; u0 < d.n; u0 += 4 * waves) {
+            const long long mine = u0 + (lane >> 4);
+            const long long s4 = mine < d.n ? d.off[mine] : 0, e4 = mine < d.n ? d.off[mine + 1] : 0;
+            const bool brief = e4 - s4 <= 16;
+            const long long i = s4 + (lane & 15);
+            const bool live = brief && i < e4;
+            const int v = live ? d.col[i] : 0, w = live ? d.w[i] : 0;
+            const int c = live ? (int)d.cls[v] : -1;
+            const unsigned p = live ? d.pos[v] : 0u;
+            const int sh = lane & 48;
+            int before = 0;
             for (int k = 0; k < RM_CLASSES; ++k) {
-                const long long c = next[k];
-                next[k] = run;
-                run += c;
+                const unsigned row = (unsigned)(bq::ballot(c == k) >> sh) & 0xFFFFu;
+                before += k < c ? __popc(row)
+                                : (k == c ? __popc(row & ((1u << (lane & 15)) - 1u)) : 0);
             }
-            rm_part<true>(d, s, e, next);
+            if (live) {
+                d.tcol[s4 + before] = p;
+                d.tw[s4 + before] = w;
+            }
+            unsigned long long rest = bq::ballot(!brief && (lane & 15) == 0);
+            while (rest != 0ull) {
+                const long long u = u0 + ((__ffsll((unsigned long long)rest) - 1) >> 4);
+                rest &= rest - 1ull;
+                const long long s = d.off[u], e = d.off[u + 1];
+                if (e - s >= (1ll << (RM_CLASSES - RM_LONG)) - 1) continue;
+                if (e - s <= 64) {
+                    const bool in = s + lane < e;
+                    const int x = in ? d.col[s + lane] : 0, y = in ? d.w[s + lane] : 0;
+                    const int cx = in ? (int)d.cls[x] : -1;
+                    const unsigned px = in ? d.pos[x] : 0u;
+                    int at = 0;
+                    for (int k = 0; k < RM_CLASSES; ++k) {
+                        const unsigned long long mk = bq::ballot(cx == k);
+                        at += k < cx ? __popcll(mk) : (k == cx ? bq::rank_in(mk) : 0);
+                    }
+                    if (in) {
+                        d.tcol[s + at] = px;
+                        d.tw[s + at] = y;
+                    }
+                    continue;
+                }
+                long long next[RM_CLASSES];
+                for (int k = 0; k < RM_CLASSES; ++k) next[k] = 0;
+                rm_part<false>(d, s, e, next);
+                long long run = s;
+                for (int k = 0; k < RM_CLASSES; ++k) {
+                    const long long c = next[k];
+                    next[k] = run;
+                    run += c;
+                }
+                rm_part<true>(d, s, e, next);
+            }
         }
     }
 }
@@ -1138,7 +1182,15 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
             a.pos = nullptr;
         }
         if (!sweep) a.chunk_owner = (decltype(a.chunk_owner))(b->chunks + chunk_off);
-        a.wrange = (decltype(a.wrange))(b->d_partials + 2 * n_units);
+        // a query after one on the same CSR (equal sizes follow each other) takes
+        // its weight range, and its units read no weights: 64 queries of RMAT-20
+        // read 67 MB instead of 4.3 GB (k_binit 630 -> 220 us)
+        const sssp_instance* prev = k > 0 && !small[k - 1] ? &h_inst[order[k - 1]] : nullptr;
+        const bool same_w = ku > 0 && prev && prev->offsets == x.offsets &&
+                            prev->cols == x.cols && prev->w == x.w && prev->n == x.n &&
+                            prev->m == x.m;
+        a.wrange = same_w ? b->h_desc[k - 1].a.wrange
+                          : (decltype(a.wrange))(b->d_partials + 2 * n_units);
         a.n = x.n;
         a.src = x.src;
         a.m = (long long)x.m;
@@ -1165,8 +1217,8 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
             un.pad = 0;
             un.v0 = (long long)x.n * j / ku;
             un.v1 = (long long)x.n * (j + 1) / ku;
-            un.e0 = (long long)x.m * j / ku;
-            un.e1 = (long long)x.m * (j + 1) / ku;
+            un.e0 = same_w ? 0 : (long long)x.m * j / ku;
+            un.e1 = same_w ? 0 : (long long)x.m * (j + 1) / ku;
         }
         n_units += ku;
         d.unit_end = n_units;
