@@ -30,6 +30,18 @@
 // it. The members are those that run when the solve starts, so no launch waits
 // for good for workgroups that other launches keep from running.
 //
+// A set q bit. In LDS it says that the vertex is in the strip's list (or, beyond
+// the list's length, that the step's `over` is set): a strip starts with the
+// source's alone set, and the source in the list; later only the min that
+// finds it clear and sets it puts the vertex in the list, and taking the vertex
+// clears it. In memory it says that the vertex's number is in its owner's ring:
+// the words start without it (the source's owner clears the source's before it
+// relaxes anything, and no candidate exists earlier), and only messages write
+// them until the solve is over. So neither array is ever filled from the other,
+// at the start least of all: a member that copied its keys from memory after
+// another's message got there would hold a set bit for a vertex that is in no
+// list, take the message for old news, and never relax the vertex.
+//
 // Memory ordering: keys in memory, ring words and rings are read and written
 // by agent-scope atomics; an entry is valid once its tag is the one of its
 // position. The LDS words of one step are separated from the next step's by
@@ -233,7 +245,9 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
             bq::st_rlx(&ctl->go.v, S.go);
         }
     } else if (threadIdx.x == 0) {
-        // the first workgroup runs and decides within microseconds
+        // the first workgroup runs, and decides at the latest when its wait
+        // above ends: 10 us, or until the keys' workgroups are there 20 us each
+        // times up to 4 (20 ms for 256), within the solve's deadline
         unsigned long long go;
         do go = bq::ld_rlx(&ctl->go.v);
         while (go == 0ull);
@@ -299,7 +313,10 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
                              ? ((unsigned)a.n - base < per ? (unsigned)a.n - base : per)
                              : 0u;
     BQ_GLOBAL const unsigned* ring = p.mail + ((unsigned long long)rank << rlog);
-    for (unsigned i = threadIdx.x; i < cnt; i += blockDim.x) S.key[i] = a.key[base + i];
+    // The keys of a new solve are known, so they are not read from memory: other
+    // members may be under way, and their first messages be in memory already.
+    for (unsigned i = threadIdx.x; i < cnt; i += blockDim.x)
+        S.key[i] = base + i == (unsigned)a.src ? pack_key(0, none, shift) : KEY_INF;
     if (threadIdx.x < 3) {
         S.lo[threadIdx.x] = LLONG_MAX;
         S.w[threadIdx.x] = StripStep{};
