@@ -500,31 +500,60 @@ __device__ int walk_finds_negative_cycle(const SolveArgs& a, int x0, unsigned bu
 // finding), a few steps per sweep beside the other waves' round trips, so the
 // search delays no sweep and runs from the start: a cycle whose vertices
 // improve nothing else keeps sweeps of a few items going, which a search that
-// waits for an amount of work finds only after millions of them. `parent(x)`
-// reads x's parent.
+// waits for an amount of work finds only after millions of them. In a gang (GANG)
+// the sum of a walk that has closed is shared out over sweeps too: the other
+// workgroups wait for the walker at the sweep's barrier, and no longer than the
+// launch's limit for one wait. Parents may change between two parts of a sum;
+// what is summed are edges, so a sum below zero that ends where it began is a
+// proof all the same. `parent(x)` reads x's parent.
 constexpr unsigned SWEEP_WALKERS = 4;
 constexpr unsigned SWEEP_WALK_FROM = 8;   // first sweep
 constexpr unsigned SWEEP_WALK_STEPS = 4;  // per sweep
+// Parts of up to 512 edges of a row that a walker sums per sweep, 0.8 us each: as
+// long a stay away as the barrier bears easily, and so many that the walks
+// of up to as many steps, which are the ordinary ones, are summed at once.
+constexpr unsigned SWEEP_WALK_SUMS = 128;
 
+// A gang's walker keeps the sum under way in LDS: in registers, which are all
+// needed in the sweeps, it cost those 3 % (a random graph of 200k vertices).
+struct WalkSum {
+    long long at, end;  // next edge and end of the row under way
+    long long best;     // its lightest edge to the step's vertex so far
+    long long sum;
+};
+
+template <bool GANG>
 struct SweepWalk {
     unsigned tort, hare, power, lam;
     bool on;
+    // GANG: steps of the closed walk still to be summed (0: the search goes on).
+    // tort is then the vertex whose step is next, and power its parent (`none`
+    // before it is read)
+    unsigned left;
     template <class Parent>
     __device__ __forceinline__ void start(unsigned x0, const Parent& parent) {
         tort = x0;
         hare = bq::bcast32(parent(x0));
         power = lam = 1u;
+        if (GANG) left = 0u;
         on = true;
     }
     // a vertex of a negative cycle, or -1
     template <class Parent>
     __device__ __forceinline__ int advance(const SolveArgs& a, const Parent& parent,
-                                           unsigned steps) {
-        const unsigned sent = (1u << (a.shift - 1u)) - 1u;
-        for (unsigned s = 0; s < steps && on; ++s) {
-            if (hare == sent || tort == hare) {
+                                           unsigned steps, WalkSum* w = nullptr) {
+        const unsigned none = (1u << (a.shift - 1u)) - 1u;
+        for (unsigned s = 0; s < steps && on && (!GANG || left == 0u); ++s) {
+            if (hare == none || tort == hare) {
+                if (GANG && hare != none) {
+                    left = lam;
+                    power = none;
+                    w->sum = 0;
+                    break;
+                }
                 on = false;
-                if (hare != sent && closed_walk_is_negative(a, hare, lam, parent)) return (int)hare;
+                if (!GANG && hare != none && closed_walk_is_negative(a, hare, lam, parent))
+                    return (int)hare;
                 break;
             }
             if (power == lam) {
@@ -535,6 +564,57 @@ struct SweepWalk {
             hare = bq::bcast32(parent(hare));
             ++lam;
         }
+        return GANG && on && left != 0u ? add_up(a, parent, none, *w) : -1;
+    }
+    template <class Parent>
+    __device__ int add_up(const SolveArgs& a, const Parent& parent, unsigned none, WalkSum& w) {
+        long long at = w.at, end = w.end, best = w.best, sum = w.sum;
+        for (unsigned s = 0; s < SWEEP_WALK_SUMS; ++s) {
+            if (power == none) {
+                power = bq::bcast32(parent(tort));
+                if (power == none) {
+                    on = false;  // the walk is no longer closed
+                    return -1;
+                }
+                at = a.off[orig_of(a, power)];
+                end = a.off[orig_of(a, power) + 1];
+                best = LLONG_MAX;
+            }
+            int t[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const long long i = at + 64 * r + bq::lane_id();
+                t[r] = i < end ? target_of(a, i) : -1;
+            }
+            long long low = LLONG_MAX;
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+                if (t[r] == (int)tort) {
+                    const long long x = weight_of(a, at + 64 * r + bq::lane_id());
+                    low = x < low ? x : low;
+                }
+            if (__any(low != LLONG_MAX)) {
+                for (int off = 32; off > 0; off >>= 1) {
+                    const long long o = __shfl_xor(low, off, 64);
+                    low = o < low ? o : low;
+                }
+                low = (long long)bq::bcast64((unsigned long long)low);
+                best = low < best ? low : best;
+            }
+            at += 512;
+            if (at < end) continue;
+            if (best == LLONG_MAX) {
+                on = false;
+                return -1;
+            }
+            sum += best;
+            tort = power;
+            power = none;
+            if (--left != 0u) continue;
+            on = false;
+            return tort == hare && sum < 0 ? (int)hare : -1;
+        }
+        w = WalkSum{at, end, best, sum};  // every lane the same
         return -1;
     }
 };

@@ -125,7 +125,7 @@ __device__ SmallResult small_instance(const SolveArgs& a, long long* dist, int* 
     const long long bkey = (long long)((unsigned long long)lbound << shift);
     const long long dmask = -1ll << shift;
     unsigned st_impr = 0, st_relax = 0;  // this lane's
-    SweepWalk walk{};
+    SweepWalk<false> walk{};
 
     for (unsigned it = 0;; ++it) {
         const unsigned cur = it % 3u, nxt = (it + 1u) % 3u, par = it & 1u;

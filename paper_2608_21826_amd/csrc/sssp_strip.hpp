@@ -624,7 +624,7 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
         } while (end());
     } else if (wid == STRIP_WORKERS + 1u) {
         // ---- look for the end, walk -----------------------------------------
-        SweepWalk walk{};
+        SweepWalk<false> walk{};
         unsigned long long seen[4] = {};  // the latest look at the state words
         bool was_end = false;
         do {

@@ -91,6 +91,7 @@ struct SweepWave {
     unsigned hv[64];
     unsigned out[SWEEP_OUT];
     alignas(4) unsigned char own[SWEEP_TILE];
+    WalkSum walk;
 };
 
 template <int WAVES>
@@ -418,7 +419,7 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned w
     SweepGang g;
     if (!gang_join<WAVES>(a, f, want, g, S, t_start)) return -1;
     const unsigned home = g.rank % a.nseg;
-    SweepWalk walk{};
+    SweepWalk<true> walk{};
     bool flagged = false;  // marking mode: this wave already raised negcycle
     int result = -1;
 
@@ -588,7 +589,7 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned w
                     parent);
                 ++st.walk;
             }
-            const int hit = walk.advance(a, parent, SWEEP_WALK_STEPS);
+            const int hit = walk.advance(a, parent, SWEEP_WALK_STEPS, &L.walk);
             if (hit >= 0) {
                 if (lane == 0 && !flagged) bq::st_rlx(&a.q.ctrl->negcycle.v, 1ull);
                 flagged = true;
