@@ -538,6 +538,18 @@ struct SweepWalk {
         if (GANG) left = 0u;
         on = true;
     }
+    // a move of the search, if there is one that has not ended or closed
+    template <class Parent>
+    __device__ __forceinline__ void move(const SolveArgs& a, const Parent& parent) {
+        if (!on || hare == (1u << (a.shift - 1u)) - 1u || tort == hare) return;
+        if (power == lam) {
+            tort = hare;
+            power <<= 1;
+            lam = 0;
+        }
+        hare = bq::bcast32(parent(hare));
+        ++lam;
+    }
     // a vertex of a negative cycle, or -1
     template <class Parent>
     __device__ __forceinline__ int advance(const SolveArgs& a, const Parent& parent,

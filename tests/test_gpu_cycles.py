@@ -75,3 +75,9 @@ def test_the_sum_of_a_long_cycle_is_shared_out(neg_inf):
 @pytest.mark.parametrize("neg_inf", [False, True])
 def test_long_cycles_in_sweeps(length, neg_inf):
     check(ring(length), neg_inf)
+
+
+@pytest.mark.parametrize("neg_inf", [False, True])
+def test_long_cycles_through_many_strips(neg_inf):
+    # each strip is busy for one part in 18 to 36 of the solve
+    check(ring(300_000, star=False), neg_inf, entries=("ctx", "batch"))
