@@ -165,8 +165,10 @@ typedef struct {
     uint64_t ticket_spins; /* extra polls of slot words in ticket waits */
     double ms;             /* device time of the call (HIP events) */
     double solve_ms;       /* the persistent solver kernel alone (HIP events) */
-    int32_t grid;          /* workgroups launched */
-    int32_t wg_size;
+    int32_t grid;          /* workgroups of the form that solved the query */
+    int32_t wg_size;       /* their threads; sssp_bf: 768 strips, 128 the queue
+                              solver, 1024 sweeps (and the one workgroup of
+                              small graphs) */
 } sssp_stats;
 
 /* Counters of the last sssp_bf_rounds call. */

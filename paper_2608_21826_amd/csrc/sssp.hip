@@ -610,6 +610,7 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
         BQ_HIP_TRY(hipMemsetAsync(c->trace, 0xff, sizeof(unsigned long long) * 4 * TRACE_CAP, s));
     }
 
+    bool strip = false;  // whether the strip form is tried
     BQ_HIP_TRY(hipEventRecord(c->ev0, s));
     if (small) {
         if (L.flags & BQ_F_VALIDATE) a.taken = (decltype(a.taken))&c->ctrl->aux[3].v;
@@ -630,6 +631,7 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
         BQ_HIP_TRY(hipGetLastError());
         BQ_HIP_TRY(hipEventRecord(c->evs0, s));
         if (f.p.ctl) {
+            strip = true;
             bq_status st = launch_strip(a, f.p, s);
             if (st != BQ_OK) return st;
         }
@@ -638,6 +640,7 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
     } else {
         StripArgs p{};
         if (strips(n, (long long)m, L) && c->sweep_mem) {
+            strip = true;
             strip_layout(c->sweep_mem, n, &p);
             p.want = strip_want(n, L);
             a.taken = (decltype(a.taken))&p.ctl->go.v;
@@ -690,8 +693,10 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
     c->last.ticket_spins = h->stats[bq::ST_SPIN].v;
     c->last.ms = ms;
     c->last.solve_ms = sms;
-    c->last.grid = grid;
-    c->last.wg_size = small ? SMALL_WG : (sweep ? SWEEP_WG : SOLVE_WG_ONE);
+    // the form that solved the query
+    const int members = strip ? (int)h->aux[5].v : 0;
+    c->last.grid = members ? members : grid;
+    c->last.wg_size = members ? STRIP_WG : (small ? SMALL_WG : (sweep ? SWEEP_WG : SOLVE_WG_ONE));
     const unsigned long long err = h->error.v;
     const bool neg = h->negcycle.v != 0ull;
     // a stopped asynchronous solve leaves its queue non-quiescent

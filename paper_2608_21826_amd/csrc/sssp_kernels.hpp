@@ -37,6 +37,7 @@ __global__ __launch_bounds__(INIT_WG) void k_init(Queue q, long long* key, int n
     for (unsigned sg = 0; sg < MAX_Q; ++sg)        // dequeue positions at start
         q.ctrl[sg].aux[2].v = q.ctrl[sg].head.v;
     c->aux[4].v = bq::now_ticks();                // clock at start
+    c->aux[5].v = 0ull;                           // strips that solved the query
     for (int i = 0; i < bq::ST_N; ++i) c->stats[i].v = 0ull;
     // enqueue src: the queue is quiescent, so slot (tail mod N) is free for
     // this round (ticket 2r) and count is 0
@@ -59,6 +60,7 @@ __device__ __forceinline__ void solve_kernel_body(const SolveArgs& a) {
                 bq::slot_word(2u * ((uint32_t)(pos >> a.q.logN) + 1u), 0u);
             c->head.v = pos + 1ull;
             c->count.v = 0ull;
+            c->aux[5].v = *a.taken;
         }
         return;
     }
@@ -122,12 +124,16 @@ __global__ __launch_bounds__(INIT_WG) void k_sweep_init(SolveArgs a, SweepArgs f
     q->negcycle.v = 0ull;
     q->aux[0].v = (unsigned long long)gridDim.x;  // number of partials
     q->aux[4].v = bq::now_ticks();                // clock at start
+    q->aux[5].v = 0ull;                           // strips that solved the query
     for (int i = 0; i < bq::ST_N; ++i) q->stats[i].v = 0ull;
 }
 
 __global__ __launch_bounds__(SWEEP_WG) void k_sweep(SolveArgs a, SweepArgs f) {
     __shared__ SweepLds<SWEEP_WAVES> S;
-    if (solved_before(a)) return;
+    if (solved_before(a)) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) a.q.ctrl->aux[5].v = *a.taken;
+        return;
+    }
     WaveStats st{};
     sweep_instance<SWEEP_WAVES>(a, f, gridDim.x, S, st);
     sum_stats(S.stats, st);

@@ -1,0 +1,89 @@
+"""Which form of the solver took a query, as the stats of the call say it, and
+that the answer is the oracle's whichever it was, also where solves compete for
+the workgroups that a form needs."""
+import threading
+
+import numpy as np
+import pytest
+from scipy.sparse import csr_matrix
+from scipy.sparse.csgraph import dijkstra
+
+import oracle
+import synth
+
+from test_gpu_strip import csr_of, mesh
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+pkg = pytest.importorskip("paper_2608_21826_amd")
+
+STRIP, SWEEP, QUEUE = 768, 1024, 128  # threads of a workgroup
+
+
+def check(g, launch, wg_size):
+    print(f"[forms] n={g.n} m={g.m} launch={launch}", flush=True)
+    ctx = pkg.SsspContext(g.n, g.m)
+    d, p, neg = ctx.solve(*csr_of(g), g.src, launch=launch)
+    st = ctx.stats()
+    ctx.close()
+    d_ref, p_ref, neg_ref = oracle.sssp(g, method="fifo")
+    assert neg == neg_ref is False
+    assert np.array_equal(d.cpu().numpy(), d_ref)
+    assert np.array_equal(p.cpu().numpy(), p_ref)
+    assert st["wg_size"] == wg_size
+    return st["grid"]
+
+
+@pytest.mark.parametrize("launch", [None, {"bucket_width": 4}, {"wg_count": 3}])
+def test_ids_that_follow_the_mesh_take_strips(launch):
+    # 90,000 vertices: 10 strips, 6 of which hold the keys
+    grid = check(mesh(300, 300, 30), launch, STRIP)
+    assert 6 <= grid <= 10
+
+
+@pytest.mark.parametrize("launch,wg_size", [(None, SWEEP), ({"bucket_width": 4}, QUEUE)])
+def test_ids_that_do_not_follow_it_fall_back(launch, wg_size):
+    check(mesh(150, 150, 31, perm=True), launch, wg_size)
+
+
+def test_other_graphs():
+    assert check(synth.potential_random(2000, 16000, seed=32), {"wg_count": 9}, SWEEP) == 1
+    assert check(synth.potential_random(20000, 160000, seed=33), {"wg_count": 9}, SWEEP) == 9
+    assert check(mesh(60, 60, 34), {"flags": pkg.BQ_F_TRACE, "wg_count": 9}, QUEUE) == 9
+
+
+def test_every_answer_of_competing_solves():
+    # each needs more than half of the CUs for its strips, so at most one at a
+    # time gets them
+    g = mesh(1500, 1450, 35, shifted=False)
+    # weights 1..1000 and distances that float64 holds exactly
+    d_ref = dijkstra(csr_matrix((g.w, g.cols, g.offsets), shape=(g.n, g.n)),
+                     indices=g.src).astype(np.int64)
+    p_ref = oracle.pred(g, d_ref)
+    launches = ({"bucket_width": 4}, {"bucket_width": 4, "wg_count": 32})
+    got, errors = {}, []
+
+    def work(i):
+        try:
+            csr, st = csr_of(g), torch.cuda.Stream()
+            ctx = pkg.SsspContext(g.n, g.m)
+            with torch.cuda.stream(st):
+                for j, launch in enumerate(launches):
+                    got[i, j] = ctx.solve(*csr, g.src, launch=launch, stream=st)
+                st.synchronize()
+            ctx.close()
+        except Exception as e:  # reported by the main thread
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors
+    assert len(got) == 6
+    for d, p, neg in got.values():
+        assert not neg
+        assert np.array_equal(d.cpu().numpy(), d_ref)
+        assert np.array_equal(p.cpu().numpy(), p_ref)
