@@ -484,8 +484,9 @@ bq_status sssp_batch_last_stats(const sssp_batch* b, sssp_stats* h_out);
  * compared by their median, a candidate replacing the fastest so far only
  * when at least 3 % faster. Returns the fastest launch and its time. The
  * result is kept per shape bucket (powers of two of the query count, total
- * vertices and total edges, and base->flags): a later call on the same
- * batch workspace with a batch of the same bucket returns it at once. */
+ * vertices and total edges; whether the queries crowd one graph) and base
+ * launch: a later call on the same batch workspace with a batch of the same
+ * bucket and the same base returns it at once. */
 bq_status sssp_batch_autotune(sssp_batch* b, int32_t count, const sssp_instance* h_inst,
                               const bq_launch* base, int32_t reps, bq_launch* h_best,
                               double* h_best_ms, void* stream);

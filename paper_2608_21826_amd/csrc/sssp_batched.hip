@@ -631,6 +631,12 @@ bool crowded(const sssp_instance* x, int count) {
     return false;
 }
 
+// What an autotuned launch may be used again for: powers of two of the query
+// count, of the total vertices and edges; whether the queries crowd one graph;
+// and the fields of the base launch that the result takes over.
+using TuneKey = std::tuple<unsigned, unsigned, unsigned, bool, uint32_t, uint64_t, int32_t, int32_t,
+                           int32_t, int32_t, int32_t, int32_t>;
+
 unsigned long long pow2ceil(unsigned long long x) {
     unsigned long long p = 1ull;
     while (p < x) p <<= 1;
@@ -677,8 +683,8 @@ struct sssp_batch {
     hipEvent_t ev0, ev1, ev_in, ev_done;
     std::vector<unsigned long long> layout;
     bool dirty;
-    // autotuned launches by shape bucket (sssp_batch_autotune)
-    std::map<unsigned long long, std::pair<bq_launch, double>> tuned;
+    // autotuned launches by shape bucket and base launch (sssp_batch_autotune)
+    std::map<TuneKey, std::pair<bq_launch, double>> tuned;
     hipGraphExec_t exec;
     hipGraph_t graph;
     unsigned long long graph_key[11];
@@ -1403,17 +1409,16 @@ bq_status sssp_batch_autotune(sssp_batch* b, int32_t count, const sssp_instance*
     if (reps < 1) reps = 3;
     bq_launch L = {};
     if (base) L = *base;
-    // shape bucket: powers of two of the query count and of the total
-    // vertices and edges, plus the caller's flags
     unsigned long long tn = 0, tm = 0;
     for (int i = 0; i < count; ++i) {
         tn += (unsigned long long)(h_inst[i].n > 0 ? h_inst[i].n : 0);
         tm += (unsigned long long)(h_inst[i].m > 0 ? h_inst[i].m : 0);
     }
-    const unsigned long long bucket = ((unsigned long long)bqh::log2_exact(count) << 48) |
-                                      ((unsigned long long)bqh::log2_exact(tn + 1) << 40) |
-                                      ((unsigned long long)bqh::log2_exact(tm + 1) << 32) |
-                                      (unsigned long long)L.flags;
+    const bool crowd =
+        L.bucket_width == 0 && !(L.flags & BQ_F_NOREMAP) && crowded(h_inst, count);
+    const TuneKey bucket(bqh::log2_exact(count), bqh::log2_exact(tn + 1), bqh::log2_exact(tm + 1),
+                         crowd, L.flags, L.timeout_us, L.wg_size, L.ticket_batch, L.row_chunk,
+                         L.queue_scale, L.segments, L.bucket_width);
     auto hit = b->tuned.find(bucket);
     if (hit != b->tuned.end()) {
         *h_best = hit->second.first;
