@@ -328,20 +328,21 @@ bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offsets, const 
                           const int32_t* d_w, int32_t src, int64_t* d_dist, int32_t* d_pred,
                           int32_t* h_neg_cycle, const bq_launch* launch, void* stream);
 
-/* Autotuner: time sssp_bf on this input (d_dist is used as scratch). Unless
- * base->bucket_width is set, a few runs at the default grid with and without
- * near / far buckets first pick the order of work (buckets when they are at
- * least 20 % faster); then, in that family: workgroup counts 4, 8, 16, ...
- * up to the co-resident maximum (stopping
- * once clearly past the fastest) and 3/4 and 3/2 of the fastest, then
- * ticket batches b = 2, 4 around the
- * fastest count, then row chunks 64 and 256 at the fastest shape, then
- * 1, 2 and 4 queue segments against the default, and with buckets bucket
- * widths 1, 2 and 16 against the family's 4 (steps of 1/16, 1/8, 1 and 1/4
- * of max |w|); `reps` runs per candidate
- * (0 = 5), compared by their median, a candidate replacing the fastest so
- * far only when at least 3 % faster; a winner that differs from the best
- * power-of-two count with default settings is finally run against it,
+/* Autotuner: time sssp_bf on this input (d_dist is used as scratch), trying
+ * what the form that solves it reads of the launch. One workgroup (small
+ * graphs) and strips (meshes whose ids follow them) read nothing that pays:
+ * `base` is timed and returned. Else, unless base->bucket_width is set, a few
+ * runs at the default grid with and without near / far buckets first pick the
+ * order of work (buckets when they are at least 20 % faster); then, in that
+ * family: workgroup counts 4, 8, 16, ... up to the co-resident maximum
+ * (stopping once clearly past the fastest) and 3/4 and 3/2 of the fastest,
+ * then, with buckets, ticket batches b = 2, 4 around the fastest count, then
+ * row chunks 64 and 256 at the fastest shape, then 1, 2 and 4 queue segments
+ * against the default, and with buckets bucket widths 1, 2 and 16 against the
+ * family's 4 (steps of 1/16, 1/8, 1 and 1/4 of max |w|); `reps` runs per
+ * candidate (0 = 5), compared by their median, a candidate replacing the
+ * fastest so far only when at least 3 % faster; a winner that differs from the
+ * best power-of-two count with default settings is finally run against it,
  * 2 * reps times each, alternating, and kept only if its median is lower.
  * *h_best gets the fastest launch (other fields copied from `base`, which
  * may be NULL), *h_best_ms its time. Synchronous. */
@@ -479,8 +480,9 @@ bq_status sssp_batch_finish(sssp_batch* b, int32_t* h_neg_cycle, int64_t* h_reac
 bq_status sssp_batch_last_stats(const sssp_batch* b, sssp_stats* h_out);
 
 /* Autotuner for a batch: workgroup counts 16, 32, ... up to the co-resident
- * maximum, then row chunks 256 / 4096, ticket batches 2 and 4 and
- * queue_scale 1 at the fastest shape; `reps` runs per candidate (0 = 3)
+ * maximum, then row chunks 256 / 4096 and, where the queue solver runs (see
+ * sssp_bf_batched), ticket batches 2 and 4, queue_scale 1 and BQ_F_NOREMAP at
+ * the fastest shape; `reps` runs per candidate (0 = 3)
  * compared by their median, a candidate replacing the fastest so far only
  * when at least 3 % faster. Returns the fastest launch and its time. The
  * result is kept per shape bucket (powers of two of the query count, total

@@ -220,6 +220,15 @@ bq_status sweep_occupancy(int* per_cu) {
     return BQ_OK;
 }
 
+bq_status sweep_max_grid(sssp_ctx* c, int* out) {
+    if (c->sweep_per_cu == 0) {
+        bq_status st = sweep_occupancy(&c->sweep_per_cu);
+        if (st != BQ_OK) return st;
+    }
+    *out = c->sweep_per_cu * bqh::device_cus();
+    return BQ_OK;
+}
+
 // workgroups of k_init and k_sweep_init
 unsigned init_blocks(int n, long long m) {
     const long long big = m > n ? m : n;
@@ -338,11 +347,6 @@ bq_status sssp_autotune(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offs
     bq_launch L = {};
     if (base) L = *base;
     L.flags &= ~(uint32_t)(BQ_F_TRACE | BQ_F_VALIDATE);
-    int max_grid = 0;
-    {
-        bq_status st = max_grid_for(c, 1, &max_grid);
-        if (st != BQ_OK) return st;
-    }
     double best = 1e300;
     bq_launch bestL = L;
     auto trial = [&](int wgs, int b, double* out_ms, int chunk = -1, int seg = -1) -> bq_status {
@@ -372,18 +376,31 @@ bq_status sssp_autotune(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offs
         }
         return BQ_OK;
     };
+    // The base launch. It also tells which form takes the graph: one workgroup
+    // reads nothing of the launch, and strips have no better number than the
+    // default (see strip_want).
+    {
+        double ms = 0;
+        bq_status st = trial(L.wg_count, L.bucket_width ? 1 : L.ticket_batch, &ms);
+        if (st != BQ_OK) return st;
+    }
+    if (c->last.wg_size == STRIP_WG || is_small(n, (long long)m, bqh::resolve(&L, 0))) {
+        *h_best = bestL;
+        *h_best_ms = best;
+        return BQ_OK;
+    }
+    best = 1e300;
     // Order of work: one FIFO per home (the method as the paper runs it) or
-    // near / far buckets. One series of each at the default grid picks the
+    // near / far buckets. One series of each at its form's default grid picks the
     // family the rest of the search tunes: on a large-diameter graph the
     // buckets save most relabels, on a power-law graph they only add work.
     // The bucket family is timed at a step of a quarter of max |w|.
     constexpr int BUCKET_FAMILY_WIDTH = 4;
     if (L.bucket_width == 0) {
-        const int g0 = default_grid(n, (long long)m, max_grid);
         std::vector<double> med(2);
         for (int fam = 0; fam < 2; ++fam) {
             bq_launch t = L;
-            t.wg_count = g0;
+            t.wg_count = 0;
             t.bucket_width = fam ? BUCKET_FAMILY_WIDTH : 0;
             std::vector<double> ts;
             for (int r = 0; r < (reps < 3 ? reps : 3); ++r) {
@@ -401,16 +418,24 @@ bq_status sssp_autotune(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offs
             bestL = L;
         }
     }
+    // sweeps size their batches themselves, the queue solver takes one of 1, 2, 4
+    const bool queue = !sweeps(bqh::resolve(&L, 0)) || !c->sweep_mem;
+    const int b1 = queue ? 1 : L.ticket_batch;
+    int max_grid = 0;
+    {
+        bq_status st = queue ? max_grid_for(c, 1, &max_grid) : sweep_max_grid(c, &max_grid);
+        if (st != BQ_OK) return st;
+    }
     // workgroup count: powers of two upwards until clearly past the minimum
     int best_wgs = 4;
     for (int wgs = 4; wgs <= max_grid; wgs *= 2) {
         double ms = 0;
-        bq_status st = trial(wgs, 1, &ms);
+        bq_status st = trial(wgs, b1, &ms);
         if (st != BQ_OK) return st;
         if (bestL.wg_count == wgs) best_wgs = wgs;
         if (ms > 2.0 * best && wgs >= 4 * best_wgs) break;
         if (wgs * 2 > max_grid && wgs != max_grid) {
-            st = trial(max_grid, 1, &ms);
+            st = trial(max_grid, b1, &ms);
             if (st != BQ_OK) return st;
         }
     }
@@ -419,12 +444,12 @@ bq_status sssp_autotune(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offs
     for (int wgs : {best_wgs * 3 / 4, best_wgs * 3 / 2}) {
         if (wgs < 1 || wgs > max_grid || wgs == best_wgs) continue;
         double ms = 0;
-        bq_status st = trial(wgs, 1, &ms);
+        bq_status st = trial(wgs, b1, &ms);
         if (st != BQ_OK) return st;
     }
     best_wgs = bestL.wg_count;
     // ticket batch at the best count and its neighbours
-    for (int b = 2; b <= 4; b *= 2) {
+    for (int b = 2; queue && b <= 4; b *= 2) {
         for (int f = -1; f <= 1; ++f) {
             int wgs = f < 0 ? best_wgs / 2 : (f > 0 ? best_wgs * 2 : best_wgs);
             if (wgs < 1 || wgs > max_grid) continue;
@@ -553,11 +578,8 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
     if (small) {
         max_grid = 1;
     } else if (sweep) {
-        if (c->sweep_per_cu == 0) {
-            bq_status st = sweep_occupancy(&c->sweep_per_cu);
-            if (st != BQ_OK) return st;
-        }
-        max_grid = c->sweep_per_cu * bqh::device_cus();
+        bq_status st = sweep_max_grid(c, &max_grid);
+        if (st != BQ_OK) return st;
     } else {
         bq_status st = max_grid_for(c, L.batch, &max_grid);
         if (st != BQ_OK) return st;

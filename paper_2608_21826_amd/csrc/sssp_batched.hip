@@ -1445,18 +1445,19 @@ bq_status sssp_batch_autotune(sssp_batch* b, int32_t count, const sssp_instance*
         }
         return BQ_OK;
     };
-    const int max_grid = batch_max_grid(b, 64);
-    for (int wgs = 16; wgs <= max_grid; wgs *= 2) {
-        bq_launch t = L;
-        t.wg_count = wgs;
-        t.ticket_batch = 1;
-        bq_status st = trial(t);
+    // gangs take no ticket batch, no queue and no key layout from the launch
+    const bool gangs = L.bucket_width == 0 && !crowd;
+    int max_grid = 0;
+    if (gangs) {
+        bq_status st = sweep_max_grid(b, &max_grid);
         if (st != BQ_OK) return st;
+    } else {
+        max_grid = batch_max_grid(b, 64);
+        L.ticket_batch = 1;
     }
-    {
+    for (int wgs = 16; wgs < 2 * max_grid; wgs *= 2) {
         bq_launch t = L;
-        t.wg_count = max_grid;
-        t.ticket_batch = 1;
+        t.wg_count = wgs < max_grid ? wgs : max_grid;
         bq_status st = trial(t);
         if (st != BQ_OK) return st;
     }
@@ -1467,7 +1468,7 @@ bq_status sssp_batch_autotune(sssp_batch* b, int32_t count, const sssp_instance*
         bq_status st = trial(t);
         if (st != BQ_OK) return st;
     }
-    {
+    if (!gangs) {
         const bq_launch at = bestL;
         for (int bb : {2, 4}) {
             bq_launch t = at;
