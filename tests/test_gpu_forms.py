@@ -53,6 +53,18 @@ def test_other_graphs():
     assert check(mesh(60, 60, 34), {"flags": pkg.BQ_F_TRACE, "wg_count": 9}, QUEUE) == 9
 
 
+def test_contexts_of_small_graphs_hold_a_queue_alone():
+    # 2^15 slots in each of 24 queues and half a MiB for the rest; a query that
+    # asks for a timeline still runs on it
+    n, m, count = 9984, 40960, 40
+    free = torch.cuda.mem_get_info()[0]
+    ctxs = [pkg.SsspContext(n, m) for _ in range(count)]
+    used = (free - torch.cuda.mem_get_info()[0]) / count
+    for ctx in ctxs:
+        ctx.close()
+    assert used <= 8 * 24 * 2**15 + 2**19
+
+
 def test_every_answer_of_competing_solves():
     # each needs more than half of the CUs for its strips, so at most one at a
     # time gets them
