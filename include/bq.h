@@ -77,10 +77,11 @@ typedef struct {
                              maximum */
     int32_t ticket_batch; /* b: a wave dequeues up to 64*b items per ticket;
                              0 = 1; the solvers take 1, 2 or 4 (BQ_EINVAL
-                             otherwise: their LDS staging grows with b); the
-                             sweeps and strips of sssp_bf size their batches
-                             themselves; a batch whose queries crowd one graph
-                             takes 4 for 0 */
+                             otherwise: their LDS staging grows with b); only
+                             the queue solver reads it (buckets, timelines, and
+                             a batch whose queries crowd one graph, which takes
+                             4 for 0): the other forms size their batches
+                             themselves */
     uint32_t flags;       /* BQ_F_* */
     uint64_t timeout_us;  /* watchdog for a single wait; 0 = 2 s. A solve
                              running longer than 10x this is stopped too
@@ -89,17 +90,19 @@ typedef struct {
                              into queue items of this size (power of two,
                              64..65536); 0 = 128; in the batched form 1024
                              with buckets and 512 when very many queries
-                             share one graph */
+                             share one graph. One workgroup and strips do
+                             without */
     int32_t queue_scale;  /* batched solver: each query's queue holds
                              pow2(queue_scale * (n + m/row_chunk + 1)) slots,
-                             1 or 2; 0 = 2 */
+                             1 or 2; 0 = 2. Where it runs: with buckets, or
+                             when very many queries share one graph */
     int32_t segments;     /* sssp_bf: the queue is split into this many
                              segments (1..8, one per XCD), workgroup i
                              publishing to segment i mod segments; a sweep
                              takes the items of all of them, and with buckets
                              a wave takes from the fullest other segment when
                              its own is empty; 0 = min(8, workgroups). Forced to 1 with
-                             BQ_F_TRACE. bq_bench_mixed / bq_bench_enqdeq:
+                             BQ_F_TRACE. One workgroup and strips do without. bq_bench_mixed / bq_bench_enqdeq:
                              1, 2, 4 or 8 segments of capacity/segments
                              slots (0 = 1). Other calls ignore it. */
     int32_t bucket_width; /* sssp_bf, sssp_bf_noalloc: 0 = every home segment
@@ -125,8 +128,11 @@ typedef struct {
                              operation whose reservation falls short returns
                              Full / Empty at once instead of re-checking head
                              and tail. sssp_bf / sssp_bf_batched: each dequeue
-                             takes from the count once, with no look before
-                             or after. Results are the same under both. */
+                             of the queue solver takes from the count once,
+                             with no look before or after; one workgroup,
+                             sweeps and strips, which share items out by
+                             position and ask no broker, are the same with it.
+                             Results are the same under both. */
 #define BQ_F_NEGINF 16u   /* sssp_bf, sssp_bf_batched, sssp_bf_rounds: a negative
                              cycle does not stop the solve; the vertices it
                              makes unbounded are marked instead: dist[v] =

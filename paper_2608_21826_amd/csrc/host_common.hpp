@@ -44,4 +44,9 @@ inline uint32_t log2_exact(unsigned long long x) {
     return r;
 }
 
+// Graphs with fewer edges per vertex on average than this have short rows:
+// meshes, road networks. Each use says what it does for them.
+constexpr long long SHORT_ROW_DEGREE = 6;
+inline bool short_rows(long long n, long long m) { return m < SHORT_ROW_DEGREE * n; }
+
 }  // namespace bqh

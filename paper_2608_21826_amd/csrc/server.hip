@@ -93,7 +93,7 @@ bool is_wide(const bq_server* s, const bq_request& r, long long n, long long m) 
     const bq_launch& l = r.graph >= 0 && s->graphs[r.graph].has_launch
                              ? s->graphs[r.graph].launch
                              : s->launch;
-    return l.bucket_width == 0 && m < 6 * n && n > 1 << 20;
+    return l.bucket_width == 0 && bqh::short_rows(n, m) && n > 1 << 20;
 }
 
 }  // namespace

@@ -95,8 +95,7 @@ int default_grid(int n, long long m, int max_grid) {
     return g < max_grid ? g : max_grid;
 }
 
-// Graphs with fewer than SHORT_ROW_DEGREE edges per vertex on average
-// (meshes, road networks) are solved by k_solve_short, which scans
+// Graphs of short rows are solved by k_solve_short, which scans
 // SHORT_ROW_UNROLL edges per lane per step instead of U: their batches hold
 // a few hundred edges, one step of either size, and the shorter step issues
 // about half the scan instructions, which is what a batch cycle on such
@@ -104,8 +103,7 @@ int default_grid(int n, long long m, int max_grid) {
 // 1.04-1.06 ms, 2048^2 road mesh 39.7 -> 38.8 ms; an RMAT graph of scale 20
 // (16 edges per vertex) needs twice the steps and was 12 % slower with it.
 constexpr int SHORT_ROW_UNROLL = 4;
-constexpr long long SHORT_ROW_DEGREE = 6;
-bool short_rows(long long n, long long m) { return m < SHORT_ROW_DEGREE * n; }
+using bqh::short_rows;
 
 // Co-resident workgroups of k_solve<B> and k_solve_short<B> (slot 0, 1, 2
 // for B = 64, 128, 256): the smaller of the two, so that either may be
@@ -146,14 +144,13 @@ bool sweeps(const bqh::Launch& L) {
     return L.bucket_width == 0 && (L.flags & BQ_F_TRACE) == 0;
 }
 
-// Graphs that one workgroup solves: their keys and queue fit one CU's LDS, and
+// Graphs that one workgroup solves (SMALL_MAX_N, SMALL_MAX_M): their keys and queue fit one CU's LDS, and
 // one CU scans their edges in less time than the sweeps of a gang take to
 // meet. Solve in us against the gang's sweeps: random graphs of 8 edges per
 // vertex, 1k vertices 40 / 101, 2k 68 / 129, 4k 105 / 150, 5k 135 / 152, 6k
 // 190 / 159; RMAT of scale 10 (16 k edges) 84 / 97, of scale 12 (65 k edges)
 // 324 / 116. Meshes have many short sweeps, so there the limit is the LDS: a 64
 // x 64 grid takes 174 against 856 us, a 64 x 64 road mesh 262 against 1124.
-constexpr long long SMALL_MAX_M = 40960;
 bool is_small(int n, long long m, const bqh::Launch& L) {
     return (unsigned)n <= SMALL_MAX_N && (m <= SMALL_MAX_M || short_rows(n, m)) &&
            (L.flags & BQ_F_TRACE) == 0;
@@ -193,17 +190,10 @@ bool strips(long long n, long long m, const bqh::Launch& L) {
            (L.flags & BQ_F_TRACE) == 0;
 }
 
-// Its workgroups: one per 8,192 vertices, at most the launch's count, but as
-// many as the keys need. Road meshes with a strip per 2,048 / 4,096 / 8,192
-// vertices: 256 x 256 1.53 / 1.39 / 1.44 ms, 512 x 512 3.61 / 3.00 / 2.98, 1024 x
-// 1024 7.4 / 7.4 / 6.1.
 unsigned strip_want(int n, const bqh::Launch& L) {
-    long long w = n / 8192;
-    if (L.wg_count > 0 && w > L.wg_count) w = L.wg_count;
-    const long long most = std::min<long long>(bqh::device_cus(), STRIP_MAX_MEMBERS);
-    if (w > most) w = most;
-    const long long need = ((long long)n + STRIP_MAX_N - 1) / STRIP_MAX_N;
-    return (unsigned)(w < need ? need : w);
+    long long most = std::min<long long>(bqh::device_cus(), STRIP_MAX_MEMBERS);
+    if (L.wg_count > 0 && most > L.wg_count) most = L.wg_count;
+    return strip_members(n, most);
 }
 
 bq_status launch_strip(const SolveArgs& a, const StripArgs& p, hipStream_t s) {

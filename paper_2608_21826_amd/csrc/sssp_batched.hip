@@ -601,14 +601,15 @@ constexpr int CROWD_CHUNK = 512;  // rows' chunk items of a crowded batch
 // strips 1.44 ms, random graph of 200k vertices on 16 1.37 ms; where the ids do
 // not follow the mesh, in sweeps, 8.3 ms).
 long long gang_work(int n, long long m) {
-    return ((long long)n + m) * (m < 6ll * n ? 4 : 1);
+    return ((long long)n + m) * (bqh::short_rows(n, m) ? 4 : 1);
 }
 
 // Queries that one workgroup solves in LDS. Alone on a CU a query takes about
 // 3 ns per edge, so one that would outlast the rest of the batch goes to a
 // gang.
 bool batch_small(int n, long long m, long long tot_work) {
-    return (unsigned)n <= SMALL_MAX_N && (m <= 40960 || m < 6ll * n || m <= tot_work / 64);
+    return (unsigned)n <= SMALL_MAX_N &&
+           (m <= SMALL_MAX_M || bqh::short_rows(n, m) || m <= tot_work / 64);
 }
 
 // Whether so many queries share one graph that their keys leave no room in the
@@ -622,7 +623,7 @@ bool batch_small(int n, long long m, long long tot_work) {
 bool crowded(const sssp_instance* x, int count) {
     std::map<std::tuple<const void*, const void*, const void*, int, long long>, long long> keys;
     for (int i = 0; i < count; ++i) {
-        if (x[i].m < 6ll * x[i].n) continue;
+        if (bqh::short_rows(x[i].n, x[i].m)) continue;
         long long& k = keys[std::make_tuple((const void*)x[i].offsets, (const void*)x[i].cols,
                                             (const void*)x[i].w, x[i].n, (long long)x[i].m)];
         k += 8ll * x[i].n;
@@ -973,8 +974,9 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
                 big_most = w > big_most ? w : big_most;
                 ++n_big;
                 big_n += x.n;
-                if (x.m < 6ll * x.n && x.n > mesh_n) mesh_n = x.n;
-                want += x.m < 6ll * x.n ? x.n / 8192 + 1 : (x.n + x.m / 16) / 128 + 8;
+                const bool mesh = bqh::short_rows(x.n, x.m);
+                if (mesh && x.n > mesh_n) mesh_n = x.n;
+                want += mesh ? x.n / STRIP_N + 1 : (x.n + x.m / 16) / 128 + 8;
             }
         }
         want += n_small;
@@ -1111,7 +1113,8 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     std::vector<unsigned long long> arena_later(count + 1, 0);
     const int gsize = sweep ? grid / gangs : 0;
     const auto strips = [&](const sssp_instance& x) {
-        return x.m > 0 && x.m < 6ll * x.n && x.n <= (long long)gsize * (long long)STRIP_MAX_N;
+        return x.m > 0 && bqh::short_rows(x.n, x.m) &&
+               x.n <= (long long)gsize * (long long)STRIP_MAX_N;
     };
     if (sweep)
         for (int k = count - 1; k > 0; --k) {
@@ -1152,11 +1155,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
             if (bytes > room) return BQ_EBUSY;
             if (strips(x) && bytes + strip_layout(nullptr, x.n, nullptr) + later <= room) {
                 bytes += strip_layout(base + bytes, x.n, &d.f.p);
-                // one workgroup per 8,192 vertices, as many as the keys need
-                const int need = (int)((x.n + STRIP_MAX_N - 1) / STRIP_MAX_N);
-                const int most = gsize < (int)STRIP_MAX_MEMBERS ? gsize : (int)STRIP_MAX_MEMBERS;
-                const int w = x.n / 8192 < most ? x.n / 8192 : most;
-                d.f.p.want = (unsigned)(w < need ? need : w);
+                d.f.p.want = strip_members(x.n, std::min<int>(gsize, STRIP_MAX_MEMBERS));
                 ++n_strips;
             }
             d.f.longp = (decltype(d.f.longp))(b->d_longp + n_units);

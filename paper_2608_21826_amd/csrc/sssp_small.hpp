@@ -28,7 +28,8 @@ constexpr int SMALL_WAVES = SMALL_WG / 64;
 constexpr int SMALL_U = 4;            // items per lane group in flight
 constexpr int SMALL_HUB = 16;         // steps of G edges a row may take alone
 constexpr unsigned SMALL_HUBS = 128;  // long rows left per sweep; more are scanned alone
-constexpr unsigned SMALL_MAX_N = 9984;
+constexpr unsigned SMALL_MAX_N = 9984;       // what the LDS holds
+constexpr long long SMALL_MAX_M = 40960;      // but for meshes, see is_small in sssp.hip
 
 struct SmallLds {
     long long red[SMALL_WAVES][2];

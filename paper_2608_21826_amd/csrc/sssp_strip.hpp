@@ -62,6 +62,7 @@ constexpr unsigned STRIP_WORKERS = 8;  // waves that relax; then one that stores
                                        // receives
 constexpr unsigned STRIP_MAX_N = 16384;     // vertices of a strip: 128 KiB of keys
 constexpr unsigned STRIP_MAX_MEMBERS = 256;
+constexpr unsigned STRIP_N = 8192;  // vertices of a strip by default, see strip_members
 constexpr unsigned STRIP_LIST = 4096;       // queued vertices; beyond, a step looks at all keys
 constexpr unsigned STRIP_OUT = 512;         // messages of a step; beyond, sent at once
 // From this step on (a 2048 x 2048 road mesh takes a sixth of that) the walk for a
@@ -117,6 +118,16 @@ struct StripLds {
     int wr[16][2];
     unsigned long long stats[bq::ST_N];
 };
+
+// Workgroups of a solve: one per STRIP_N vertices, at most `most`, but as many as
+// the keys need. Road meshes with a strip per 2,048 / 4,096 / 8,192 vertices:
+// 256 x 256 1.53 / 1.39 / 1.44 ms, 512 x 512 3.61 / 3.00 / 2.98, 1024 x 1024 7.4 /
+// 7.4 / 6.1.
+inline unsigned strip_members(long long n, long long most) {
+    const long long w = n / STRIP_N < most ? n / STRIP_N : most;
+    const long long need = (n + STRIP_MAX_N - 1) / STRIP_MAX_N;
+    return (unsigned)(w < need ? need : w);
+}
 
 __host__ __device__ inline unsigned long long strip_mail_words(unsigned long long n) {
     return 2ull * (n + STRIP_MAX_MEMBERS);
