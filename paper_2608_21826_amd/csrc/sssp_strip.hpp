@@ -678,7 +678,7 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
             } else if (pending && step >= SWEEP_WALK_FROM) {
                 // ---- negative cycles: a step on the parents at a time -------
                 int hit = -1;
-                if (!walk.on && now.over == 0u && now.cnt != 0u) {
+                if (!walk.on && now.cnt != 0u) {  // (the list's start holds whatever is over)
                     const unsigned q = now.cnt < STRIP_LIST ? now.cnt : STRIP_LIST;
                     walk.start(base + (unsigned)bq::bcast32((int)S.list[b0][step % q]), parent);
                     ++st.walk;

@@ -6,6 +6,8 @@ import pytest
 
 import synth
 
+from test_gpu_strip import mesh
+
 pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
@@ -41,9 +43,10 @@ def check(g, neg_inf, launch=None, entries=("ctx", "noalloc", "batch")):
     csr = (torch.from_numpy(g.offsets).to(DEV), torch.from_numpy(g.cols).to(DEV),
            torch.from_numpy(g.w).to(DEV))
     ref = np.full(g.n, MINUS_INF)
-    if g.src == g.n - 1:
-        ref[g.src] = 0  # no edge leads back to the source
-        ref[np.setdiff1d(np.arange(g.n - 1), g.cols)] = np.iinfo(np.int64).max
+    # here the cycle reaches all that any edge leads to
+    ref[np.setdiff1d(np.arange(g.n), g.cols)] = np.iinfo(np.int64).max
+    if g.src not in g.cols:
+        ref[g.src] = 0
     for entry in entries:
         d = torch.empty(g.n, dtype=torch.int64, device=DEV)
         p = torch.empty(g.n, dtype=torch.int32, device=DEV)
@@ -81,3 +84,22 @@ def test_long_cycles_in_sweeps(length, neg_inf):
 def test_long_cycles_through_many_strips(neg_inf):
     # each strip is busy for one part in 18 to 36 of the solve
     check(ring(300_000, star=False), neg_inf, entries=("ctx", "batch"))
+
+
+@pytest.mark.parametrize("launch", [None, {"bucket_width": 4}], ids=str)
+@pytest.mark.parametrize("neg_inf", [False, True])
+def test_a_short_cycle_under_a_crowded_strip(neg_inf, launch):
+    # three vertices on a cycle of weight -3 reach 60 others each, those 6,000 between
+    # them: from the third step on every step holds more vertices than the list. The
+    # edge that nothing reaches keeps the labels' lower bound far off
+    ring = np.array([100, 101, 102])
+    mid = 200 + np.arange(180).reshape(3, 60)
+    far = 1000 + np.tile(np.arange(6000).reshape(60, 100), (3, 1))
+    u = np.concatenate([ring, np.repeat(ring, 60), np.repeat(mid.ravel(), 100)])
+    v = np.concatenate([np.roll(ring, -1), mid.ravel(), far.ravel()])
+    w = np.concatenate([[-1, -1, -1], np.ones(u.size - 3, np.int64)])
+    g = mesh(120, 120, 51, shifted=False, extra=np.stack([u, v, w], 1))
+    s, t, x = synth.edges_of(g)
+    g = synth.csr_from_edges(g.n + 1, np.append(s, g.n), np.append(t, 0), np.append(x, -10**6),
+                             source=100)
+    check(g, neg_inf, launch)
