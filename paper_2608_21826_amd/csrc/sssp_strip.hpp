@@ -634,7 +634,9 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
             for (unsigned i = lane; i < items; i += 64u) {
                 const unsigned v = scan ? i : (unsigned)S.list[b0][i];
                 const long long k = S.key[v];
-                if (!scan || (k & 1ll) != 0)
+                // (in a scan the q bit tells nothing: the workers, eight times as
+                // fast, have cleared it)
+                if (!scan || k != KEY_INF)
                     bq::st_rlx(&p.par[base + v],
                                is_neg_key(k) ? none : (unsigned)((unsigned long long)k >> 1) & none);
             }

@@ -88,12 +88,13 @@ def test_long_cycles_through_many_strips(neg_inf):
 
 @pytest.mark.parametrize("launch", [None, {"bucket_width": 4}], ids=str)
 @pytest.mark.parametrize("neg_inf", [False, True])
-def test_a_short_cycle_under_a_crowded_strip(neg_inf, launch):
+@pytest.mark.parametrize("at", [100, 14_000])
+def test_a_short_cycle_under_a_crowded_strip(at, neg_inf, launch):
     # three vertices on a cycle of weight -3 reach 60 others each, those 6,000 between
     # them: from the third step on every step holds more vertices than the list. The
     # edge that nothing reaches keeps the labels' lower bound far off
-    ring = np.array([100, 101, 102])
-    mid = 200 + np.arange(180).reshape(3, 60)
+    ring = at + np.arange(3)
+    mid = at + 100 + np.arange(180).reshape(3, 60)
     far = 1000 + np.tile(np.arange(6000).reshape(60, 100), (3, 1))
     u = np.concatenate([ring, np.repeat(ring, 60), np.repeat(mid.ravel(), 100)])
     v = np.concatenate([np.roll(ring, -1), mid.ravel(), far.ravel()])
@@ -101,5 +102,5 @@ def test_a_short_cycle_under_a_crowded_strip(neg_inf, launch):
     g = mesh(120, 120, 51, shifted=False, extra=np.stack([u, v, w], 1))
     s, t, x = synth.edges_of(g)
     g = synth.csr_from_edges(g.n + 1, np.append(s, g.n), np.append(t, 0), np.append(x, -10**6),
-                             source=100)
+                             source=at)
     check(g, neg_inf, launch)
