@@ -182,12 +182,10 @@ int sweep_grid(int n, long long m, int max_grid) {
     return g < max_grid ? g : max_grid;
 }
 
-// The strip form is tried on graphs of short rows whose keys fit the CUs' LDS;
-// it looks at the ids itself.
+// Whether the strip form is tried; it looks at the ids and the longest row itself.
 bool strips(long long n, long long m, const bqh::Launch& L) {
     const long long cus = std::min<long long>(bqh::device_cus(), STRIP_MAX_MEMBERS);
-    return m > 0 && short_rows(n, m) && n <= cus * (long long)STRIP_MAX_N &&
-           (L.flags & BQ_F_TRACE) == 0;
+    return strip_shape(n, m, cus) && (L.flags & BQ_F_TRACE) == 0;
 }
 
 unsigned strip_want(int n, const bqh::Launch& L) {
@@ -644,9 +642,11 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
         if (strips(n, (long long)m, L)) {
             strip_layout(c->sweep_mem + at, n, &f.p);
             f.p.want = strip_want(n, L);
+            f.p.max_row = strip_row_sweeps(n);
             a.taken = (decltype(a.taken))&f.p.ctl->go.v;
         }
         f.longp = (decltype(f.longp))(c->wrange + 2 * INIT_MAX_BLOCKS);
+        f.p.longp = f.longp;
         hipLaunchKernelGGL(k_sweep_init, dim3(init_blocks(n, (long long)m)), dim3(INIT_WG), 0, s,
                            a, f, c->wrange);
         BQ_HIP_TRY(hipGetLastError());
@@ -664,9 +664,12 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
             strip = true;
             strip_layout(c->sweep_mem, n, &p);
             p.want = strip_want(n, L);
+            p.max_row = STRIP_ROW_QUEUE;
+            unsigned* longp = (unsigned*)(c->wrange + 2 * INIT_MAX_BLOCKS);
+            p.longp = (decltype(p.longp))longp;
             a.taken = (decltype(a.taken))&p.ctl->go.v;
             hipLaunchKernelGGL(k_strip_init, dim3(init_blocks(n, (long long)m)), dim3(INIT_WG), 0,
-                               s, p, n);
+                               s, p, (const long long*)d_offsets, n, longp);
             BQ_HIP_TRY(hipGetLastError());
         }
         hipLaunchKernelGGL(k_init, dim3(init_blocks(n, (long long)m)), dim3(INIT_WG), 0, s, q,
@@ -879,8 +882,10 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
         if (strips(n, (long long)m, L) && used + strip_layout(nullptr, n, nullptr) <= room) {
             strip_layout(at + flags + used, n, &f.p);
             f.p.want = strip_want(n, L);
+            f.p.max_row = strip_row_sweeps(n);
         }
         f.longp = (decltype(f.longp))at;
+        f.p.longp = f.longp;
     } else if (!small) {
         // the array keeps the previous call's contents: clear the control
         // blocks and the slots this call uses
@@ -963,14 +968,17 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
         BQ_HIP_TRY(hipGetLastError());
     } else {
         StripArgs p{};
-        const unsigned long long at = round256(total);
+        const unsigned long long lp = round256(total), at = lp + 4ull * INIT_MAX_BLOCKS;
         if (strips(n, (long long)m, L) &&
             at + strip_layout(nullptr, n, nullptr) <= NOALLOC_SCRATCH_BYTES) {
             strip_layout((char*)base + at, n, &p);
             p.want = strip_want(n, L);
+            p.max_row = STRIP_ROW_QUEUE;
+            unsigned* longp = (unsigned*)(base + lp);
+            p.longp = (decltype(p.longp))longp;
             a.taken = (decltype(a.taken))&p.ctl->go.v;
             hipLaunchKernelGGL(k_strip_init, dim3(init_blocks(n, (long long)m)), dim3(INIT_WG), 0,
-                               s, p, n);
+                               s, p, (const long long*)d_offsets, n, longp);
             BQ_HIP_TRY(hipGetLastError());
         }
         hipLaunchKernelGGL(k_init, dim3(init_blocks(n, (long long)m)), dim3(INIT_WG), 0, s, q,

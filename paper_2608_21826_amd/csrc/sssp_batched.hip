@@ -341,7 +341,8 @@ __global__ __launch_bounds__(BINIT_WG) void k_binit(const InstDesc* D, const Uni
         if (threadIdx.x < (unsigned)bq::ST_N) bc->stats[threadIdx.x].v = 0ull;
         for (int i = (int)threadIdx.x; i < count; i += BINIT_WG) reached[i] = 0ull;
     }
-    __shared__ int slo[BINIT_WG / 64], shi[BINIT_WG / 64], slong;
+    __shared__ int slo[BINIT_WG / 64], shi[BINIT_WG / 64];
+    __shared__ unsigned slong;
     for (int u = blockIdx.x; u < n_units; u += gridDim.x) {
         const Unit un = units[u];
         const InstDesc& d = D[un.inst];
@@ -352,15 +353,14 @@ __global__ __launch_bounds__(BINIT_WG) void k_binit(const InstDesc* D, const Uni
             a.key[v] = (v == spos) ? srckey : KEY_INF;
         const bool sweep = d.f.ctl != nullptr;
         const long long C = 1ll << a.chunk_log;
-        if (threadIdx.x == 0) slong = 0;
-        bool lr = false;
+        if (threadIdx.x == 0) slong = 0u;
+        long long lr = 0;
         if (sweep)
             for (long long v = un.v0 + threadIdx.x; v < un.v1; v += blockDim.x) {
                 const long long r = (long long)orig_of(a, (unsigned)v);
-                if (a.off[r + 1] - a.off[r] > C) {
-                    lr = true;
-                    d.f.stamp[v] = 0u;
-                }
+                const long long deg = a.off[r + 1] - a.off[r];
+                lr = deg > lr ? deg : lr;
+                if (deg > C) d.f.stamp[v] = 0u;
             }
         int lo = INT_MAX, hi = INT_MIN;
         for (long long e = un.e0 + threadIdx.x; e < un.e1; e += blockDim.x) {
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(BINIT_WG) void k_binit(const InstDesc* D, const Uni
             shi[threadIdx.x >> 6] = hi;
         }
         __syncthreads();
-        if (lr) slong = 1;
+        note_row(&slong, lr);
         if (sweep && u == d.unit_begin)
             sweep_seed(a, d.f, threadIdx.x, BINIT_WG);
         if (sweep && d.f.p.ctl != nullptr)
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(BINIT_WG) void k_binit(const InstDesc* D, const Uni
             }
             partials[2 * u] = lo;
             partials[2 * u + 1] = hi;
-            if (sweep) d.f.longp[u - d.unit_begin] = (unsigned)slong;
+            if (sweep) d.f.longp[u - d.unit_begin] = slong;
             if (u == d.unit_begin) {
                 bq::Ctrl* c = a.q.ctrl;
                 c->abort.v = 0ull;
@@ -692,7 +692,7 @@ struct sssp_batch {
     int per_cu[3];
     int sweep_per_cu;
     bool sweeping;      // the started launch is the sweep form
-    unsigned* d_longp;  // per unit: a row longer than C exists
+    unsigned* d_longp;  // per unit: its longest row (note_row)
     sssp_stats last;
 };
 
@@ -1113,8 +1113,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
     std::vector<unsigned long long> arena_later(count + 1, 0);
     const int gsize = sweep ? grid / gangs : 0;
     const auto strips = [&](const sssp_instance& x) {
-        return x.m > 0 && bqh::short_rows(x.n, x.m) &&
-               x.n <= (long long)gsize * (long long)STRIP_MAX_N;
+        return strip_shape(x.n, x.m, gsize);
     };
     if (sweep)
         for (int k = count - 1; k > 0; --k) {
@@ -1156,9 +1155,11 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
             if (strips(x) && bytes + strip_layout(nullptr, x.n, nullptr) + later <= room) {
                 bytes += strip_layout(base + bytes, x.n, &d.f.p);
                 d.f.p.want = strip_members(x.n, std::min<int>(gsize, STRIP_MAX_MEMBERS));
+                d.f.p.max_row = strip_row_sweeps(x.n);
                 ++n_strips;
             }
             d.f.longp = (decltype(d.f.longp))(b->d_longp + n_units);
+            d.f.p.longp = d.f.longp;
             slot_off += (size_t)(bytes / 8);
             nseg = (unsigned)ns;
         }

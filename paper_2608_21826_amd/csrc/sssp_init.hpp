@@ -10,6 +10,13 @@ namespace {
 constexpr int INIT_WG = 256;
 constexpr int INIT_MAX_BLOCKS = 1024;
 
+// The longest row of a block, in LDS, 0 where none is longer than the smallest
+// row chunk: a thread's share.
+constexpr long long NOTED_ROW = 64;
+__device__ __forceinline__ void note_row(unsigned* longest, long long deg) {
+    if (deg > NOTED_ROW) atomicMax(longest, deg < (long long)UINT_MAX ? (unsigned)deg : UINT_MAX);
+}
+
 // Keys of a new solve, in 16-byte stores after a scalar head up to 16-byte
 // alignment and with a scalar tail (the caller's array needs only its
 // element alignment).

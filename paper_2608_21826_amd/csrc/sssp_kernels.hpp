@@ -101,19 +101,19 @@ __global__ __launch_bounds__(INIT_WG) void k_sweep_init(SolveArgs a, SweepArgs f
     init_keys((long long*)a.key, a.n, a.src, a.shift, tid, stride);
     int lo, hi;
     weight_range((const int*)a.w, a.m, tid, stride, lo, hi);
-    bool lr = false;
-    for (long long v = tid; v < a.n; v += stride)
-        if (a.off[v + 1] - a.off[v] > C) {
-            lr = true;
-            f.stamp[v] = 0u;
-        }
+    long long lr = 0;
+    for (long long v = tid; v < a.n; v += stride) {
+        const long long deg = a.off[v + 1] - a.off[v];
+        lr = deg > lr ? deg : lr;
+        if (deg > C) f.stamp[v] = 0u;
+    }
     if (f.p.ctl != nullptr) strip_seed(f.p, a.n, 0, a.n, true, tid, stride);
-    __shared__ int slr;
-    if (threadIdx.x == 0) slr = 0;
+    __shared__ unsigned slr;
+    if (threadIdx.x == 0) slr = 0u;
     block_weight_range(lo, hi, wrange);  // synchronizes
-    if (lr) slr = 1;
+    note_row(&slr, lr);
     __syncthreads();
-    if (threadIdx.x == 0) f.longp[blockIdx.x] = (unsigned)slr;
+    if (threadIdx.x == 0) f.longp[blockIdx.x] = slr;
     if (blockIdx.x != 0) return;
     // block 0: control words and the source's items
     sweep_seed(a, f, threadIdx.x, INIT_WG);
@@ -143,9 +143,20 @@ __global__ __launch_bounds__(SWEEP_WG) void k_sweep(SolveArgs a, SweepArgs f) {
 
 // The words of a strip solve whose query falls to the asynchronous solver if
 // the strip form refuses it.
-__global__ __launch_bounds__(INIT_WG) void k_strip_init(StripArgs p, int n) {
+__global__ __launch_bounds__(INIT_WG) void k_strip_init(StripArgs p, const long long* off, int n,
+                                                        unsigned* longp) {
     const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    strip_seed(p, n, 0, n, true, tid, (long long)gridDim.x * blockDim.x);
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    strip_seed(p, n, 0, n, true, tid, stride);
+    long long lr = 0;
+    for (long long v = tid; v < n; v += stride)
+        lr = off[v + 1] - off[v] > lr ? off[v + 1] - off[v] : lr;
+    __shared__ unsigned slr;
+    if (threadIdx.x == 0) slr = 0u;
+    __syncthreads();
+    note_row(&slr, lr);
+    __syncthreads();
+    if (threadIdx.x == 0) longp[blockIdx.x] = slr;
 }
 
 __global__ __launch_bounds__(STRIP_WG) void k_strip(SolveArgs a, StripArgs p) {

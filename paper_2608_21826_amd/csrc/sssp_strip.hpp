@@ -26,8 +26,8 @@
 //
 // Ids that do not follow the mesh make every edge a message; the first
 // workgroup looks at a sample of rows and refuses such a graph, as it does one
-// with too few workgroups to hold the keys, and the caller's other form solves
-// it. The members are those that run when the solve starts, so no launch waits
+// with a row too long for one wave or with too few workgroups to hold the keys,
+// and the caller's other form solves it. The members are those that run when the solve starts, so no launch waits
 // for good for workgroups that other launches keep from running.
 //
 // A set q bit. In LDS it says that the vertex is in the strip's list (or, beyond
@@ -50,6 +50,7 @@
 #include <hip/hip_runtime.h>
 #include <limits.h>
 
+#include "host_common.hpp"
 #include "sssp_device.hpp"
 
 namespace {
@@ -93,6 +94,8 @@ struct StripArgs {
     BQ_GLOBAL StripCtl* ctl;   // null: no strip form
     BQ_GLOBAL unsigned* mail;  // [strip_mail_words(n)] the members' rings, one after another
     BQ_GLOBAL unsigned* par;   // [n] parents of vertices when last relaxed, for the walks
+    BQ_GLOBAL const unsigned* longp;  // per weight-range partial: longest row (note_row)
+    unsigned max_row;          // longest row that it takes
     unsigned want;             // members at most
 };
 
@@ -114,7 +117,7 @@ struct StripLds {
     unsigned stop;       // number of the last step, plus one
     unsigned long long go;
     unsigned rank;
-    unsigned rows, far;  // the first workgroup's sample
+    unsigned rows, far, lrow;  // the first workgroup's sample, and the longest row
     int wr[16][2];
     unsigned long long stats[bq::ST_N];
 };
@@ -149,6 +152,25 @@ inline unsigned long long strip_layout(char* base, int n, StripArgs* p) {
     if (p) *p = t;
     return at;
 }
+
+// Whether a graph may be one for strips on `workgroups` of them: short rows, keys
+// that fit their LDS, and edges for more than one vertex in 16 (1M vertices with
+// 10,000 edges 71 us without the strips' words to clear, 86 with).
+inline bool strip_shape(long long n, long long m, long long workgroups) {
+    return bqh::short_rows(n, m) && 16 * m >= n && n <= workgroups * (long long)STRIP_MAX_N;
+}
+
+// Longest row that strips take, where the sweeps solve the query otherwise, and
+// where the queue solver does. One wave relaxes a row, and beyond its strip each
+// edge is a message (25 ns an edge); and a row that reaches much of the graph
+// leaves no long chain, which is what strips are for. Road meshes of n vertices
+// with a row of L edges spread over them, ms in strips / in sweeps / by the queue
+// solver: n = 90,000, L = 500 0.44 / 0.46 / 3.2, 2,000 0.44 / 0.30 / 3.2, 22,000
+// 0.77 / 0.21 / 3.0, 90,000 2.3 / 0.21 / 3.2; 1M, 2,000 0.65 / 1.02 / 2.1, 8,000 0.69
+// / 0.67 / 1.9, 64,000 1.86 / 0.50 / 1.9, 128,000 3.4 / 0.49 / 1.9; 4M, 8,000 1.34 /
+// 2.1 / 5.2, 32,000 1.81 / 1.57 / 4.7, 128,000 4.1 / 1.3 / 4.4.
+inline unsigned strip_row_sweeps(long long n) { return (unsigned)(n / 128); }
+constexpr unsigned STRIP_ROW_QUEUE = 65536;
 
 // Words of a new solve, by threads tid of `threads`: rings and parents of
 // vertices [v0, v1); with `first` the control words and the rings' rest.
@@ -220,7 +242,7 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
     // ---- members ------------------------------------------------------------
     if (threadIdx.x == 0) {
         S.rank = (unsigned)bq::add_rlx(&ctl->joined.v, 1ull);
-        S.rows = S.far = 0u;
+        S.rows = S.far = S.lrow = 0u;
         if (S.rank == 0) {
             // The others get 10 us; as many as hold the keys get up to 20 us each,
             // which other launches on the chip may take to end, times 1 to 4,
@@ -253,11 +275,17 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
             ++rows;
             far += (d < 0 ? -d : d) > (long long)per0;
         }
+        unsigned lrow = 0;
+        const int parts = (int)bq::ld_rlx(&a.q.ctrl->aux[0].v);
+        for (int i = (int)threadIdx.x; i < parts; i += (int)blockDim.x)
+            lrow = p.longp[i] > lrow ? p.longp[i] : lrow;
         atomicAdd(&S.rows, rows);
         atomicAdd(&S.far, far);
+        atomicMax(&S.lrow, lrow);
         __syncthreads();
         if (threadIdx.x == 0) {
-            const bool ok = per0 <= STRIP_MAX_N && S.far * 16u <= S.rows;
+            const bool ok =
+                per0 <= STRIP_MAX_N && S.far * 16u <= S.rows && S.lrow <= p.max_row;
             S.go = ok ? (unsigned long long)m0 : STRIP_REFUSED;
             bq::st_rlx(&ctl->go.v, S.go);
         }
@@ -468,7 +496,7 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
             S.out_v[b1][at] = c;
             S.out_c[b1][at] = cand;
         }
-        if (__any(live && at >= STRIP_OUT)) send(live && at >= STRIP_OUT, c, cand);
+        if (__builtin_expect(__any(live && at >= STRIP_OUT), 0)) send(live && at >= STRIP_OUT, c, cand);
     };
     // candidate into key li of the strip
     const auto lower = [&](bool live, unsigned li, long long cand, long long cd) {
@@ -542,7 +570,8 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
                 S.out_c[b1][at_c + rank_c[j]] = cand[j];
             }
         }
-        if (at_c + ncross > STRIP_OUT)
+        // rare, and kept out of the loop's way (2048 x 2048 road mesh 13.4 -> 13.0 ms)
+        if (__builtin_expect(at_c + ncross > STRIP_OUT, 0))
 #pragma unroll
             for (int j = 0; j < K; ++j)
                 send(cross[j] && at_c + rank_c[j] >= STRIP_OUT, (unsigned)c[j], cand[j]);

@@ -77,7 +77,7 @@ struct SweepArgs {
     BQ_GLOBAL unsigned* light;             // [2][nseg][cap_light]
     BQ_GLOBAL unsigned long long* chunk;   // [2][nseg][cap_chunk]
     BQ_GLOBAL unsigned* stamp;             // [n] used for chunked rows only
-    BQ_GLOBAL unsigned* longp;             // per init block: a row longer than C exists
+    BQ_GLOBAL unsigned* longp;             // per init block: its longest row (note_row)
     unsigned cap_light;
     unsigned cap_chunk;
     StripArgs p;  // of the strip form, which is tried first; p.ctl null: it is not
@@ -381,7 +381,7 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned w
             const int x = a.wrange[2 * i], y = a.wrange[2 * i + 1];
             lo = x < lo ? x : lo;
             hi = y > hi ? y : hi;
-            lr |= f.longp[i];
+            lr |= f.longp[i] > (unsigned long long)C ? 1u : 0u;
         }
         for (int off = 32; off > 0; off >>= 1) {
             const int x = __shfl_xor(lo, off, 64), y = __shfl_xor(hi, off, 64);

@@ -47,9 +47,30 @@ def test_ids_that_do_not_follow_it_fall_back(launch, wg_size):
     check(mesh(150, 150, 31, perm=True), launch, wg_size)
 
 
+@pytest.mark.parametrize("length,launch,wg_size", [
+    (699, None, STRIP), (700, None, SWEEP), (30_000, {"bucket_width": 4}, STRIP),
+    (30_000, {"bucket_width": 4, "row_chunk": 65536}, STRIP),
+    (65, {"row_chunk": 64}, STRIP), (700, {"row_chunk": 4096}, SWEEP)], ids=str)
+def test_one_long_row_in_a_mesh(length, launch, wg_size):
+    # 90,000 vertices (and 4 edges of the mesh): sweeps take rows of more than 703
+    to = np.random.default_rng(36).permutation(90_000)[:length]
+    extra = np.stack([np.full(length, 777), to, np.full(length, 500)], 1)
+    check(mesh(300, 300, 37, shifted=False, extra=extra), launch, wg_size)
+
+
+@pytest.mark.parametrize("n,launch,wg_size", [
+    (30_000, None, SWEEP), (300_000, None, SWEEP), (60_000, {"bucket_width": 4}, STRIP),
+    (300_000, {"bucket_width": 4}, QUEUE)], ids=str)
+def test_stars(n, launch, wg_size):
+    w = np.random.default_rng(n).integers(1, 1000, n - 1)
+    check(synth.csr_from_edges(n, np.zeros(n - 1, np.int64), np.arange(1, n), w, source=0),
+          launch, wg_size)
+
+
 def test_other_graphs():
     assert check(synth.potential_random(2000, 16000, seed=32), {"wg_count": 9}, SWEEP) == 1
     assert check(synth.potential_random(20000, 160000, seed=33), {"wg_count": 9}, SWEEP) == 9
+    check(synth.random_small(100_000, 6_000, 1, 9, 38), None, SWEEP)
     assert check(mesh(60, 60, 34), {"flags": pkg.BQ_F_TRACE, "wg_count": 9}, QUEUE) == 9
 
 
