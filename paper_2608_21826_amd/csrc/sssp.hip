@@ -643,6 +643,7 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
             strip_layout(c->sweep_mem + at, n, &f.p);
             f.p.want = strip_want(n, L);
             f.p.max_row = strip_row_sweeps(n);
+            f.p.max_cross = STRIP_CROSS_SWEEPS;
             a.taken = (decltype(a.taken))&f.p.ctl->go.v;
         }
         f.longp = (decltype(f.longp))(c->wrange + 2 * INIT_MAX_BLOCKS);
@@ -665,6 +666,7 @@ bq_status sssp_bf(sssp_ctx* c, int32_t n, int64_t m, const int64_t* d_offsets,
             strip_layout(c->sweep_mem, n, &p);
             p.want = strip_want(n, L);
             p.max_row = STRIP_ROW_QUEUE;
+            p.max_cross = strip_cross_queue(n);
             unsigned* longp = (unsigned*)(c->wrange + 2 * INIT_MAX_BLOCKS);
             p.longp = (decltype(p.longp))longp;
             a.taken = (decltype(a.taken))&p.ctl->go.v;
@@ -883,6 +885,7 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
             strip_layout(at + flags + used, n, &f.p);
             f.p.want = strip_want(n, L);
             f.p.max_row = strip_row_sweeps(n);
+            f.p.max_cross = STRIP_CROSS_SWEEPS;
         }
         f.longp = (decltype(f.longp))at;
         f.p.longp = f.longp;
@@ -974,6 +977,7 @@ extern "C" bq_status sssp_bf_noalloc(int32_t n, int64_t m, const int64_t* d_offs
             strip_layout((char*)base + at, n, &p);
             p.want = strip_want(n, L);
             p.max_row = STRIP_ROW_QUEUE;
+            p.max_cross = strip_cross_queue(n);
             unsigned* longp = (unsigned*)(base + lp);
             p.longp = (decltype(p.longp))longp;
             a.taken = (decltype(a.taken))&p.ctl->go.v;

@@ -1156,6 +1156,7 @@ bq_status sssp_bf_batched_start(sssp_batch* b, int32_t count, const sssp_instanc
                 bytes += strip_layout(base + bytes, x.n, &d.f.p);
                 d.f.p.want = strip_members(x.n, std::min<int>(gsize, STRIP_MAX_MEMBERS));
                 d.f.p.max_row = strip_row_sweeps(x.n);
+                d.f.p.max_cross = STRIP_CROSS_SWEEPS;
                 ++n_strips;
             }
             d.f.longp = (decltype(d.f.longp))(b->d_longp + n_units);

@@ -26,8 +26,9 @@
 //
 // Ids that do not follow the mesh make every edge a message; the first
 // workgroup looks at a sample of rows and refuses such a graph, as it does one
-// with a row too long for one wave or with too few workgroups to hold the keys,
-// and the caller's other form solves it. The members are those that run when the solve starts, so no launch waits
+// with a row too long for one wave, with many edges between the strips of a graph
+// that is no mesh, or with too few workgroups to hold the keys, and the caller's
+// other form solves it. The members are those that run when the solve starts, so no launch waits
 // for good for workgroups that other launches keep from running.
 //
 // A set q bit. In LDS it says that the vertex is in the strip's list (or, beyond
@@ -96,6 +97,8 @@ struct StripArgs {
     BQ_GLOBAL unsigned* par;   // [n] parents of vertices when last relaxed, for the walks
     BQ_GLOBAL const unsigned* longp;  // per weight-range partial: longest row (note_row)
     unsigned max_row;          // longest row that it takes
+    unsigned max_cross;        // edges between strips, of 1,024, that it takes where
+                               // neighbourhoods grow fast
     unsigned want;             // members at most
 };
 
@@ -117,7 +120,9 @@ struct StripLds {
     unsigned stop;       // number of the last step, plus one
     unsigned long long go;
     unsigned rank;
-    unsigned rows, far, lrow;  // the first workgroup's sample, and the longest row
+    // the first workgroup's sample: edges, those beyond the next strip and those
+    // out of their own, the longest row; and what its probes found (strip_probe)
+    unsigned rows, far, cross, lrow, ring4, ring5, dense;
     int wr[16][2];
     unsigned long long stats[bq::ST_N];
 };
@@ -171,6 +176,20 @@ inline bool strip_shape(long long n, long long m, long long workgroups) {
 // 2.1 / 5.2, 32,000 1.81 / 1.57 / 4.7, 128,000 4.1 / 1.3 / 4.4.
 inline unsigned strip_row_sweeps(long long n) { return (unsigned)(n / 128); }
 constexpr unsigned STRIP_ROW_QUEUE = 65536;
+
+// Edges out of a strip, of 1,024, that strips take from a graph whose
+// neighbourhoods grow like a tree's and not like a mesh's (strip_probe): there a
+// step holds thousands of vertices, few strips are busy at a time, and a good
+// part of a strip's work is messages. Such graphs of n vertices with edges to
+// random ids within K, of out-degree g, ms in strips / in sweeps / by the queue
+// solver: n = 1M, g = 3, K = 300 (2 % of the edges leave the strip) 19 / 59 / 28,
+// 1,000 (6 %) 18 / 18 / 8.7, 2,000 (12 %) 21 / 9.9 / 4.6, 8,000 21 / 2.5 / 1.9; g = 5.5,
+// 300 39 / 81 / 34, 1,000 39 / 28 / 11; n = 30,000, g = 5.5, 2,000 (7 %) 1.6 / 0.38 /
+// 2.1, 4,000 (13 %) 1.8 / 0.32 / 2.0, 8,000 (27 %) 3.1 / 0.29 / 2.0. A 256 x 4,096
+// mesh, 25 % of whose edges leave their strip, takes 19 / 108 / 51. From 3/8 on
+// strips lose on all.
+constexpr unsigned STRIP_CROSS_SWEEPS = 82;
+inline unsigned strip_cross_queue(long long n) { return n < 65536 ? 146u : 16u; }
 
 // Words of a new solve, by threads tid of `threads`: rings and parents of
 // vertices [v0, v1); with `first` the control words and the rings' rest.
@@ -228,6 +247,74 @@ __device__ __forceinline__ void strip_stop_all(const StripArgs& p, unsigned memb
                               __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Vertices 4 and 5 edges away from a sample vertex of this wave, added to S.ring4
+// and S.ring5 (8 edges of a row at most), or S.dense, if they are too many for
+// the wave's part of the keys' array, which is not in use yet. The fifth ring of a
+// plane mesh has 1.2 times the fourth's vertices, of a 3-dimensional grid 1.5, of
+// random ids within a band twice and more until the band is full. Five pairs
+// of dependent loads, 10 us.
+__device__ __forceinline__ void strip_probe(const SolveArgs& a, StripLds& S, unsigned wid) {
+    constexpr unsigned SET = 1024, LIST = 512;
+    static_assert(sizeof(S.key) >= STRIP_WAVES * (SET + 2 * LIST) * sizeof(unsigned), "");
+    const unsigned lane = (unsigned)bq::lane_id();
+    unsigned* set = (unsigned*)S.key + wid * (SET + 2 * LIST);
+    unsigned* cur = set + SET;
+    unsigned* nxt = cur + LIST;
+    const auto insert = [&](unsigned v) -> bool {  // whether it is new; never full
+        unsigned h = (v * 2654435761u) >> 22;
+        for (;;) {
+            const unsigned old = atomicCAS(&set[h], ~0u, v);
+            if (old == ~0u) return true;
+            if (old == v) return false;
+            h = (h + 1u) & (SET - 1u);
+        }
+    };
+    for (unsigned i = lane; i < SET; i += 64) set[i] = ~0u;
+    __builtin_amdgcn_wave_barrier();
+    if (lane == 0) {
+        cur[0] = (unsigned)((unsigned long long)a.n * (2u * wid + 1u) / (2u * STRIP_WAVES));
+        insert(cur[0]);
+    }
+    __builtin_amdgcn_wave_barrier();
+    unsigned nc = 1, seen = 1, ring[2] = {0u, 0u};
+    bool dense = false;
+    for (int hop = 1; hop <= 5 && !dense; ++hop) {
+        unsigned nn = 0;
+        for (unsigned b = 0; b < nc && !dense; b += 64) {
+            long long e = 0, e1 = 0;
+            if (b + lane < nc) {
+                const unsigned u = cur[b + lane];
+                e = a.off[u];
+                e1 = a.off[u + 1];
+            }
+            int c[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) c[j] = e + j < e1 ? a.col[e + j] : -1;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (seen + 64u > SET - 64u || nn + 64u > LIST) dense = true;  // wave-uniform
+                if (!dense) {
+                    const bool fresh = c[j] >= 0 && insert((unsigned)c[j]);
+                    const unsigned long long m = bq::ballot(fresh);
+                    if (fresh) nxt[nn + (unsigned)bq::rank_in(m)] = (unsigned)c[j];
+                    nn += (unsigned)__popcll(m);
+                    seen += (unsigned)__popcll(m);
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        unsigned* t = cur;
+        cur = nxt;
+        nxt = t;
+        nc = nn;
+        if (hop >= 4) ring[hop - 4] = nn;
+    }
+    if (lane != 0) return;
+    if (dense) atomicOr(&S.dense, 1u);
+    atomicAdd(&S.ring4, ring[0]);
+    atomicAdd(&S.ring5, ring[1]);
+}
+
 // The solve of one query by up to p.want workgroups that call it with the same
 // arguments (STRIP_WG threads each or more, `S` in LDS). Returns 1 when the query was
 // solved or stopped by those that took it, 0 when it is left to another form.
@@ -242,7 +329,7 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
     // ---- members ------------------------------------------------------------
     if (threadIdx.x == 0) {
         S.rank = (unsigned)bq::add_rlx(&ctl->joined.v, 1ull);
-        S.rows = S.far = S.lrow = 0u;
+        S.rows = S.far = S.cross = S.lrow = S.ring4 = S.ring5 = S.dense = 0u;
         if (S.rank == 0) {
             // The others get 10 us; as many as hold the keys get up to 20 us each,
             // which other launches on the chip may take to end, times 1 to 4,
@@ -269,11 +356,12 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
         const unsigned v =
             (unsigned)((unsigned long long)a.n * threadIdx.x / blockDim.x);
         long long e = a.off[v], e1 = a.off[v + 1];
-        unsigned rows = 0, far = 0;
+        unsigned rows = 0, far = 0, cross = 0;
         for (int k = 0; k < 8 && e < e1; ++k, ++e) {
             const long long d = (long long)a.col[e] - (long long)v;
             ++rows;
             far += (d < 0 ? -d : d) > (long long)per0;
+            cross += (unsigned)a.col[e] / per0 != v / per0;
         }
         unsigned lrow = 0;
         const int parts = (int)bq::ld_rlx(&a.q.ctrl->aux[0].v);
@@ -281,11 +369,17 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
             lrow = p.longp[i] > lrow ? p.longp[i] : lrow;
         atomicAdd(&S.rows, rows);
         atomicAdd(&S.far, far);
+        atomicAdd(&S.cross, cross);
         atomicMax(&S.lrow, lrow);
         __syncthreads();
+        bool ok = per0 <= STRIP_MAX_N && S.far * 16u <= S.rows && S.lrow <= p.max_row &&
+                  S.cross * 8u <= S.rows * 3u;
+        if (ok && __builtin_expect(S.cross * 1024u > S.rows * p.max_cross, 0)) {
+            if (wid < (unsigned)STRIP_WAVES) strip_probe(a, S, wid);
+            __syncthreads();
+            ok = S.dense == 0u && S.ring5 * 10u <= S.ring4 * 17u;
+        }
         if (threadIdx.x == 0) {
-            const bool ok =
-                per0 <= STRIP_MAX_N && S.far * 16u <= S.rows && S.lrow <= p.max_row;
             S.go = ok ? (unsigned long long)m0 : STRIP_REFUSED;
             bq::st_rlx(&ctl->go.v, S.go);
         }

@@ -67,6 +67,40 @@ def test_stars(n, launch, wg_size):
           launch, wg_size)
 
 
+def band(n, reach, degree, seed):
+    """Edges to random ids within `reach`."""
+    rng = np.random.default_rng(seed)
+    s = rng.integers(0, n, int(n * degree))
+    t = np.clip(s + rng.integers(-reach, reach + 1, s.size), 0, n - 1)
+    return synth.csr_from_edges(n, s, t, rng.integers(1, 1001, s.size), source=n // 2)
+
+
+@pytest.mark.parametrize("n,reach,degree,launch,wg_size", [
+    (100_000, 300, 3, None, STRIP), (100_000, 1000, 5.5, None, STRIP),
+    (100_000, 2000, 3, None, SWEEP), (100_000, 4000, 5.5, None, SWEEP),
+    (100_000, 100, 3, {"bucket_width": 4}, STRIP), (100_000, 1000, 3, {"bucket_width": 4}, QUEUE),
+    (30_000, 2000, 3, {"bucket_width": 4}, STRIP), (30_000, 8000, 3, {"bucket_width": 4}, QUEUE),
+    (200_000, 8000, 1.5, None, SWEEP)], ids=str)
+def test_ids_within_a_band(n, reach, degree, launch, wg_size):
+    # the more edges leave a strip, where neighbourhoods grow fast, the worse
+    check(band(n, reach, degree, n + reach), launch, wg_size)
+
+
+@pytest.mark.parametrize("launch", [None, {"bucket_width": 4}], ids=str)
+@pytest.mark.parametrize("dims", [(20, 4096), (8, 64, 64), (4096, 20), (30, 31, 32)], ids=str)
+def test_meshes_whose_edges_leave_the_strips(dims, launch):
+    # a quarter of a strip's edges and more lead out of it, but rings grow slowly
+    i = np.arange(np.prod(dims)).reshape(dims)
+    s, t = [], []
+    for axis in range(len(dims)):
+        a = np.take(i, np.arange(dims[axis] - 1), axis).ravel()
+        b = np.take(i, np.arange(1, dims[axis]), axis).ravel()
+        s, t = s + [a, b], t + [b, a]
+    s, t = np.concatenate(s), np.concatenate(t)
+    w = np.random.default_rng(39).integers(1, 1001, s.size)
+    check(synth.csr_from_edges(i.size, s, t, w, source=i.size // 2), launch, STRIP)
+
+
 def test_other_graphs():
     assert check(synth.potential_random(2000, 16000, seed=32), {"wg_count": 9}, SWEEP) == 1
     assert check(synth.potential_random(20000, 160000, seed=33), {"wg_count": 9}, SWEEP) == 9
