@@ -92,8 +92,8 @@ __global__ __launch_bounds__(SOLVE_WG_ONE, SSSP_MIN_WAVES) void k_solve_short(So
 }
 
 // k_init's work (keys, weight range, control words) for the sweep form: also
-// finds whether a row is longer than C, clears the stamps of such rows, and
-// puts the source into the first buffer.
+// notes the longest row, clears the stamps of rows longer than C, and puts the
+// source into the first buffer.
 __global__ __launch_bounds__(INIT_WG) void k_sweep_init(SolveArgs a, SweepArgs f, int* wrange) {
     const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long stride = (long long)gridDim.x * blockDim.x;
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(SWEEP_WG) void k_sweep(SolveArgs a, SweepArgs f) {
 }
 
 // The words of a strip solve whose query falls to the asynchronous solver if
-// the strip form refuses it.
+// the strip form refuses it, and the longest row.
 __global__ __launch_bounds__(INIT_WG) void k_strip_init(StripArgs p, const long long* off, int n,
                                                         unsigned* longp) {
     const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
