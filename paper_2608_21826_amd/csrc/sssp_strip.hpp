@@ -801,14 +801,16 @@ __device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& 
                 if (end && was_end && __all(same)) strip_stop_all(p, members);
                 was_end = end;
             } else if (pending && step >= SWEEP_WALK_FROM) {
-                // ---- negative cycles: a step on the parents at a time -------
+                // ---- negative cycles: some moves on the parents a step ------
                 int hit = -1;
                 if (!walk.on && now.cnt != 0u) {  // (the list's start holds whatever is over)
                     const unsigned q = now.cnt < STRIP_LIST ? now.cnt : STRIP_LIST;
                     walk.start(base + (unsigned)bq::bcast32((int)S.list[b0][step % q]), parent);
                     ++st.walk;
                 } else if (walk.on) {
-                    hit = walk.advance(a, parent, 1u);
+                    // moves that the step's own work leaves time for
+                    const unsigned more = now.cnt >> 7;
+                    hit = walk.advance(a, parent, 1u + (more < 31u ? more : 31u));
                 }
                 if (hit >= 0) {
                     if (lane == 0) bq::st_rlx(&a.q.ctrl->negcycle.v, 1ull);

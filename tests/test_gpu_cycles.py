@@ -4,6 +4,7 @@ the cycle and of the rows on it."""
 import numpy as np
 import pytest
 
+import oracle
 import synth
 
 from test_gpu_strip import mesh
@@ -104,3 +105,26 @@ def test_a_short_cycle_under_a_crowded_strip(at, neg_inf, launch):
     g = synth.csr_from_edges(g.n + 1, np.append(s, g.n), np.append(t, 0), np.append(x, -10**6),
                              source=at)
     check(g, neg_inf, launch)
+
+
+@pytest.mark.parametrize("launch", [{}, {"bucket_width": 4}], ids=str)
+@pytest.mark.parametrize("neg_inf", [False, True])
+def test_a_long_cycle_among_thousands_of_queued_vertices(neg_inf, launch):
+    # one strip whose steps hold thousands of vertices: with a move a step a walk goes
+    # round this cycle in some hundred ms, and the solve may take 40
+    rng = np.random.default_rng(52)
+    n, m, length = 15_000, 57_000, 2000
+    s, t, w = rng.integers(0, n, m), rng.integers(0, n, m), rng.integers(1, 1001, m)
+    p = rng.integers(0, 1001, n)
+    c = 3000 + np.arange(length)
+    s, t, w = np.append(s, c), np.append(t, np.roll(c, -1)), np.append(w, np.full(length, -1))
+    g = synth.csr_from_edges(n, s, t, w + p[s] - p[t], source=int(s[0]))
+    csr = [torch.from_numpy(x).to(DEV) for x in (g.offsets, g.cols, g.w)]
+    ctx = pkg.SsspContext(g.n, g.m)
+    ref = oracle.neg_inf(g, g.src)[0] if neg_inf else None
+    for _ in range(3):
+        d, _, neg = ctx.solve(*csr, g.src, launch={**launch, "timeout_us": 4000}, neg_inf=neg_inf)
+        assert neg
+        assert ctx.stats()["wg_size"] == 768
+        assert not neg_inf or np.array_equal(d.cpu().numpy(), ref)
+    ctx.close()
