@@ -318,7 +318,8 @@ __device__ __forceinline__ void strip_probe(const SolveArgs& a, StripLds& S, uns
 // The solve of one query by up to p.want workgroups that call it with the same
 // arguments (STRIP_WG threads each or more, `S` in LDS). Returns 1 when the query was
 // solved or stopped by those that took it, 0 when it is left to another form.
-__device__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& S, WaveStats& st) {
+__device__ __forceinline__ int strip_instance(const SolveArgs& a, const StripArgs& p, StripLds& S,
+                                              WaveStats& st) {
     const unsigned lane = (unsigned)bq::lane_id();
     const unsigned wid = (unsigned)bq::bcast32(threadIdx.x >> 6);
     const unsigned shift = a.shift;

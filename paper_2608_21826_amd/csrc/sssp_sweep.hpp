@@ -103,6 +103,8 @@ struct SweepLds {
     unsigned long long base;
     unsigned long long go;
     unsigned rank;
+    int walk_hit;        // gang_walk: a vertex of a negative cycle, or -1
+    unsigned walk_over;  // gang_walk: the solve is over
 };
 
 __device__ __forceinline__ void sweep_stop(const SweepArgs& f) {
@@ -156,6 +158,43 @@ __device__ bool gang_join(const SolveArgs& a, const SweepArgs& f, unsigned want,
     return in;
 }
 
+// A member's arrival after its sweep and its wait for the next one, by one
+// thread: the next value of `go`.
+__device__ unsigned long long gang_meet(const SolveArgs& a, const SweepArgs& f, const SweepGang& g,
+                                        unsigned long long t_start) {
+    BQ_GLOBAL SweepCtl* c = f.ctl;
+    const unsigned grp = g.rank & 7u;
+    const unsigned ng = g.members < 8u ? g.members : 8u, gs = (g.members + 7u - grp) >> 3;
+    const unsigned next = g.sweep + 1u;
+    if (atomicInc((unsigned*)&c->arrive[grp].v, gs - 1u) == gs - 1u) {
+        const unsigned long long j = bq::ld_rlx(&c->joined.v);
+        if (atomicInc((unsigned*)&c->root.v, ng - 1u) == ng - 1u) {
+            const unsigned m = (unsigned)j > g.members ? (unsigned)j : g.members;
+            __hip_atomic_fetch_max(&c->go.v, ((unsigned long long)next << 32) | m,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    const unsigned long long t0 = bq::now_ticks();
+    unsigned long long go;
+    for (unsigned it = 1;; ++it) {
+        go = bq::ld_rlx(&c->go.v);
+        if ((unsigned)(go >> 32) >= next) break;
+        if ((it & 63u) == 0u) {
+            const unsigned long long t = bq::now_ticks();
+            if (t - t0 > a.limit || t - t_start > a.deadline) {
+                bq::raise_error(a.q, bq::ERR_TIMEOUT);
+                sweep_stop(f);
+            }
+        }
+    }
+    if (go != SWEEP_STOP && bq::now_ticks() - t_start > a.deadline) {
+        bq::raise_error(a.q, bq::ERR_TIMEOUT);
+        sweep_stop(f);
+        go = SWEEP_STOP;
+    }
+    return go;
+}
+
 // The members meet after a sweep; returns false when the solve was stopped,
 // else g is the next sweep with the members it has. Arrivals go to one
 // self-resetting word per rank mod 8, the last of a group arrives at the root,
@@ -169,39 +208,7 @@ __device__ bool gang_barrier(const SolveArgs& a, const SweepArgs& f, SweepGang& 
                              SweepLds<WAVES>& S, unsigned long long t_start) {
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) {
-        BQ_GLOBAL SweepCtl* c = f.ctl;
-        const unsigned grp = g.rank & 7u;
-        const unsigned ng = g.members < 8u ? g.members : 8u, gs = (g.members + 7u - grp) >> 3;
-        const unsigned next = g.sweep + 1u;
-        if (atomicInc((unsigned*)&c->arrive[grp].v, gs - 1u) == gs - 1u) {
-            const unsigned long long j = bq::ld_rlx(&c->joined.v);
-            if (atomicInc((unsigned*)&c->root.v, ng - 1u) == ng - 1u) {
-                const unsigned m = (unsigned)j > g.members ? (unsigned)j : g.members;
-                __hip_atomic_fetch_max(&c->go.v, ((unsigned long long)next << 32) | m,
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        const unsigned long long t0 = bq::now_ticks();
-        unsigned long long go;
-        for (unsigned it = 1;; ++it) {
-            go = bq::ld_rlx(&c->go.v);
-            if ((unsigned)(go >> 32) >= next) break;
-            if ((it & 63u) == 0u) {
-                const unsigned long long t = bq::now_ticks();
-                if (t - t0 > a.limit || t - t_start > a.deadline) {
-                    bq::raise_error(a.q, bq::ERR_TIMEOUT);
-                    sweep_stop(f);
-                }
-            }
-        }
-        if (go != SWEEP_STOP && bq::now_ticks() - t_start > a.deadline) {
-            bq::raise_error(a.q, bq::ERR_TIMEOUT);
-            sweep_stop(f);
-            go = SWEEP_STOP;
-        }
-        S.go = go;
-    }
+    if (threadIdx.x == 0) S.go = gang_meet(a, f, g, t_start);
     __syncthreads();
     g.members = (unsigned)S.go;
     ++g.sweep;
@@ -356,12 +363,96 @@ __device__ __forceinline__ SweepSlot sweep_slot(unsigned nseg, unsigned pre, uns
     return SweepSlot{seg, g - first};
 }
 
+// Whether the member of rank 1 walks for good (gang_walk). A solve that has so
+// many sweeps has a long chain of steps, where a member less costs little, or a
+// negative cycle. (RMAT and random graphs take 15 to 30 sweeps.)
+__device__ __forceinline__ bool gang_walks(const SweepGang& g) {
+    const unsigned from = g.members >= 64u ? 64u : (g.members >= 8u ? 512u : 4096u);
+    return g.members >= 2u && g.sweep >= from;
+}
+
+// The member that searches for negative cycles while the others sweep. Its first
+// wave meets them at every sweep, at once, with nothing done; the others walk
+// from vertices drawn at random and wait for nobody. A few moves a sweep are
+// enough to close a short cycle, but a sweep of a wide queue takes as long as a
+// hundred moves, and on long cycles the parents changed before such a walk was
+// round: random graphs of 15k to 400k vertices with a cycle of 2,000 to 8,000
+// vertices took 3 to 850 ms, with it 1 to 7. (A random graph of 200k vertices takes
+// 439 us for 432: its 20 sweeps end before this, but the loop has more to hold.
+// Called instead of inlined it took 546.)
+template <int WAVES>
+__device__ __forceinline__ void gang_walk(const SolveArgs& a, const SweepArgs& f, SweepGang& g,
+                                          SweepLds<WAVES>& S, unsigned wid, unsigned home,
+                                          bool long_rows, WaveStats& st,
+                                          unsigned long long t_start) {
+    const int lane = bq::lane_id();
+    SweepWave& L = S.w[wid];
+    if (threadIdx.x == 0) {
+        S.walk_hit = -1;
+        S.walk_over = 0u;
+    }
+    __syncthreads();
+    if (wid == 0u) {
+        bool flagged = false;
+        for (;;) {
+            int hit = -1;
+            if (lane == 0) hit = atomicExch(&S.walk_hit, -1);
+            hit = (int)bq::bcast32((unsigned)hit);
+            if (hit >= 0) {
+                if (lane == 0 && !flagged) bq::st_rlx(&a.q.ctrl->negcycle.v, 1ull);
+                flagged = true;
+                if (!a.neginf) {
+                    if (lane == 0) {
+                        bq::st_rlx(&a.q.ctrl->abort.v, 1ull);
+                        sweep_stop(f);
+                    }
+                } else {
+                    // a mark is published before this member meets the others
+                    long long old = 0;
+                    if (lane == 0)
+                        old = __hip_atomic_fetch_min(&a.key[hit], KEY_NEG, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+                    old = (long long)bq::bcast64((unsigned long long)old);
+                    if (KEY_NEG < old && (old & 1ll) == 0) {
+                        if (lane == 0) L.out[0] = (unsigned)hit;
+                        sweep_publish(a, f, L, 1, g.sweep + 1u, home, long_rows, st);
+                    }
+                }
+            }
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            unsigned long long go = 0;
+            if (lane == 0) go = gang_meet(a, f, g, t_start);
+            go = bq::bcast64(go);
+            if (go == SWEEP_STOP) break;
+            g.members = (unsigned)go;
+            ++g.sweep;
+        }
+        if (lane == 0)
+            __hip_atomic_store(&S.walk_over, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else {
+        const auto parent = [&](unsigned x) { return parent_of(a, (int)x); };
+        SweepWalk<true> walk{};
+        unsigned draw = wid * 0x9E3779B9u + g.sweep;
+        while (__hip_atomic_load(&S.walk_over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) ==
+               0u) {
+            if (!walk.on) {
+                draw = draw * 1664525u + 1013904223u;
+                walk.start((unsigned)(((unsigned long long)draw * (unsigned)a.n) >> 32), parent);
+                ++st.walk;
+            }
+            const int hit = walk.advance(a, parent, 32u, &L.walk);
+            if (hit >= 0 && lane == 0) atomicExch(&S.walk_hit, hit);
+        }
+    }
+    __syncthreads();
+}
+
 // One gang's solve of one query; up to `want` workgroups call it with the same
 // arguments. Returns 1 when the queue ran empty, -1 when the solve was stopped
 // (error or negative cycle) or over before this workgroup joined.
 template <int WAVES>
-__device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned want,
-                              SweepLds<WAVES>& S, WaveStats& st) {
+__device__ __forceinline__ int sweep_instance(const SolveArgs& a, const SweepArgs& f,
+                                              unsigned want, SweepLds<WAVES>& S, WaveStats& st) {
     const int lane = bq::lane_id();
     const unsigned wid = (unsigned)bq::bcast32(threadIdx.x >> 6);
     SweepWave& L = S.w[wid];
@@ -424,10 +515,12 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned w
     int result = -1;
 
     while (true) {
-        const unsigned it = g.sweep, W = g.members * WAVES;
+        const unsigned it = g.sweep;
+        const bool walks = gang_walks(g);
+        const unsigned workers = g.members - (walks ? 1u : 0u), W = workers * WAVES;
         // consecutive batches go to different workgroups, so a short sweep
         // spreads over the gang's CUs
-        const unsigned gw = wid * g.members + g.rank;
+        const unsigned gw = wid * workers + g.rank - (walks && g.rank > 1u ? 1u : 0u);
         // ---- the sweep's items, by segment ------------------------------
         unsigned long long tw = 0;
         if ((unsigned)lane < a.nseg) tw = bq::ld_rlx(&f.ctl->tail[it % 3u][lane].v);
@@ -443,6 +536,10 @@ __device__ int sweep_instance(const SolveArgs& a, const SweepArgs& f, unsigned w
         if (NL + NC == 0u) {
             if (g.rank == 0 && threadIdx.x == 0) sweep_stop(f);  // nobody joins any more
             result = 1;
+            break;
+        }
+        if (walks && g.rank == 1u) {
+            gang_walk<WAVES>(a, f, g, S, wid, home, long_rows, st, t_start);
             break;
         }
         // the buffer after next is empty; its words were last read before the

@@ -3,6 +3,8 @@ are flagged (or marked) within the launch's time limits, whatever the length of
 the cycle and of the rows on it."""
 import numpy as np
 import pytest
+from scipy.sparse import csr_matrix
+from scipy.sparse.csgraph import breadth_first_order
 
 import oracle
 import synth
@@ -128,3 +130,45 @@ def test_a_long_cycle_among_thousands_of_queued_vertices(neg_inf, launch):
         assert ctx.stats()["wg_size"] == 768
         assert not neg_inf or np.array_equal(d.cpu().numpy(), ref)
     ctx.close()
+
+
+def hidden_cycle(n, deg, length, seed):
+    """A random graph with a cycle of weight -`length` through random vertices, the
+    source on it; a random potential hides which edges are negative. Also the marked
+    labels: all that the source reaches are on no shortest path."""
+    rng = np.random.default_rng(seed)
+    s, t, w = (rng.integers(0, n, n * deg), rng.integers(0, n, n * deg),
+               rng.integers(1, 1001, n * deg))
+    p = rng.integers(0, 1001, n)
+    c = rng.permutation(n)[:length]
+    s, t, w = np.append(s, c), np.append(t, np.roll(c, -1)), np.append(w, np.full(length, -1))
+    g = synth.csr_from_edges(n, s, t, w + p[s] - p[t], source=int(c[0]))
+    rows = csr_matrix((np.ones(g.m), g.cols, g.offsets), shape=(n, n))
+    ref = np.full(n, np.iinfo(np.int64).max)
+    ref[breadth_first_order(rows, g.src, return_predecessors=False)] = MINUS_INF
+    return g, ref
+
+
+def check_hidden(g, ref, neg_inf, timeout_us, wg_size):
+    csr = [torch.from_numpy(x).to(DEV) for x in (g.offsets, g.cols, g.w)]
+    ctx = pkg.SsspContext(g.n, g.m)
+    for _ in range(3):
+        d, _, neg = ctx.solve(*csr, g.src, launch={"timeout_us": timeout_us}, neg_inf=neg_inf)
+        assert neg
+        assert ctx.stats()["wg_size"] == wg_size
+        assert not neg_inf or np.array_equal(d.cpu().numpy(), ref)
+    ctx.close()
+    d = torch.empty(g.n, dtype=torch.int64, device=DEV)
+    p = torch.empty(g.n, dtype=torch.int32, device=DEV)
+    batch = pkg.SsspBatch(1, g.n, g.m)
+    flags = pkg.BQ_F_NEGINF if neg_inf else 0
+    assert batch.solve([(*csr, g.src, d, p)], launch={"timeout_us": timeout_us, "flags": flags})[0]
+    assert not neg_inf or np.array_equal(d.cpu().numpy(), ref)
+    batch.close()
+
+
+@pytest.mark.parametrize("neg_inf", [False, True])
+def test_a_long_cycle_under_wide_sweeps(neg_inf):
+    # a walk with a few moves a sweep went round this cycle in 260 to 620 ms; the
+    # solve may take 80
+    check_hidden(*hidden_cycle(15_000, 8, 8000, 53), neg_inf, 8000, 1024)
