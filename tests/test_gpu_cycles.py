@@ -172,3 +172,9 @@ def test_a_long_cycle_under_wide_sweeps(neg_inf):
     # a walk with a few moves a sweep went round this cycle in 260 to 620 ms; the
     # solve may take 80
     check_hidden(*hidden_cycle(15_000, 8, 8000, 53), neg_inf, 8000, 1024)
+
+
+@pytest.mark.parametrize("neg_inf", [False, True])
+def test_a_long_cycle_in_one_workgroup(neg_inf):
+    # 27 to 650 ms with a few moves a sweep; the solve may take 20
+    check_hidden(*hidden_cycle(8000, 5, 2000, 54), neg_inf, 2000, 1024)
