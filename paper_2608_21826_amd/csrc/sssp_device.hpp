@@ -500,7 +500,9 @@ __device__ int walk_finds_negative_cycle(const SolveArgs& a, int x0, unsigned bu
 // finding), a few steps per sweep beside the other waves' round trips, so the
 // search delays no sweep and runs from the start: a cycle whose vertices
 // improve nothing else keeps sweeps of a few items going, which a search that
-// waits for an amount of work finds only after millions of them. In a gang (GANG)
+// waits for an amount of work finds only after millions of them. Cycles of
+// thousands of vertices need more moves before their parents change: gang_walk,
+// and the walk of k_small that the others wait for. In a gang (GANG)
 // the sum of a walk that has closed is shared out over sweeps too: the other
 // workgroups wait for the walker at the sweep's barrier, and no longer than the
 // launch's limit for one wait. Parents may change between two parts of a sum;
@@ -509,6 +511,7 @@ __device__ int walk_finds_negative_cycle(const SolveArgs& a, int x0, unsigned bu
 constexpr unsigned SWEEP_WALKERS = 4;
 constexpr unsigned SWEEP_WALK_FROM = 8;   // first sweep
 constexpr unsigned SWEEP_WALK_STEPS = 4;  // per sweep
+constexpr int SWEEP_WALK_LONG = 512;      // times as many for a long walk
 // Parts of up to 512 edges of a row that a walker sums per sweep, 0.8 us each: as
 // long a stay away as the barrier bears easily, and so many that the walks
 // of up to as many steps, which are the ordinary ones, are summed at once.

@@ -378,7 +378,7 @@ __device__ __forceinline__ bool gang_walks(const SweepGang& g) {
 // hundred moves, and on long cycles the parents changed before such a walk was
 // round: random graphs of 15k to 400k vertices with a cycle of 2,000 to 8,000
 // vertices took 3 to 850 ms, with it 1 to 7. (A random graph of 200k vertices takes
-// 439 us for 432: its 20 sweeps end before this, but the loop has more to hold.
+// 439 us for 432: its 29 sweeps end before this, but the loop has more to hold.
 // Called instead of inlined it took 546.)
 template <int WAVES>
 __device__ __forceinline__ void gang_walk(const SolveArgs& a, const SweepArgs& f, SweepGang& g,
@@ -512,6 +512,7 @@ __device__ __forceinline__ int sweep_instance(const SolveArgs& a, const SweepArg
     const unsigned home = g.rank % a.nseg;
     SweepWalk<true> walk{};
     bool flagged = false;  // marking mode: this wave already raised negcycle
+    long long to_long = 16ll * a.n;  // items to the next long walk
     int result = -1;
 
     while (true) {
@@ -677,6 +678,20 @@ __device__ __forceinline__ int sweep_instance(const SolveArgs& a, const SweepArg
         // ---- negative-cycle search ---------------------------------------
         if (gw + SWEEP_WALKERS >= W && it >= SWEEP_WALK_FROM && ok) {
             const auto parent = [&](unsigned x) { return parent_of(a, (int)x); };
+            // a few moves a sweep; in a small gang, whose sweeps are long, after
+            // 16 n items one walk at up to 2,048 moves a sweep (1.5 ms) until it ends,
+            // while the others wait: 64 random graphs of 15k vertices with a cycle of
+            // 2,000 took 150 ms, with this 5.4, 256 of them 550 and 20; 64 permuted
+            // meshes of 300 x 300 (22 n items each) 28.1 and 28.4
+            int rounds = 1;
+            if (g.members < 64u) {
+                const bool first = to_long >= 0;
+                to_long -= (long long)NL + NC;
+                if (to_long < 0) {
+                    rounds = SWEEP_WALK_LONG;
+                    walk.on = walk.on && !first;
+                }
+            }
             if (!walk.on) {
                 const unsigned k = (it + gw) % (NL > 0 ? NL : NC);
                 const SweepSlot at = sweep_slot(a.nseg, NL > 0 ? pre_l : pre_c, k);
@@ -686,7 +701,12 @@ __device__ __forceinline__ int sweep_instance(const SolveArgs& a, const SweepArg
                     parent);
                 ++st.walk;
             }
-            const int hit = walk.advance(a, parent, SWEEP_WALK_STEPS, &L.walk);
+            int hit;
+            do {
+                hit = walk.advance(a, parent, SWEEP_WALK_STEPS, &L.walk);
+                rounds -= walk.left != 0u ? (int)SWEEP_WALK_SUMS / (int)SWEEP_WALK_STEPS : 1;
+            } while (walk.on && rounds > 0);
+            if (to_long < 0 && !walk.on) to_long = 16ll * a.n;
             if (hit >= 0) {
                 if (lane == 0 && !flagged) bq::st_rlx(&a.q.ctrl->negcycle.v, 1ull);
                 flagged = true;

@@ -178,3 +178,22 @@ def test_a_long_cycle_under_wide_sweeps(neg_inf):
 def test_a_long_cycle_in_one_workgroup(neg_inf):
     # 27 to 650 ms with a few moves a sweep; the solve may take 20
     check_hidden(*hidden_cycle(8000, 5, 2000, 54), neg_inf, 2000, 1024)
+
+
+@pytest.mark.parametrize("count,timeout_us", [(64, 5000), (256, 20_000)])
+@pytest.mark.parametrize("neg_inf", [False, True])
+def test_long_cycles_in_a_batch_of_small_gangs(count, timeout_us, neg_inf):
+    # four workgroups each or one: 150 ms and 550 with a few moves a sweep; the solve
+    # may take ten times the limit
+    g, ref = hidden_cycle(15_000, 8, 2000, 55)
+    csr = [torch.from_numpy(x).to(DEV) for x in (g.offsets, g.cols, g.w)]
+    outs = [(torch.empty(g.n, dtype=torch.int64, device=DEV),
+             torch.empty(g.n, dtype=torch.int32, device=DEV)) for _ in range(count)]
+    batch = pkg.SsspBatch(count, count * g.n, count * g.m)
+    flags = pkg.BQ_F_NEGINF if neg_inf else 0
+    # each query's graph is its own
+    neg = batch.solve([(*[x.clone() for x in csr], g.src, d, p) for d, p in outs],
+                      launch={"timeout_us": timeout_us, "flags": flags})
+    assert all(neg)
+    assert not neg_inf or all(np.array_equal(d.cpu().numpy(), ref) for d, _ in outs)
+    batch.close()
